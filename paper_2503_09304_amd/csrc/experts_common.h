@@ -26,7 +26,7 @@ struct KArgs {
     const int32_t *stop;      // [host memory mapped into the device] the context's stop word
     int32_t *cnt_self;        // [device] workgroups of this kernel that ran, per row range, indexed by its first sorted row
     const int32_t *cnt_need;  // down projection: the gate-up kernel's counters (the activation rows must be complete)
-    int need;                 // gate-up workgroups per 64-row tile (fp32) or per row range (bf16) that make them complete
+    int need;                 // gate-up workgroups per 32-row tile (fp32) or per row range (bf16) that make them complete
 };
 
 // Entry protocol of a workgroup of a stoppable launch; the same answer for every thread of the

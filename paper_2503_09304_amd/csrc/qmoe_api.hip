@@ -441,75 +441,59 @@ static int32_t launch_unit_list(moe_ctx *ctx, const void *x, const moe_weights *
     bool contiguous = true;                       // ids = u0, u0+1, ..., a range of the device unit list
     for (size_t i = 1; i < ids.size(); ++i) contiguous = contiguous && ids[i] == ids[i - 1] + 1;
     hipError_t e = hipSuccess;
-    if (ctx->cfg.dtype == MOE_BF16) {
-        // Row segments: units sorted by (expert, row), row-adjacent units of one expert (its LS part
-        // and the start of its BE part, or consecutive chunks) merged while they fit 256 rows, so
-        // that one pass over the expert's weights serves them all.  Which rows share a workgroup
-        // never changes what is computed for a row.
-        std::vector<uint32_t> idx(ids);
-        std::stable_sort(idx.begin(), idx.end(), [un](uint32_t p, uint32_t q) {
-            if (un[p].expert != un[q].expert) return un[p].expert < un[q].expert;
-            return un[p].row0 < un[q].row0;
-        });
-        // First the runs of row-adjacent units of one expert, then each run cut into ceil(rows/256)
-        // segments of (nearly) equal numbers of 32-row tiles: workgroups that share an expert's weight
-        // tiles then advance through K at the same pace and meet in L2, which a 256/256/256/128 cut
-        // does not give them.
-        struct Run { uint32_t row0, rows; uint16_t expert; };
-        std::vector<Run> runs;
-        for (uint32_t i : idx) {
-            const moe_unit &u = un[i];
-            if (!runs.empty() && runs.back().expert == (uint16_t)u.expert && runs.back().row0 + runs.back().rows == (uint32_t)u.row0)
-                runs.back().rows += (uint32_t)u.rows;
-            else
-                runs.push_back(Run{(uint32_t)u.row0, (uint32_t)u.rows, (uint16_t)u.expert});
+    // Row segments: units sorted by (expert, row), row-adjacent units of one expert (its LS part
+    // and the start of its BE part, or consecutive chunks) merged while they fit 256 rows, so
+    // that one pass over the expert's weights serves them all.  Which rows share a workgroup
+    // never changes what is computed for a row.
+    std::vector<uint32_t> idx(ids);
+    std::stable_sort(idx.begin(), idx.end(), [un](uint32_t p, uint32_t q) {
+        if (un[p].expert != un[q].expert) return un[p].expert < un[q].expert;
+        return un[p].row0 < un[q].row0;
+    });
+    // First the runs of row-adjacent units of one expert, then each run cut into ceil(rows/256)
+    // segments of (nearly) equal numbers of 32-row tiles: workgroups that share an expert's weight
+    // tiles then advance through K at the same pace and meet in L2, which a 256/256/256/128 cut
+    // does not give them.
+    struct Run { uint32_t row0, rows; uint16_t expert; };
+    std::vector<Run> runs;
+    for (uint32_t i : idx) {
+        const moe_unit &u = un[i];
+        if (!runs.empty() && runs.back().expert == (uint16_t)u.expert && runs.back().row0 + runs.back().rows == (uint32_t)u.row0)
+            runs.back().rows += (uint32_t)u.rows;
+        else
+            runs.push_back(Run{(uint32_t)u.row0, (uint32_t)u.rows, (uint16_t)u.expert});
+    }
+    std::vector<qmoe::Seg> segs;
+    for (const Run &r : runs) {
+        const uint32_t nseg = (r.rows + 255) / 256, tiles = (r.rows + 31) / 32;
+        const uint32_t base = tiles / nseg, extra = tiles % nseg;
+        uint32_t row = r.row0, left = r.rows;
+        for (uint32_t j = 0; j < nseg; ++j) {
+            const uint32_t want = (base + (j < extra ? 1 : 0)) * 32;
+            const uint32_t take = want < left ? want : left;
+            segs.push_back(qmoe::Seg{row, (uint16_t)take, r.expert});
+            row += take;
+            left -= take;
         }
-        std::vector<qmoe::Seg> segs;
-        for (const Run &r : runs) {
-            const uint32_t nseg = (r.rows + 255) / 256, tiles = (r.rows + 31) / 32;
-            const uint32_t base = tiles / nseg, extra = tiles % nseg;
-            uint32_t row = r.row0, left = r.rows;
-            for (uint32_t j = 0; j < nseg; ++j) {
-                const uint32_t want = (base + (j < extra ? 1 : 0)) * 32;
-                const uint32_t take = want < left ? want : left;
-                segs.push_back(qmoe::Seg{row, (uint16_t)take, r.expert});
-                row += take;
-                left -= take;
-            }
-        }
-        if (segs.size() > (size_t)qmoe::kMaxSegs && contiguous) {
-            // too many segments for the kernel arguments: the launch reads the device unit list
-            if (ranges)
-                for (uint32_t i : ids) ranges->push_back(qmoe::Seg{(uint32_t)un[i].row0, (uint16_t)un[i].rows, (uint16_t)un[i].expert});
-            a.u0 = ids.front(); a.nu = (uint32_t)ids.size();
-            a.max_rows = 0;
-            for (uint32_t i : ids) a.max_rows = std::max(a.max_rows, (int)un[i].rows);
-            a.segs = nullptr; a.nseg = 0;
-            e = qmoe::launch_experts(a, stream);
-        } else {
-            if (ranges) ranges->insert(ranges->end(), segs.begin(), segs.end());
-            for (size_t s0 = 0; s0 < segs.size() && e == hipSuccess; s0 += qmoe::kMaxSegs) {
-                const size_t cnt = std::min(segs.size() - s0, (size_t)qmoe::kMaxSegs);
-                a.segs = segs.data() + s0; a.nseg = (int)cnt;
-                a.u0 = 0; a.nu = 0;
-                a.max_rows = 0;
-                for (size_t i = 0; i < cnt; ++i) a.max_rows = std::max(a.max_rows, (int)segs[s0 + i].rows);
-                e = qmoe::launch_experts(a, stream);
-            }
-        }
-    } else {
-        // fp32 kernels walk ranges of the device unit list: one launch per run of consecutive ids
+    }
+    if (segs.size() > (size_t)qmoe::kMaxSegs && contiguous) {
+        // too many segments for the kernel arguments: the launch reads the device unit list
         if (ranges)
             for (uint32_t i : ids) ranges->push_back(qmoe::Seg{(uint32_t)un[i].row0, (uint16_t)un[i].rows, (uint16_t)un[i].expert});
-        for (size_t i = 0; i < ids.size() && e == hipSuccess;) {
-            size_t j = i + 1;
-            while (j < ids.size() && ids[j] == ids[j - 1] + 1) ++j;
-            a.u0 = ids[i]; a.nu = (uint32_t)(j - i);
+        a.u0 = ids.front(); a.nu = (uint32_t)ids.size();
+        a.max_rows = 0;
+        for (uint32_t i : ids) a.max_rows = std::max(a.max_rows, (int)un[i].rows);
+        a.segs = nullptr; a.nseg = 0;
+        e = qmoe::launch_experts(a, stream);
+    } else {
+        if (ranges) ranges->insert(ranges->end(), segs.begin(), segs.end());
+        for (size_t s0 = 0; s0 < segs.size() && e == hipSuccess; s0 += qmoe::kMaxSegs) {
+            const size_t cnt = std::min(segs.size() - s0, (size_t)qmoe::kMaxSegs);
+            a.segs = segs.data() + s0; a.nseg = (int)cnt;
+            a.u0 = 0; a.nu = 0;
             a.max_rows = 0;
-            for (size_t q = i; q < j; ++q) a.max_rows = std::max(a.max_rows, (int)un[ids[q]].rows);
-            a.segs = nullptr; a.nseg = 0;
+            for (size_t i = 0; i < cnt; ++i) a.max_rows = std::max(a.max_rows, (int)segs[s0 + i].rows);
             e = qmoe::launch_experts(a, stream);
-            i = j;
         }
     }
     if (e != hipSuccess) return hip_fail(e, who);

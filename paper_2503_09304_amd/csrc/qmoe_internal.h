@@ -100,10 +100,12 @@ struct ExpertArgs {
     int32_t *cnt_gu, *cnt_dn;   // [device] workgroups that ran per row range (indexed by first sorted row): gate-up, down
 };
 
+constexpr int kF32RowTile = 32, kF32ColTile = 32;   // rows and output columns of a workgroup of the fp32 expert kernels
+
 // Workgroups of the down projection that cover a row range of `rows` rows: what its counter reads
 // when the range is complete.
 __host__ __device__ inline int down_wgs_of_range(int dtype, int H, int ksplit, int rows) {
-    return dtype == MOE_BF16 ? ((H + 255) / 256) * ksplit : ((H + 63) / 64) * ((rows + 63) / 64);
+    return dtype == MOE_BF16 ? ((H + 255) / 256) * ksplit : ((H + kF32ColTile - 1) / kF32ColTile) * ((rows + kF32RowTile - 1) / kF32RowTile);
 }
 hipError_t launch_experts(const ExpertArgs &a, hipStream_t s);
 
