@@ -1,7 +1,5 @@
 // bf16 expert path: launch dispatch, the plane reduction of the K-split down projection, and the
 // weight re-layout kernel.  The GEMM kernels themselves are the templates of experts_bf16_tile.h.
-#include <vector>
-
 #include "experts_bf16_tile.h"
 
 namespace qmoe {
@@ -147,52 +145,14 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
     b.ksplit = 1;
     b.plane = 0;
     b.nseg = a.segs ? a.nseg : 0;
-    if (b.nseg > 0) {
-        // Packets are groups of 4 consecutive segments.  Where an expert has several segments, its
-        // groups are padded with empty segments so that no packet spans two experts: the workgroups
-        // of a packet then share one set of weight tiles, fetched into that XCD's L2 once.
-        int n = 0;
-        bool shared = false;
-        for (int i = 1; i < a.nseg; ++i) shared = shared || a.segs[i].expert == a.segs[i - 1].expert;
-        if (shared) {
-            // experts in descending order of their rows in this launch (the order of experts is free:
-            // the busiest ones start first, the small ones fill the tail), each expert's segments
-            // kept together and in row order
-            struct Group { int first, count, rows; };
-            std::vector<Group> groups;
-            for (int i = 0; i < a.nseg; ++i) {
-                if (i == 0 || a.segs[i].expert != a.segs[i - 1].expert) groups.push_back(Group{i, 0, 0});
-                groups.back().count += 1;
-                groups.back().rows += a.segs[i].rows;
-            }
-            std::stable_sort(groups.begin(), groups.end(), [](const Group &x, const Group &y) { return x.rows > y.rows; });
-            for (const Group &g : groups) {
-                while ((n & ((1 << QMOE_PK_U) - 1)) && n < kMaxSegs) b.seg[n++] = Seg{0, 0, 0};
-                for (int i = g.first; i < g.first + g.count; ++i) {
-                    if (n < kMaxSegs) b.seg[n] = a.segs[i];
-                    ++n;
-                }
-                if (n > kMaxSegs) break;
-            }
-        }
-        if (!shared || n > kMaxSegs) {
-            std::copy(a.segs, a.segs + a.nseg, b.seg);
-            n = a.nseg;
-        }
-        b.nseg = n;
-    }
+    const bool stream = b.nseg > 0 && items_stream(a.segs, b.nseg);
+    if (b.nseg > 0) plan_items(a.segs, b.nseg, stream, b.seg);
     const int tiles = (a.max_rows + 31) / 32;
     const unsigned n = b.nseg > 0 ? (unsigned)b.nseg : a.nu;
-    // segments are sorted by expert: the weights are streamed once iff no two neighbours share one
-    bool stream = b.nseg > 0;
-    for (int i = 1; i < b.nseg; ++i) stream = stream && b.seg[i].expert != b.seg[i - 1].expert;
-    // With one segment per expert the order of the segments is free: longest first, so that the
-    // workgroups with the most tiles do not form the tail of the launch.
-    if (stream) std::stable_sort(b.seg, b.seg + b.nseg, [](const Seg &x, const Seg &y) { return x.rows > y.rows; });
-
     b.k = gu_in;
     b.k.cw = a.wave_cols ? a.wave_cols : gate_up_wave_columns(stream, a.wfmt, tiles, (int)n, a.F);
     b.k.col_tiles = (a.F + 4 * b.k.cw - 1) / (4 * b.k.cw);
+    b.items = n * (unsigned)b.k.col_tiles;
     auto launch = [&](bool gateup) {
         if (a.wfmt == bf16k::WF_MXFP4) bf16k::launch_expert_kernels<bf16k::WF_MXFP4>(gateup, tiles, stream, b, s);
         else if (a.wfmt == bf16k::WF_PACKED) bf16k::launch_expert_kernels<bf16k::WF_PACKED>(gateup, tiles, stream, b, s);
@@ -206,16 +166,13 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
     b.k.cw = 32;
     b.k.col_tiles = (a.H + 255) / 256;
     if (a.ksplit > 1 && a.partial != nullptr) {
+        // the planes stay apart: moe_combine adds them in the fixed order ((p0+p1)+p2)+p3 as it reads them
         b.ksplit = a.ksplit;
         b.plane = a.plane;
         b.k.dst = a.partial;
-        // the planes stay apart: moe_combine adds them in the fixed order ((p0+p1)+p2)+p3 as it reads them
-        Scope sc(a.prof, MOE_PROF_DOWN, s);
-        launch(false);
-    } else {
-        Scope sc(a.prof, MOE_PROF_DOWN, s);
-        launch(false);
     }
+    b.items = n * (unsigned)(b.k.col_tiles * b.ksplit);
+    { Scope sc(a.prof, MOE_PROF_DOWN, s); launch(false); }
 }
 
 }  // namespace qmoe

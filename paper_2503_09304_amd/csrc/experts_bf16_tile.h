@@ -41,6 +41,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "expert_items.h"
 #include "experts_common.h"
 
 namespace qmoe {
@@ -56,13 +57,6 @@ enum { WF_ROWMAJOR = 0, WF_PACKED = 1, WF_MXFP4 = 2 };
 #define QMOE_P3_MIN_T 4
 #endif
 constexpr int kP3MinT = QMOE_P3_MIN_T;
-// A packet (32 workgroups, one XCD's CUs) is 2^QMOE_PK_U segments x 2^(5 - QMOE_PK_U) column tiles.
-// 4 x 8 fetches the least (measured on the 3584-token prefill's gate-up launch: 3.1 GB against 3.4 GB
-// for 8 x 4 and 5.0 GB for 2 x 16; the launch time follows weakly: +1 % and +6 %).
-#ifndef QMOE_PK_U
-#define QMOE_PK_U 2
-#endif
-
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -99,7 +93,8 @@ struct BArgs {
     int ksplit;          // 1, or 2 or 4: K ranges, one workgroup each, partial planes in k.dst
     long plane;          // elements between partial planes
     int nseg;            // > 0: work on seg[0..nseg); 0: on units[u0 .. u0+nu) of the device list
-    Seg seg[kMaxSegs];
+    unsigned items;      // (segments or units) x column tiles x K ranges
+    ItemSeg seg[kMaxSegs];
 };
 
 // One (unit, column tile, K range) on a workgroup.
@@ -443,45 +438,22 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     }
 }
 
-// Workgroup id -> (unit, column tile, K range).  The hardware deals consecutive workgroup ids
-// round-robin to the 8 XCDs (each with its own L2).  Work is cut into packets of 4 consecutive
-// units (in launch order) x 8 consecutive column tiles = 32 workgroups = one XCD's 32 CUs: the 4
-// token tiles are each shared by 8 workgroups and, when the units belong to one expert (chunks of
-// a long queue, or its LS and BE part), the 8 weight tiles by up to 4.  Packet q goes to XCD q % 8;
-// the workgroups of a packet get ids 8 apart.  With a K-split the column-tile axis is
-// (range, tile), range slowest, so a packet stays inside one K range.
-template <bool STREAM>
+// Workgroup id -> (unit, column tile, K range): see expert_items.h.
 __device__ __forceinline__ bool map_block(const BArgs &b, moe_unit &un, int &ct, int &kq) {
-    const int w = blockIdx.x;
-    const int x = w & 7, j = w >> 3;
-    const int packet = (j >> 5) * 8 + x, within = j & 31;
-    const int n = b.nseg > 0 ? b.nseg : b.k.nu;
-    constexpr int PU = QMOE_PK_U, PC = 5 - PU;      // log2 of units and of column tiles per packet
-    const int ugroups = (n + (1 << PU) - 1) >> PU;
-    // Streaming launches list their segments longest first: the packets walk the column tiles of one
-    // group of segments before the next group, so the long segments really start first.  Launches
-    // that share weights walk the groups first: the packets of one column block run side by side.
-    int ctb, ug;
-    if (STREAM) {
-        const int ctbs = (b.k.col_tiles * b.ksplit + (1 << PC) - 1) >> PC;
-        ug = packet / ctbs;
-        ctb = packet - ug * ctbs;
-    } else {
-        ctb = packet / ugroups;
-        ug = packet - ctb * ugroups;
-    }
-    const int pos = (ug << PU) + (within >> PC);
-    const int cq = (ctb << PC) + (within & ((1 << PC) - 1));
-    if (pos >= n || cq >= b.k.col_tiles * b.ksplit) return false;
+    unsigned item;
+    if (!item_of(blockIdx.x, b.items, item)) return false;
+    const unsigned cols = (unsigned)(b.k.col_tiles * b.ksplit);
+    ItemPos ip;
     if (b.nseg > 0) {
-        const Seg g = b.seg[pos];
-        if (g.rows == 0) return false;      // padding between experts
+        ip = item_pos(item, cols, [&](unsigned q, unsigned &in, unsigned &size) { in = b.seg[q].grp & 15; size = b.seg[q].grp >> 4; });
+        const ItemSeg g = b.seg[ip.pos];
         un.expert = g.expert; un.cls = 0; un.row0 = (int)g.row0; un.rows = g.rows;
     } else {
-        un = b.k.units[b.k.u0 + pos];
+        ip = item_pos(item, cols, [&](unsigned q, unsigned &in, unsigned &size) { unit_place(q, (unsigned)b.k.nu, in, size); });
+        un = b.k.units[b.k.u0 + ip.pos];
     }
-    kq = cq / b.k.col_tiles;
-    ct = cq - kq * b.k.col_tiles;
+    kq = (int)ip.cq / b.k.col_tiles;
+    ct = (int)ip.cq - kq * b.k.col_tiles;
     return true;
 }
 
@@ -505,7 +477,7 @@ __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
     }
     int ct, kq;
     moe_unit un;
-    if (!map_block<STREAM>(b, un, ct, kq)) return;
+    if (!map_block(b, un, ct, kq)) return;
     const int t_cnt = (un.rows + 31) >> 5;
     // Prefetch distance of the weights: 2 iterations for the three-stage variants (their loop is unrolled by
     // a multiple of 3) and the 2-tile variant, 3 for the 1-tile variant.
@@ -520,11 +492,7 @@ __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
 
 template <int TCAP, bool GATEUP, int WF, bool STREAM>
 void launch1(const BArgs &b, hipStream_t s) {
-    const unsigned n = b.nseg > 0 ? (unsigned)b.nseg : (unsigned)b.k.nu;
-    const unsigned ugroups = (n + (1u << QMOE_PK_U) - 1) >> QMOE_PK_U, ctb = (b.k.col_tiles * b.ksplit + (32u >> QMOE_PK_U) - 1) / (32u >> QMOE_PK_U);
-    const unsigned packets = ugroups * ctb;
-    const unsigned grid = (packets + 7) / 8 * 8 * 32;
-    hipLaunchKernelGGL((expert_bf16<TCAP, GATEUP, WF, STREAM>), dim3(grid), dim3(256), 0, s, b);
+    hipLaunchKernelGGL((expert_bf16<TCAP, GATEUP, WF, STREAM>), dim3(item_grid(b.items)), dim3(256), 0, s, b);
 }
 
 template <bool GATEUP, int WF, bool STREAM>

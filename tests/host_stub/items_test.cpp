@@ -1,0 +1,61 @@
+// Checks of expert_items.h on the CPU: every (segment, column, K range) of a launch is done by exactly
+// one workgroup, the XCDs get equal shares, and a group mixes experts only where no expert repeats.
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "expert_items.h"
+
+using namespace qmoe;
+
+#define CHECK(c) do { if (!(c)) { std::printf("failed line %d: %s (n %d cols %u)\n", __LINE__, #c, n, cols); std::exit(1); } } while (0)
+
+// Workgroups as launch1 starts them and map_block decodes them.
+template <class Place>
+static void walk(int n, unsigned cols, Place &&place) {
+    const unsigned items = n * cols;
+    unsigned share[kXcds] = {};
+    std::vector<int> seen(items, 0);
+    for (unsigned w = 0; w < item_grid(items); ++w) {
+        unsigned item;
+        if (!item_of(w, items, item)) continue;
+        CHECK(item < items);
+        const ItemPos p = item_pos(item, cols, place);
+        CHECK(p.pos < (unsigned)n && p.cq < cols);
+        ++seen[(size_t)p.pos * cols + p.cq];
+        ++share[w % kXcds];
+    }
+    for (int v : seen) CHECK(v == 1);
+    CHECK(*std::max_element(share, share + kXcds) - *std::min_element(share, share + kXcds) <= 1);
+}
+
+int main() {
+    std::srand(5);
+    for (int n : {1, 2, 3, 4, 5, 8, 9, 31, 32, 33, 64, 65, 383, 384})
+        for (unsigned cols : {1u, 2u, 5u, 7u, 8u, 9u, 10u, 11u, 16u, 31u, 32u, 33u, 64u, 112u, 128u}) {
+            for (int most : {1, 3, 40}) {                 // most segments of one expert
+                std::vector<Seg> segs;
+                for (int e = 0; (int)segs.size() < n && e < kMaxExperts; ++e)
+                    for (int c = e == 255 ? 400 : 1 + std::rand() % most; c > 0 && (int)segs.size() < n; --c)
+                        segs.push_back(Seg{(uint32_t)segs.size() * 256, (uint16_t)(1 + std::rand() % 256), (uint16_t)e});
+                const bool stream = items_stream(segs.data(), n);
+                std::vector<ItemSeg> it(n);
+                plan_items(segs.data(), n, stream, it.data());
+                std::vector<int> taken(n, 0);
+                for (int i = 0; i < n; ++i) {
+                    const Seg &s = segs[it[i].row0 / 256];
+                    CHECK(it[i].rows == s.rows && it[i].expert == s.expert);
+                    ++taken[it[i].row0 / 256];
+                    const int in = it[i].grp & 15, size = it[i].grp >> 4;
+                    CHECK(size >= 1 && size <= kGroupSegs && in < size && i - in >= 0 && i - in + size <= n);
+                    CHECK(it[i - in].grp == (size << 4));
+                    CHECK(stream || it[i - in].expert == it[i].expert);
+                }
+                for (int t : taken) CHECK(t == 1);
+                walk(n, cols, [&](unsigned q, unsigned &in, unsigned &size) { in = it[q].grp & 15; size = it[q].grp >> 4; });
+            }
+            walk(n, cols, [&](unsigned q, unsigned &in, unsigned &size) { unit_place(q, (unsigned)n, in, size); });
+        }
+    std::printf("all item checks passed\n");
+    return 0;
+}
