@@ -70,8 +70,9 @@ typedef struct {
                             ascending order ((p0+p1)+p2)+p3 (bf16, F % (64*down_ksplit) == 0 only).
                             0 picks 1 unless max_tokens*k <= 256*E (weight-streaming shapes, where
                             the split supplies the parallelism): there it picks the fewest ranges
-                            (1, 2, 4) for which E * ceil(H/256) * ranges reaches the 256 compute
-                            units, as far as F allows (with 4-bit weights and decode-sized batches 4
+                            (1, 2, 4) for which experts * ceil(H/256) * ranges reaches the 256
+                            compute units, as far as F allows, with as many experts as max_tokens
+                            tokens that choose k at random reach (with 4-bit weights and decode-sized batches 4
                             ranges are faster than that choice: set it).  Choose 4 for a
                             context whose batches are fed a few units per call so that they can be
                             stopped quickly: a launch of few units has only H/256 workgroups per unit in

@@ -10,6 +10,7 @@
 #include <atomic>
 #include <chrono>
 #include <climits>
+#include <cmath>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -68,13 +69,17 @@ struct Layout {
 int down_ksplit(const moe_config &c) {
     if (c.down_ksplit) return c.down_ksplit;
     if (c.dtype != MOE_BF16 || (int64_t)c.max_tokens * c.k > (int64_t)256 * c.E) return 1;
-    // Weight-streaming shapes: a launch has one workgroup per (expert, 256 columns, K range).  The
-    // fewest ranges that give each of the 256 CUs a workgroup: more ranges only add partial planes
-    // (Mixtral shape, 512 tokens: 2 ranges 0.17 ms, 4 ranges 0.19-0.20 ms, none 0.26 ms).
-    const int64_t wgs = (int64_t)c.E * ((c.H + 255) / 256);
-    if (wgs >= 256) return 1;
-    if (2 * wgs >= 256 && c.F % 128 == 0) return 2;
-    return c.F % 256 == 0 ? 4 : (c.F % 128 == 0 ? 2 : 1);
+    // Weight-streaming shapes: a launch has one workgroup per (expert with rows, 256 columns, K range).
+    // The fewest ranges that give each of the 256 CUs a workgroup: more ranges only add partial planes
+    // (Mixtral shape, 512 tokens: 2 ranges 0.17 ms, 4 ranges 0.19-0.20 ms, none 0.26 ms).  The experts
+    // with rows: as many as a full batch reaches if its tokens choose at random.  One token reaches 2
+    // of 8 experts: 4 ranges = 128 workgroups 41 us, 2 ranges 75 us (8 ranges, 37 us, would be a
+    // template of the combine for one shape in a corner).
+    const double reached = c.E * (1. - std::pow(1. - (double)c.k / c.E, (double)c.max_tokens));
+    const int64_t wgs = (int64_t)std::ceil(reached - 1e-9) * ((c.H + 255) / 256);
+    int ks = 1;
+    while (ks < 4 && ks * wgs < 256 && c.F % (128 * ks) == 0) ks *= 2;
+    return ks;
 }
 
 Layout make_layout(const moe_config &c) {

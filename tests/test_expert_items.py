@@ -15,3 +15,17 @@ def test_every_item_once_and_equal_shares(tmp_path):
     assert r.returncode == 0, r.stderr[-4000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "all item checks passed" in r.stdout, r.stdout[-2000:]
+
+
+def test_few_tokens_split_the_down_projection_by_the_experts_they_reach():
+    """down_ksplit = 0: the K ranges follow from the experts that max_tokens tokens reach, not from all E;
+    the workspace size shows the choice."""
+    import paper_2503_09304_amd as q
+
+    def picks(E, k, H, F, tokens):
+        size = {ks: q.moe_workspace_bytes(q.MoeConfig(E, k, H, F, q.MOE_BF16, 256, tokens, ks)) for ks in (0, 1, 2, 4) if ks < 2 or F % (64 * ks) == 0}
+        return [ks for ks in size if ks and size[ks] == size[0]][0]
+
+    assert [picks(8, 2, 4096, 14336, n) for n in (1, 2, 5, 8, 512)] == [4, 4, 4, 2, 2]
+    assert [picks(64, 8, 2048, 1536, n) for n in (1, 2, 3, 8)] == [4, 4, 2, 1]
+    assert picks(64, 8, 2048, 1408, 1) == 2          # F is a multiple of 128, not of 256
