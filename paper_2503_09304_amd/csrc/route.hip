@@ -8,12 +8,14 @@
 // A workgroup owns 16 tokens; its 8 waves split the hidden dimension into 8 contiguous ranges and
 // add their partial tiles through LDS in wave order, so the summation order is fixed; the same
 // workgroup then selects the experts (fused, no second launch).
-// fp32: one wave per token, lanes stride the hidden dimension, butterfly reduction; separate top-k.
-// top-k: one wave per token.  bf16: every lane ranks its experts against the whole row of logits in
-// LDS (order: logit desc, index asc).  fp32: k rounds of a wave-wide arg-max over the same order.
+// fp32: one wave per token, lanes stride the hidden dimension, butterfly reduction, then the same selection.
+// top-k: k rounds of a wave-wide maximum in the order (logit desc, index asc).
+//
+// These kernels are chains of latencies, 7 to 15 us of a layer of 40 to 500: what counts is their length.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "qmoe_internal.h"
 
@@ -37,114 +39,78 @@ __global__ __launch_bounds__(256) void wg_transpose_bf16(const uint16_t *__restr
     WgT[i] = e < E ? Wg[(long)h * E + e] : (uint16_t)0;
 }
 
-// Wave-wide top-k of one token's logits: lane l holds the logits of experts l, l+64, l+128, l+192
-// in v[]; k rounds of an arg-max over (logit descending, expert index ascending), butterfly
-// shuffles; lane j ends up with slot j; weights = softmax over the k selected logits.
-constexpr int kSlots = kMaxExperts / 64;
-__device__ __forceinline__ void wave_topk(const float (&v)[kSlots], int l, int E, int k, int32_t *__restrict__ idx_out,
-                                          float *__restrict__ w_out) {
-    unsigned picked = 0;
-    float my_v = 0.f;
-    int my_e = 0;
-    for (int j = 0; j < k; ++j) {
-        float bv = -INFINITY;
-        int be = 0x7fffffff;
-#pragma unroll
-        for (int c = 0; c < kSlots; ++c) {
-            const int e = l + 64 * c;
-            const bool ok = e < E && !((picked >> c) & 1u);
-            if (ok && (be == 0x7fffffff || v[c] > bv)) { bv = v[c]; be = e; }   // ascending e: '>' keeps the lowest index
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float ov = __shfl_xor(bv, o, 64);
-            const int oe = __shfl_xor(be, o, 64);
-            const bool take = (oe != 0x7fffffff) && (be == 0x7fffffff || ov > bv || (ov == bv && oe < be));
-            if (take) { bv = ov; be = oe; }
-        }
-        if ((be & 63) == l) picked |= 1u << (be >> 6);
-        if (l == j) { my_v = bv; my_e = be; }
-    }
-    const float top = __shfl(my_v, 0, 64);
-    const float p = l < k ? expf(my_v - top) : 0.f;
-    float s = p;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (l < k) {
-        idx_out[l] = my_e;
-        w_out[l] = p / s;
-    }
+// Largest value of the wave's 64 lanes, in every lane (v_max_f32 over DPP row shifts and broadcasts; a NaN
+// loses against a number).
+__device__ __forceinline__ float wave_max(float v) {
+    auto step = [&](auto ctrl) {
+        const int old = __builtin_bit_cast(int, v);
+        v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(old, old, decltype(ctrl)::value, 0xf, 0xf, false)));
+    };
+    step(std::integral_constant<int, 0x111>{});      // row_shr 1, 2, 4, 8: lane 15 of a row holds the row's maximum
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    step(std::integral_constant<int, 0x142>{});      // row_bcast 15 and 31: lane 63 holds the wave's
+    step(std::integral_constant<int, 0x143>{});
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
-// Top-k by ranking, for logits that sit in LDS: lane l counts, for each of its experts l, l+64, ...,
-// how many experts precede it in the order (logit descending, index ascending); an expert of rank
-// < k is the token's slot `rank`.  No chain of dependent shuffles: the E reads of the row are
-// broadcasts.  The selected logits go through `slot_v` / `slot_e` (k entries of LDS, private to the
-// wave) so that lane j holds slot j, and the weights are the same softmax, summed in the same
-// butterfly order, as wave_topk computes.
-template <int NT>
-__device__ __forceinline__ void wave_topk_rank(const float *const (&row)[NT], float (*__restrict__ slot_v)[kMaxTopK],
-                                               int32_t (*__restrict__ slot_e)[kMaxTopK], int l, int E, int k,
-                                               int32_t *const (&idx_out)[NT], float *const (&w_out)[NT]) {
-    // NT tokens of the wave side by side: their LDS reads and shuffles overlap.  idx_out[h] == nullptr:
-    // token h is past the end of the batch (its row holds a copy of the last token) and stores nothing.
-    float mine[NT][kSlots];
-    int rank[NT][kSlots];
-#pragma unroll
-    for (int h = 0; h < NT; ++h)
-#pragma unroll
-        for (int c = 0; c < kSlots; ++c) {
-            const int e = l + 64 * c;
-            mine[h][c] = e < E ? row[h][e] : 0.f;
-            rank[h][c] = 0;
-        }
-    const int nslots = (E + 63) >> 6;
-    const int E8 = E & ~7;
-    for (int o0 = 0; o0 < E8; o0 += 8) {                 // 8 broadcast reads per token in flight at a time
-        float ov[NT][8];
-#pragma unroll
-        for (int h = 0; h < NT; ++h)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) ov[h][i] = row[h][o0 + i];
-#pragma unroll
-        for (int c = 0; c < kSlots; ++c) {
-            if (c < nslots) {
-                const int e = l + 64 * c;
-#pragma unroll
-                for (int h = 0; h < NT; ++h)
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        rank[h][c] += (ov[h][i] > mine[h][c] || (ov[h][i] == mine[h][c] && o0 + i < e)) ? 1 : 0;
-            }
-        }
-    }
-    for (int o = E8; o < E; ++o) {
-#pragma unroll
-        for (int h = 0; h < NT; ++h) {
-            const float ov = row[h][o];
-#pragma unroll
-            for (int c = 0; c < kSlots; ++c) {
-                const int e = l + 64 * c;
-                if (c < nslots) rank[h][c] += (ov > mine[h][c] || (ov == mine[h][c] && o < e)) ? 1 : 0;
-            }
-        }
-    }
-#pragma unroll
-    for (int h = 0; h < NT; ++h)
-#pragma unroll
-        for (int c = 0; c < kSlots; ++c) {
-            const int e = l + 64 * c;
-            if (e < E && rank[h][c] < k) { slot_v[h][rank[h][c]] = mine[h][c]; slot_e[h][rank[h][c]] = e; }
-        }
-    __builtin_amdgcn_s_waitcnt(0xc07f);      // this wave's LDS writes have landed
-    __builtin_amdgcn_wave_barrier();
-    float my_v[NT], p[NT], s[NT];
+// Top-k of NT tokens by one wave, side by side.  Lane l holds the logits of experts l, l+64, ... (NS of
+// them) in v[h][].  k rounds in the order (logit descending, expert index ascending): the wave's maximum,
+// one ballot per slot for the lanes that hold it, the first of them is taken.  What is left is kept as
+// one bit mask per slot, so that a logit of -inf is chosen like any other; if only NaNs are left the
+// lowest index is taken.  Lane j ends up with slot j; weights = softmax over the k selected logits.
+// Bound by the latency of a round, k rounds.  Comparing every expert with every other one (the tokens'
+// logits in LDS) took 15000 cycles for 64 experts, top-8, 16 tokens in 8 waves: of the router's 17.8 us on
+// 32 tokens x 64 experts it left 13.9, and 11.4 -> 9.6 on 64 x 8.
+// idx_out[h] == nullptr: nothing is stored for token h.
+constexpr int kSlots = kMaxExperts / 64;
+template <int NT, int NS>
+__device__ __forceinline__ void wave_topk(const float (&v)[NT][NS], int l, int E, int k, int32_t *const (&idx_out)[NT],
+                                          float *const (&w_out)[NT]) {
+    unsigned long long left[NT][NS];
+    float cur[NT][NS], my_v[NT], p[NT], s[NT];       // cur: v with what has been taken set to -inf
     int my_e[NT];
 #pragma unroll
     for (int h = 0; h < NT; ++h) {
-        my_v[h] = l < k ? slot_v[h][l] : 0.f;
-        my_e[h] = l < k ? slot_e[h][l] : 0;
-        const float top = __shfl(my_v[h], 0, 64);
+        my_v[h] = 0.f;
+        my_e[h] = 0;
+#pragma unroll
+        for (int c = 0; c < NS; ++c) {
+            left[h][c] = __ballot(l + 64 * c < E);
+            cur[h][c] = l + 64 * c < E ? v[h][c] : -INFINITY;
+        }
+    }
+    for (int j = 0; j < k; ++j) {
+#pragma unroll
+        for (int h = 0; h < NT; ++h) {
+            float best = -INFINITY;
+#pragma unroll
+            for (int c = 0; c < NS; ++c) best = fmaxf(best, cur[h][c]);
+            best = wave_max(best);
+            int e = -1, any = 0;
+#pragma unroll
+            for (int c = NS - 1; c >= 0; --c) {
+                const unsigned long long m = __ballot(v[h][c] == best) & left[h][c];
+                if (m) e = 64 * c + __builtin_ctzll(m);
+                if (left[h][c]) any = 64 * c + __builtin_ctzll(left[h][c]);
+            }
+            if (e < 0) e = any;
+            float ev = v[h][0];
+#pragma unroll
+            for (int c = 0; c < NS; ++c)
+                if (c == e >> 6) {
+                    left[h][c] &= ~(1ull << (e & 63));
+                    cur[h][c] = l == (e & 63) ? -INFINITY : cur[h][c];
+                    ev = v[h][c];
+                }
+            ev = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ev), e & 63));
+            if (l == j) { my_v[h] = ev; my_e[h] = e; }
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < NT; ++h) {
+        const float top = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_v[h]), 0));
         p[h] = l < k ? expf(my_v[h] - top) : 0.f;
         s[h] = p[h];
     }
@@ -173,8 +139,6 @@ __global__ __launch_bounds__(512) void gate_topk_bf16(const uint16_t *__restrict
     __shared__ float red[8][NB][4][64];
     __shared__ float lt[16][NB * 16 + 1];
     __shared__ float sbias[NB * 16];
-    __shared__ float slot_v[8][2][kMaxTopK];
-    __shared__ int32_t slot_e[8][2][kMaxTopK];
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int t16 = l & 15, q = l >> 4;
     int tok = blockIdx.x * 16 + t16;
@@ -187,7 +151,12 @@ __global__ __launch_bounds__(512) void gate_topk_bf16(const uint16_t *__restrict
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     const uint16_t *xa = x + (long)tok * H + q * 8;
-    const uint16_t *wb = WgT + (long)t16 * H + q * 8;
+    // Expert rows from E on are padding: their lanes read the last expert again (no bytes of their own), and
+    // nothing uses what they compute.  A CU takes 11 to 20 bytes a clock here: with 8 experts that is half
+    // of the weights' time (one token, H 4096: 7.7 -> 5.7 us; all k-steps requested at once gave nothing).
+    const uint16_t *wb[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) wb[b] = WgT + (long)min(b * 16 + t16, E - 1) * H + q * 8;
     constexpr int CH = NB == 1 ? 8 : (NB == 2 ? 4 : 2);   // k-steps whose loads are issued together
     for (int s = s0; s < s1; s += CH) {
         bf16x8 a[CH], bv[CH][NB];
@@ -197,7 +166,7 @@ __global__ __launch_bounds__(512) void gate_topk_bf16(const uint16_t *__restrict
             a[c] = *reinterpret_cast<const bf16x8 *>(xa + sc * 32);
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-                bv[c][b] = *reinterpret_cast<const bf16x8 *>(wb + (long)min(b, nb - 1) * 16 * H + sc * 32);
+                bv[c][b] = *reinterpret_cast<const bf16x8 *>(wb[b] + sc * 32);
         }
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
@@ -234,53 +203,85 @@ __global__ __launch_bounds__(512) void gate_topk_bf16(const uint16_t *__restrict
     __syncthreads();
     const int t0 = blockIdx.x * 16 + w * 2;             // this wave's two tokens
     if (t0 < N) {
-        const float *const rows[2] = {lt[w * 2], lt[w * 2 + 1]};
+        constexpr int NS = (NB + 3) / 4;
+        float v[2][NS];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < NS; ++c) v[h][c] = l + 64 * c < E ? lt[w * 2 + h][l + 64 * c] : -INFINITY;
         int32_t *const io[2] = {topk_idx + (long)t0 * k, t0 + 1 < N ? topk_idx + (long)(t0 + 1) * k : nullptr};
         float *const wo[2] = {topk_w + (long)t0 * k, t0 + 1 < N ? topk_w + (long)(t0 + 1) * k : nullptr};
-        wave_topk_rank<2>(rows, slot_v[w], slot_e[w], l, E, k, io, wo);
+        wave_topk<2, NS>(v, l, E, k, io, wo);
     }
 }
 
-// One wave per token, 8 experts at a time.
-__global__ __launch_bounds__(256) void gate_logits_f32(const float *__restrict__ x, const float *__restrict__ Wg,
-                                                       const float *__restrict__ bias, float *__restrict__ logits,
-                                                       int N, int H, int E) {
+// One wave per token: lane l sums the elements h = l, l + 64, ... of EB logits at a time (U of them
+// loaded together), a butterfly adds the lanes, and the wave selects its experts.  VEC: E is a multiple of
+// EB, so the EB weights of a row are read 16 bytes at a time (rows need only 4-byte alignment).
+// 509 tokens x 8 experts, H 1024: 20.6 us with scalar loads one element at a time, and 4.8 us for the
+// selection as a launch of its own; 6.2 us here.  The sums are the same, bit for bit.
+template <int EB, bool VEC>
+__global__ __launch_bounds__(256) void gate_topk_f32(const float *__restrict__ x, const float *__restrict__ Wg,
+                                                     const float *__restrict__ bias, float *__restrict__ logits,
+                                                     int32_t *__restrict__ topk_idx, float *__restrict__ topk_w, int N, int H,
+                                                     int E, int k) {
+    constexpr int U = 8;
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int tok = blockIdx.x * 4 + w;
     if (tok >= N) return;
-    for (int e0 = 0; e0 < E; e0 += 8) {
-        float acc[8];
+    const float *xr = x + (long)tok * H;
+    float v[1][kSlots];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-        for (int h = l; h < H; h += 64) {
-            const float xv = x[(long)tok * H + h];
+    for (int c = 0; c < kSlots; ++c) v[0][c] = -INFINITY;
+    for (int e0 = 0; e0 < E; e0 += EB) {
+        float acc[EB];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (e0 + j < E) acc[j] = fmaf(xv, Wg[(long)h * E + e0 + j], acc[j]);
+        for (int j = 0; j < EB; ++j) acc[j] = 0.f;
+        for (int h0 = l; h0 < H; h0 += 64 * U) {
+            float xv[U], wv[U][EB];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int h = min(h0 + 64 * u, H - 1);
+                xv[u] = xr[h];
+                const float *wr = Wg + (long)h * E + e0;
+                if constexpr (VEC) {
+#pragma unroll
+                    for (int j = 0; j < EB; j += 4) {
+                        const f32x4u t = *reinterpret_cast<const f32x4u *>(wr + j);
+                        wv[u][j] = t[0]; wv[u][j + 1] = t[1]; wv[u][j + 2] = t[2]; wv[u][j + 3] = t[3];
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < EB; ++j) wv[u][j] = e0 + j < E ? wr[j] : 0.f;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (h0 + 64 * u < H) {
+#pragma unroll
+                    for (int j = 0; j < EB; ++j) acc[j] = fmaf(xv[u], wv[u][j], acc[j]);
+                }
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            float v = acc[j];
+        for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (l == 0 && e0 + j < E) logits[(long)tok * E + e0 + j] = v + (bias ? bias[e0 + j] : 0.f);
+            for (int j = 0; j < EB; ++j) acc[j] += __shfl_xor(acc[j], o, 64);
+#pragma unroll
+        for (int j = 0; j < EB; ++j) {
+            const int e = e0 + j;
+            if (e < E && (e & 63) == l) {
+                const float lg = acc[j] + (bias ? bias[e] : 0.f);
+                logits[(long)tok * E + e] = lg;
+#pragma unroll
+                for (int c = 0; c < kSlots; ++c)
+                    if (c == e >> 6) v[0][c] = lg;
+            }
         }
     }
-}
-
-// One wave per token (fp32 path).
-__global__ __launch_bounds__(256) void topk_softmax(const float *__restrict__ logits, int32_t *__restrict__ topk_idx,
-                                                    float *__restrict__ topk_w, int N, int E, int k) {
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int tok = blockIdx.x * 4 + w;
-    if (tok >= N) return;
-    float v[kSlots];
-#pragma unroll
-    for (int c = 0; c < kSlots; ++c) {
-        const int e = l + 64 * c;
-        v[c] = e < E ? logits[(long)tok * E + e] : -INFINITY;
-    }
-    wave_topk(v, l, E, k, topk_idx + (long)tok * k, topk_w + (long)tok * k);
+    int32_t *const io[1] = {topk_idx + (long)tok * k};
+    float *const wo[1] = {topk_w + (long)tok * k};
+    wave_topk<1, kSlots>(v, l, E, k, io, wo);
 }
 
 }  // namespace
@@ -311,10 +312,11 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t s) {
         else QMOE_GATE(16);
 #undef QMOE_GATE
     } else {
-        hipLaunchKernelGGL(gate_logits_f32, dim3((a.N + 3) / 4), dim3(256), 0, s, (const float *)a.x,
-                           (const float *)a.Wg, a.bias, a.logits, a.N, a.H, a.E);
-        hipLaunchKernelGGL(topk_softmax, dim3((a.N + 3) / 4), dim3(256), 0, s, (const float *)a.logits, a.topk_idx,
-                           a.topk_w, a.N, a.E, a.k);
+        const dim3 g((a.N + 3) / 4), b(256);
+        const float *x = (const float *)a.x, *wg = (const float *)a.Wg;
+        if (a.E % 8 == 0) hipLaunchKernelGGL((gate_topk_f32<8, true>), g, b, 0, s, x, wg, a.bias, a.logits, a.topk_idx, a.topk_w, a.N, a.H, a.E, a.k);
+        else if (a.E % 4 == 0) hipLaunchKernelGGL((gate_topk_f32<4, true>), g, b, 0, s, x, wg, a.bias, a.logits, a.topk_idx, a.topk_w, a.N, a.H, a.E, a.k);
+        else hipLaunchKernelGGL((gate_topk_f32<8, false>), g, b, 0, s, x, wg, a.bias, a.logits, a.topk_idx, a.topk_w, a.N, a.H, a.E, a.k);
     }
     return hipGetLastError();
 }
