@@ -1,8 +1,12 @@
 // Gate-weighted combine of complete tokens (Sec. 3.1, "Top-k expert selection": finished expert
 // outputs are tracked as state and only fully processed tokens feed the next layer).
 //   y[n,:] = sum_j w[n,j] * out[inv[n*k+j], :],  j = 0..k-1 in slot order, fp32 fma chain from 0,
-// one rounding to the output type.  HBM-bound gather-reduce: one workgroup per token, 16-byte
-// loads along the hidden dimension.
+// one rounding to the output type.  A gather-reduce: bound by HBM for large batches (8192 tokens x top-8,
+// H 2048: 102 us for 571 MB, 5.6 TB/s), by a chain of dependent reads for small ones.  One workgroup per
+// token and 1024 columns: the token's positions and weights are the same for every lane, so they come
+// through scalar loads without LDS or barriers, and the rows of a column are all requested before the
+// first is used.  One workgroup per token, positions through LDS and one row at a time took 7.5 us for 64
+// tokens (H 4096, top-2, 2 K ranges), 6.2 with 4 ranges and 10.5 for 512 tokens; 4.4, 4.3 and 8.2 here.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,6 +34,22 @@ __device__ __forceinline__ f32x4 load_out(const float *__restrict__ p, long plan
     return v;
 }
 
+// acc += w[j] * out[inv[j], h..h+3] for j = j0 .. j0+U-1 in slot order: the loads of all U rows are requested
+// before the first is used.
+template <int KS, int U>
+__device__ __forceinline__ void add_rows(f32x4 &acc, const float *__restrict__ out, long plane, const int32_t *__restrict__ inv,
+                                         const float *__restrict__ w, int j0, int H, int h) {
+    f32x4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = load_out<KS>(out + (long)inv[j0 + u] * H + h, plane);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float wj = w[j0 + u];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = fmaf(wj, v[u][i], acc[i]);
+    }
+}
+
 // done == nullptr: tokens are selected by class (the host has checked that the class is finished).
 // done != nullptr: a token is selected when done[] is set for all k of its sorted positions;
 // complete[n] (if given) reports the selection.
@@ -37,55 +57,45 @@ template <bool BF16, int KS>
 __global__ __launch_bounds__(256) void combine_rows(const float *__restrict__ out, long plane, const float *__restrict__ topk_w,
                                                     const int32_t *__restrict__ inv, const uint8_t *__restrict__ cls,
                                                     const uint8_t *__restrict__ done, uint8_t *__restrict__ complete,
-                                                    void *__restrict__ y, int N, int H, int k, int class_mask) {
+                                                    void *__restrict__ y, int H, int k, int class_mask) {
     const int n = blockIdx.x;
-    if (n >= N) return;
+    const int32_t *pos = inv + (long)n * k;             // the same for every lane: scalar loads
+    const float *wgt = topk_w + (long)n * k;
     if (done == nullptr) {
         const int bit = cls[n] == 0 ? MOE_CLASS_LS : MOE_CLASS_BE;
         if (!(class_mask & bit)) return;
-    }
-    __shared__ float sw[kMaxTopK];
-    __shared__ int32_t sp[kMaxTopK];
-    __shared__ int missing;
-    if (threadIdx.x == 0) missing = 0;
-    __syncthreads();
-    if (threadIdx.x < k) {
-        const int32_t p = inv[(long)n * k + threadIdx.x];
-        sw[threadIdx.x] = topk_w[(long)n * k + threadIdx.x];
-        sp[threadIdx.x] = p;
-        if (done != nullptr && done[p] == 0) missing = 1;     // any writer stores the same value
-    }
-    __syncthreads();
-    if (done != nullptr) {
-        if (complete != nullptr && threadIdx.x == 0) complete[n] = missing ? 0 : 1;
+    } else {
+        bool missing = false;
+        for (int j = 0; j < k; ++j) missing |= done[pos[j]] == 0;
+        if (complete != nullptr && blockIdx.y == 0 && threadIdx.x == 0) complete[n] = missing ? 0 : 1;
         if (missing) return;
     }
+    const int step = (int)gridDim.y * 256;
     if ((H & 3) == 0) {
-        for (int h = threadIdx.x * 4; h < H; h += 1024) {
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int j = 0; j < k; ++j) {
-                const f32x4 v = load_out<KS>(out + (long)sp[j] * H + h, plane);
-                const float wj = sw[j];
-                acc.x = fmaf(wj, v.x, acc.x);
-                acc.y = fmaf(wj, v.y, acc.y);
-                acc.z = fmaf(wj, v.z, acc.z);
-                acc.w = fmaf(wj, v.w, acc.w);
-            }
+        constexpr int U = KS == 4 ? 4 : 8;              // at most 16 rows of 16 bytes in flight per lane
+        for (int h = ((int)blockIdx.y * 256 + (int)threadIdx.x) * 4; h < H; h += step * 4) {
+            f32x4 acc{0.f, 0.f, 0.f, 0.f};
+            int j = 0;
+            for (; j + U <= k; j += U) add_rows<KS, U>(acc, out, plane, pos, wgt, j, H, h);
+            if (U > 4 && (k & 4)) { add_rows<KS, 4>(acc, out, plane, pos, wgt, j, H, h); j += 4; }
+            if (k & 2) { add_rows<KS, 2>(acc, out, plane, pos, wgt, j, H, h); j += 2; }
+            if (k & 1) add_rows<KS, 1>(acc, out, plane, pos, wgt, j, H, h);
             if (BF16) {
-                __bf16 r[4] = {(__bf16)acc.x, (__bf16)acc.y, (__bf16)acc.z, (__bf16)acc.w};
+                __bf16 r[4] = {(__bf16)acc[0], (__bf16)acc[1], (__bf16)acc[2], (__bf16)acc[3]};
                 *reinterpret_cast<uint2 *>((uint16_t *)y + (long)n * H + h) = *reinterpret_cast<uint2 *>(r);
             } else {
-                *reinterpret_cast<float4 *>((float *)y + (long)n * H + h) = acc;
+                *reinterpret_cast<f32x4 *>((float *)y + (long)n * H + h) = acc;
             }
         }
     } else {
-        for (int h = threadIdx.x; h < H; h += 256) {
+        for (int h = (int)blockIdx.y * 256 + (int)threadIdx.x; h < H; h += step) {
             float acc = 0.f;
             for (int j = 0; j < k; ++j) {
-                float v = out[(long)sp[j] * H + h];
+                const long at = (long)pos[j] * H + h;
+                float v = out[at];
 #pragma unroll
-                for (int q = 1; q < KS; ++q) v = v + out[q * plane + (long)sp[j] * H + h];
-                acc = fmaf(sw[j], v, acc);
+                for (int q = 1; q < KS; ++q) v = v + out[q * plane + at];
+                acc = fmaf(wgt[j], v, acc);
             }
             if (BF16) ((__bf16 *)y)[(long)n * H + h] = (__bf16)acc;
             else ((float *)y)[(long)n * H + h] = acc;
@@ -162,8 +172,9 @@ hipError_t launch_clear_words(int32_t *p, long n, hipStream_t s) {
 
 template <bool BF16, int KS>
 static void launch_combine_ks(const CombineArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL((combine_rows<BF16, KS>), dim3(a.N), dim3(256), 0, s, a.out, a.plane, a.topk_w, a.inv, a.cls, a.done,
-                       a.complete, a.y, a.N, a.H, a.k, a.class_mask);
+    const int chunks = a.H % 4 == 0 ? (a.H + 1023) / 1024 : (a.H + 255) / 256;
+    hipLaunchKernelGGL((combine_rows<BF16, KS>), dim3(a.N, std::min(chunks, 64)), dim3(256), 0, s, a.out, a.plane, a.topk_w, a.inv,
+                       a.cls, a.done, a.complete, a.y, a.H, a.k, a.class_mask);
 }
 
 hipError_t launch_combine(const CombineArgs &a, hipStream_t s) {
