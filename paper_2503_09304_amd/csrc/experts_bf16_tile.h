@@ -449,7 +449,7 @@ __device__ __forceinline__ bool map_block(const BArgs &b, moe_unit &un, int &ct,
         const ItemSeg g = b.seg[ip.pos];
         un.expert = g.expert; un.cls = 0; un.row0 = (int)g.row0; un.rows = g.rows;
     } else {
-        ip = item_pos(item, cols, [&](unsigned q, unsigned &in, unsigned &size) { unit_place(q, (unsigned)b.k.nu, in, size); });
+        ip = unit_item_pos(item, (unsigned)b.k.nu, cols);
         un = b.k.units[b.k.u0 + ip.pos];
     }
     kq = (int)ip.cq / b.k.col_tiles;

@@ -11,8 +11,8 @@ using namespace qmoe;
 #define CHECK(c) do { if (!(c)) { std::printf("failed line %d: %s (n %d cols %u)\n", __LINE__, #c, n, cols); std::exit(1); } } while (0)
 
 // Workgroups as launch1 starts them and map_block decodes them.
-template <class Place>
-static void walk(int n, unsigned cols, Place &&place) {
+template <class Pos>
+static void walk(int n, unsigned cols, Pos &&pos) {
     const unsigned items = n * cols;
     unsigned share[kXcds] = {};
     std::vector<int> seen(items, 0);
@@ -20,7 +20,7 @@ static void walk(int n, unsigned cols, Place &&place) {
         unsigned item;
         if (!item_of(w, items, item)) continue;
         CHECK(item < items);
-        const ItemPos p = item_pos(item, cols, place);
+        const ItemPos p = pos(item);
         CHECK(p.pos < (unsigned)n && p.cq < cols);
         ++seen[(size_t)p.pos * cols + p.cq];
         ++share[w % kXcds];
@@ -52,9 +52,11 @@ int main() {
                     CHECK(stream || it[i - in].expert == it[i].expert);
                 }
                 for (int t : taken) CHECK(t == 1);
-                walk(n, cols, [&](unsigned q, unsigned &in, unsigned &size) { in = it[q].grp & 15; size = it[q].grp >> 4; });
+                walk(n, cols, [&](unsigned item) {
+                    return item_pos(item, cols, [&](unsigned q, unsigned &in, unsigned &size) { in = it[q].grp & 15; size = it[q].grp >> 4; });
+                });
             }
-            walk(n, cols, [&](unsigned q, unsigned &in, unsigned &size) { unit_place(q, (unsigned)n, in, size); });
+            walk(n, cols, [&](unsigned item) { return unit_item_pos(item, (unsigned)n, cols); });
         }
     std::printf("all item checks passed\n");
     return 0;
