@@ -204,22 +204,34 @@ __global__ __launch_bounds__(256) void expert_f32(const FArgs f) {
 
 }  // namespace
 
+// One kernel over all n segments or units of f, in launches of as many as one can hold.
+template <bool GATEUP>
+static void launch_f32(FArgs &f, const Seg *segs, unsigned n, hipStream_t s) {
+    const unsigned u0 = f.k.u0, wgs = (unsigned)f.row_tiles * (unsigned)f.k.col_tiles, most = segs_per_launch(wgs);
+    for (unsigned at = 0; at < n; at += std::min(most, n - at)) {
+        const unsigned cnt = std::min(most, n - at);
+        if (segs) {
+            f.nseg = (int)cnt;
+            std::copy(segs + at, segs + at + cnt, f.seg);
+        } else {
+            f.k.u0 = u0 + at;
+        }
+        hipLaunchKernelGGL(expert_f32<GATEUP>, dim3(cnt * wgs), dim3(256), 0, s, f);
+    }
+}
+
 void launch_experts_f32(const ExpertArgs &a, const KArgs &gu_in, const KArgs &dn_in, hipStream_t s) {
     FArgs f{};
-    f.nseg = a.segs ? a.nseg : 0;
-    if (f.nseg > 0) std::copy(a.segs, a.segs + a.nseg, f.seg);
-    const unsigned n = f.nseg > 0 ? (unsigned)f.nseg : a.nu;
+    const unsigned n = a.segs ? (unsigned)a.nseg : a.nu;
     f.row_tiles = (a.max_rows + BM - 1) / BM;
     const int gu_cols = (a.F + BN - 1) / BN, dn_cols = (a.H + BN - 1) / BN;
     f.k = gu_in;
     f.k.col_tiles = gu_cols;
-    { Scope sc(a.prof, MOE_PROF_GATE_UP, s);
-      hipLaunchKernelGGL(expert_f32<true>, dim3(n * f.row_tiles * gu_cols), dim3(256), 0, s, f); }
+    { Scope sc(a.prof, MOE_PROF_GATE_UP, s); launch_f32<true>(f, a.segs, n, s); }
     f.k = dn_in;
     f.k.col_tiles = dn_cols;
     f.k.need = gu_cols;              // gate-up workgroups per row tile
-    { Scope sc(a.prof, MOE_PROF_DOWN, s);
-      hipLaunchKernelGGL(expert_f32<false>, dim3(n * f.row_tiles * dn_cols), dim3(256), 0, s, f); }
+    { Scope sc(a.prof, MOE_PROF_DOWN, s); launch_f32<false>(f, a.segs, n, s); }
 }
 
 }  // namespace qmoe

@@ -102,6 +102,15 @@ struct ExpertArgs {
 
 constexpr int kF32RowTile = 32, kF32ColTile = 32;   // rows and output columns of a workgroup of the fp32 expert kernels
 
+// A launch of 2^32 threads or more loses the excess without an error.  Segments (or units) of `wgs` workgroups of
+// 256 threads each that one launch may hold, with 7 workgroups to spare for a grid that is rounded up to 8: a
+// launch over the device's unit list can have 2^24 workgroups and more (65536 units of one row x 8192 fp32
+// columns), and goes out in pieces of this many.
+inline uint32_t segs_per_launch(uint64_t wgs) {
+    const uint64_t most = ((uint64_t(1) << 24) - 8) / (wgs ? wgs : 1);
+    return most < 1 ? 1 : (uint32_t)most;
+}
+
 // Workgroups of the down projection that cover a row range of `rows` rows: what its counter reads
 // when the range is complete.
 __host__ __device__ inline int down_wgs_of_range(int dtype, int H, int ksplit, int rows) {

@@ -1,5 +1,6 @@
 // Checks of expert_items.h on the CPU: every (segment, column, K range) of a launch is done by exactly
-// one workgroup, the XCDs get equal shares, and a group mixes experts only where no expert repeats.
+// one workgroup, the XCDs get equal shares, and a group mixes experts only where no expert repeats;
+// and of the pieces a launch is cut into.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -58,6 +59,13 @@ int main() {
             }
             walk(n, cols, [&](unsigned item) { return unit_item_pos(item, (unsigned)n, cols); });
         }
+    // pieces of an fp32 launch: never 2^32 threads, and never more pieces than that needs
+    for (uint64_t wgs : {uint64_t(1), uint64_t(3), uint64_t(256), uint64_t(512), uint64_t(4096), uint64_t(65535), (uint64_t(1) << 24) - 8}) {
+        const int n = 0;
+        const unsigned cols = (unsigned)wgs;
+        const uint64_t most = segs_per_launch(wgs);
+        CHECK(most >= 1 && (most * wgs + 7) * 256 < uint64_t(1) << 32 && (most + 1) * wgs + 8 > uint64_t(1) << 24);
+    }
     std::printf("all item checks passed\n");
     return 0;
 }
