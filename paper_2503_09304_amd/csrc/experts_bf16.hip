@@ -152,11 +152,20 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
     b.k = gu_in;
     b.k.cw = a.wave_cols ? a.wave_cols : gate_up_wave_columns(stream, a.wfmt, tiles, (int)n, a.F);
     b.k.col_tiles = (a.F + 4 * b.k.cw - 1) / (4 * b.k.cw);
-    b.items = n * (unsigned)b.k.col_tiles;
-    auto launch = [&](bool gateup) {
+    auto launch_one = [&](bool gateup) {
         if (a.wfmt == bf16k::WF_MXFP4) bf16k::launch_expert_kernels<bf16k::WF_MXFP4>(gateup, tiles, stream, b, s);
         else if (a.wfmt == bf16k::WF_PACKED) bf16k::launch_expert_kernels<bf16k::WF_PACKED>(gateup, tiles, stream, b, s);
         else bf16k::launch_expert_kernels<bf16k::WF_ROWMAJOR>(gateup, tiles, stream, b, s);
+    };
+    auto launch = [&](bool gateup) {
+        // segments in the arguments are one launch, a range of the unit list as many as it takes
+        const unsigned cols = (unsigned)(b.k.col_tiles * b.ksplit), most = b.nseg > 0 ? n : segs_per_launch(cols);
+        for (unsigned at = 0; at < n; at += (unsigned)b.k.nu) {
+            b.k.u0 = a.u0 + at;
+            b.k.nu = (int)std::min(most, n - at);
+            b.items = (unsigned)b.k.nu * cols;
+            launch_one(gateup);
+        }
     };
     { Scope sc(a.prof, MOE_PROF_GATE_UP, s); launch(true); }
 
@@ -171,7 +180,6 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
         b.plane = a.plane;
         b.k.dst = a.partial;
     }
-    b.items = n * (unsigned)(b.k.col_tiles * b.ksplit);
     { Scope sc(a.prof, MOE_PROF_DOWN, s); launch(false); }
 }
 
