@@ -64,3 +64,42 @@ def test_more_workgroups_than_one_launch_holds(dtype, H, F, cols):
     assert ctx.expert_run(x, w) == q.MOE_DONE
     torch.cuda.synchronize()
     check(ctx, x, W, 1, dtype)
+
+
+@pytest.mark.parametrize("dtype,H,F", [("f32", 64, 100), ("f32", 33, 72), ("bf16", 512, 1408), ("bf16", 320, 1152)])
+def test_same_bits_whole_cut_enqueued_and_scattered(dtype, H, F):
+    """One launch over the unit list, its first 100 units as segments, the enqueued (counted) launch, and scattered units
+    in launches of at most 384 segments: the same outputs, bit for bit; the first against plain products."""
+    k, N = 8, 16384
+    ctx, x, w, W, prio, Wg = make(dtype, 64, k, H, F, N, 4000, 256, 5)
+    nu = ctx.cursor.n_units
+    y = torch.zeros_like(x)
+
+    def result():
+        ctx.combine(y)
+        out = ctx.get("expert_out").clone()
+        torch.cuda.synchronize()
+        return out, y.clone()
+
+    def again():
+        ctx.get("expert_out").fill_(float("nan"))
+        ctx.route(x, w)
+        ctx.permute(prio)
+
+    assert ctx.expert_run(x, w) == q.MOE_DONE
+    base = result()
+    check(ctx, x, W, k, dtype)
+
+    again()
+    assert ctx.expert_run(x, w, 100) == q.MOE_OK and ctx.expert_run(x, w) == q.MOE_DONE
+    cut = result()
+    again()
+    assert ctx.expert_enqueue(x, w, q.UINT32_MAX) == q.MOE_OK and ctx.expert_collect() == q.MOE_DONE
+    queued = result()
+    again()
+    rest = [u for u in range(nu) if u % 5]                       # 4 of 5 units: runs of rows broken up, in several launches
+    assert len(rest) > 384
+    assert ctx.expert_run_units(x, w, rest) == q.MOE_OK and ctx.expert_run(x, w) == q.MOE_DONE
+    scattered = result()
+    for other in (cut, queued, scattered):
+        assert all(torch.equal(a, b) for a, b in zip(base, other))
