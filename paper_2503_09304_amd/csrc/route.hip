@@ -128,11 +128,14 @@ __device__ __forceinline__ void wave_topk(const float (&v)[NT][NS], int l, int E
 
 // Gate GEMM and top-k of 16 tokens per workgroup.  NB = number of 16-expert blocks held in
 // registers (E16 <= 16*NB).  The 8 waves split the hidden dimension into 8 contiguous ranges (loads
-// issued 8, 4 or 2 k-steps at a time: few enough registers that at least two workgroups share a CU,
-// which halves the router's time on 8192 tokens x 64 experts), add their partial tiles through LDS
-// in wave order, and then each wave selects the experts of 2 of the 16 tokens.
+// issued 8, 4 or 2 k-steps at a time), add their partial tiles through LDS in wave order, and then
+// each wave selects the experts of 2 of the 16 tokens.
+// Up to 128 experts (NB <= 8) registers and LDS leave room for at least two workgroups on a CU, which halves
+// the time on 8192 tokens x 64 experts.  NB = 8 has to be told: by itself it takes 132 registers, one workgroup
+// per CU, 44.6 us for 8192 tokens x 128 experts, top-8, H 2048; 40.1 us with 128 registers, and small batches
+// the same.  NB = 16 fills the LDS of a CU alone.
 template <int NB>
-__global__ __launch_bounds__(512) void gate_topk_bf16(const uint16_t *__restrict__ x, const uint16_t *__restrict__ WgT,
+__global__ __launch_bounds__(512, NB == 8 ? 4 : 2) void gate_topk_bf16(const uint16_t *__restrict__ x, const uint16_t *__restrict__ WgT,
                                                       const float *__restrict__ bias, float *__restrict__ logits,
                                                       int32_t *__restrict__ topk_idx, float *__restrict__ topk_w, int N, int H,
                                                       int E, int nb, int k) {
