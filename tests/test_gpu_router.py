@@ -1,5 +1,6 @@
 """The router kernels at the edges of their tiles: expert counts around 4, 8, 16, 64, ragged hidden sizes and
-token counts, ties, -inf logits (an expert switched off by its bias), k = 1 .. E."""
+token counts, ties, -inf logits (an expert switched off by its bias), k = 1 .. E, on both sides of the k from which
+up to 64 experts are ranked instead of chosen in k rounds."""
 import numpy as np
 import pytest
 import torch
@@ -55,3 +56,23 @@ def test_selection_and_logits(dtype, E, k):
     logits, idx, w = _route(dtype, E, k, H, torch.zeros_like(x), Wg, torch.from_numpy(tied).to(DEV))
     assert np.array_equal(logits, np.broadcast_to(tied, logits.shape))
     _check(logits, idx, w, k)
+
+
+@pytest.mark.parametrize("E", [1, 2, 7, 8, 15, 16, 17, 31, 32, 33, 56, 57, 63, 64, 65])
+def test_rounds_and_ranks_choose_alike(E):
+    """Every k of one set of logits with ties, both zeros, infinities and, in the second set, NaNs (chosen last, the
+    lowest index first): the first k of the order, by rounds below E / 4 and by ranks from there on."""
+    rng = np.random.default_rng(E)
+    H, N = 64, 19
+    x = torch.zeros((N, H), dtype=torch.bfloat16, device=DEV)
+    Wg = torch.zeros((H, E), dtype=torch.bfloat16, device=DEV)
+    for values in ([-np.inf, -1.5, -0.0, 0.0, 2.0], [-np.inf, -1.0, 0.0, 1.0, np.inf, np.nan]):
+        bias = torch.from_numpy(rng.choice(np.array(values, dtype=np.float32), E)).to(DEV)
+        if not np.isnan(values).any():
+            bias[0] = 2.0                             # the largest logit is finite: the weights are numbers
+        for k in range(1, min(E, 32) + 1):
+            logits, idx, w = _route(torch.bfloat16, E, k, H, x, Wg, bias)
+            order = np.lexsort((np.arange(E), -logits[0]))
+            assert np.array_equal(idx, np.broadcast_to(order[:k], (N, k))), (k, bias)
+            if not np.isnan(values).any():
+                _check(logits, idx, w, k)
