@@ -2,11 +2,11 @@
 // outputs are tracked as state and only fully processed tokens feed the next layer).
 //   y[n,:] = sum_j w[n,j] * out[inv[n*k+j], :],  j = 0..k-1 in slot order, fp32 fma chain from 0,
 // one rounding to the output type.  A gather-reduce: bound by HBM for large batches (8192 tokens x top-8,
-// H 2048: 102 us for 571 MB, 5.6 TB/s), by a chain of dependent reads for small ones.  One workgroup per
-// token and 1024 columns: the token's positions and weights are the same for every lane, so they come
-// through scalar loads without LDS or barriers, and the rows of a column are all requested before the
-// first is used.  One workgroup per token, positions through LDS and one row at a time took 7.5 us for 64
-// tokens (H 4096, top-2, 2 K ranges), 6.2 with 4 ranges and 10.5 for 512 tokens; 4.4, 4.3 and 8.2 here.
+// H 2048: 103 us for 571 MB, 5.6 TB/s), by a chain of dependent reads for small ones.  A workgroup takes a token
+// or, in small batches, 1024 columns of one: the token's positions and weights are the same for every lane, so they
+// come through scalar loads without LDS or barriers, and the rows of a column are all requested before the first is
+// used.  Positions through LDS and one row at a time took 5.8 us for 64 tokens (H 4096, top-2, 4 K ranges), 8.2 for
+// 512 tokens (2 K ranges), 28.4 for 2048 x top-8 (H 2048) and 103 for 8192 of these; 3.0, 6.2, 26.3 and 103 here.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -65,8 +65,8 @@ __global__ __launch_bounds__(256) void combine_rows(const float *__restrict__ ou
         const int bit = cls[n] == 0 ? MOE_CLASS_LS : MOE_CLASS_BE;
         if (!(class_mask & bit)) return;
     } else {
-        bool missing = false;
-        for (int j = 0; j < k; ++j) missing |= done[pos[j]] == 0;
+        const int lane = threadIdx.x & 63;              // lane j of every wave looks at row j (k <= 32)
+        const bool missing = __any(lane < k && done[pos[lane]] == 0);
         if (complete != nullptr && blockIdx.y == 0 && threadIdx.x == 0) complete[n] = missing ? 0 : 1;
         if (missing) return;
     }
@@ -172,9 +172,13 @@ hipError_t launch_clear_words(int32_t *p, long n, hipStream_t s) {
 
 template <bool BF16, int KS>
 static void launch_combine_ks(const CombineArgs &a, hipStream_t s) {
+    // A token's chunks go to workgroups of their own only where the tokens alone are too few for the chip: beyond that
+    // a workgroup's start costs more than it hides.  Us without / with such a split: 64 tokens x top-2, H 4096,
+    // 4 K ranges 5.8 / 3.0; 512 tokens, 2 K ranges 6.3 / 6.2; 1024 tokens, top-1 6.5 / 6.9; 2048 x top-8, H 2048
+    // 26.3 / 29.1; 3584 x top-2, H 4096 27.0 / 26.6; 8192 x top-1 38.1 / 44.8; 8192 x top-8, H 2048 102.7 / 106.5.
     const int chunks = a.H % 4 == 0 ? (a.H + 1023) / 1024 : (a.H + 255) / 256;
-    hipLaunchKernelGGL((combine_rows<BF16, KS>), dim3(a.N, std::min(chunks, 64)), dim3(256), 0, s, a.out, a.plane, a.topk_w, a.inv,
-                       a.cls, a.done, a.complete, a.y, a.H, a.k, a.class_mask);
+    hipLaunchKernelGGL((combine_rows<BF16, KS>), dim3(a.N, std::min(chunks, std::max(1, 2048 / a.N))), dim3(256), 0, s, a.out,
+                       a.plane, a.topk_w, a.inv, a.cls, a.done, a.complete, a.y, a.H, a.k, a.class_mask);
 }
 
 hipError_t launch_combine(const CombineArgs &a, hipStream_t s) {

@@ -1,6 +1,6 @@
 """The combine at the edges of its loops: top-k beside the row groups it requests together (1, 2, 4, 8, 16, 32),
-every number of K ranges, hidden sizes beside its 1024-column workgroups, no multiple of 4, and past the
-64 workgroups per token from which a workgroup walks several of them; by class and by completeness."""
+every number of K ranges, hidden sizes beside its 1024-column workgroups, no multiple of 4, few tokens (a workgroup
+takes 1024 columns) and more than 1024 (it takes all of a token's); by class and by completeness."""
 import numpy as np
 import pytest
 import torch
@@ -24,6 +24,11 @@ CASES = [  # dtype, E, k, H, F, N, K ranges
     ("bf16", 16, 13, 2112, 256, 6, 4),
     ("bf16", 32, 23, 960, 64, 5, 1),
     ("bf16", 2, 2, 65600, 64, 2, 1),
+    ("bf16", 8, 2, 2112, 64, 682, 1),
+    ("bf16", 8, 3, 2112, 256, 683, 4),
+    ("bf16", 8, 1, 1088, 128, 1025, 2),
+    ("f32", 4, 2, 1030, 3, 1024, 1),
+    ("f32", 16, 5, 2052, 2, 1100, 1),
 ]
 
 
@@ -43,7 +48,18 @@ def test_combine(dtype, E, k, H, F, N, ks):
     prio = torch.from_numpy((np.arange(N) % 2).astype(np.uint8)).to(DEV)
     ctx.route(x, w, None)
     ctx.permute(prio)
-    ctx.expert_run(x, w)
+    yc, done = torch.full((N, H), 3.0, dtype=dt, device=DEV), torch.full((N,), 7, dtype=torch.uint8, device=DEV)
+    units = ctx.units()
+    ctx.expert_run(x, w, len(units) // 2)
+    ctx.combine_complete(yc, done)                # the tokens whose rows are all among these units
+    row_done = np.zeros(N * k, dtype=bool)
+    for _, _, row0, rows in units[: len(units) // 2]:
+        row_done[row0: row0 + rows] = True
+    want = row_done[ctx.get("inv").cpu().numpy().reshape(N, k)].all(1)
+    assert np.array_equal(done.cpu().numpy(), want)
+    some = yc.clone()
+    if len(units) // 2 < len(units):
+        ctx.expert_run(x, w)
     y = torch.full((N, H), 3.0, dtype=dt, device=DEV)
     ctx.combine(y, q.MOE_CLASS_LS)                # the odd tokens only
     torch.cuda.synchronize()
@@ -52,8 +68,9 @@ def test_combine(dtype, E, k, H, F, N, ks):
     ctx.combine(y)
     y32 = torch.zeros((N, H), device=DEV)
     ctx.combine(y32, q.MOE_CLASS_ALL | q.MOE_Y_F32)
-    done = torch.zeros(N, dtype=torch.uint8, device=DEV)
-    yc = torch.zeros_like(y)
+    assert torch.equal(some[torch.from_numpy(want).to(DEV)], y[torch.from_numpy(want).to(DEV)])
+    assert (some[torch.from_numpy(~want).to(DEV)] == 3.0).all()
+    yc.zero_()
     ctx.combine_complete(yc, done)
     torch.cuda.synchronize()
     assert torch.equal(ls[1::2], y[1::2]) and torch.equal(yc, y) and done.bool().all()
