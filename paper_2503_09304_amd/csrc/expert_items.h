@@ -13,8 +13,9 @@
 // Against packets of 4 segments x 8 column tiles dealt out whether full or not (14 half-empty packets
 // are 32 workgroups on six XCDs and 16 on two; with 11 column tiles the full packets all fall on even
 // XCDs): one token on 2 of 8 experts, H 4096, F 14336: gate-up 92 -> 73 us, layer 190 -> 171 us; 32 tokens
-// on 64 experts, H 2048, F 1408: 90 -> 74 us, 170 -> 154 us; 8192 tokens on the same 1.29 -> 1.265 ms; launches
-// that filled their packets are unchanged.
+// on 64 experts, H 2048, F 1408: 90 -> 74 us, 170 -> 154 us; 8192 tokens on the same 1.30 -> 1.23 ms.  Where the
+// packets kept an XCD to one expert of two segments the list was slower, by 1 % for 1531 tokens on 8 experts to 6 %
+// for 2048: those launches deal their experts out (see plan_items).
 // Other cuts, measured: a contiguous eighth of the list for each XCD: 8192 tokens on 64 experts +2 %,
 // 4-bit decode down projection 48 -> 64 us (four XCDs get all the long segments); eighths of equal cost
 // instead of equal count: 3584 tokens on 8 experts +9 % (a few more short items add a round); segments
@@ -59,6 +60,13 @@ __host__ __device__ inline bool item_of(unsigned id, unsigned items, unsigned &i
     return item < full + left * (x + 1) / kXcds;
 }
 
+// The same of a launch that deals its segments to the XCDs: XCD x has segments xcd[x] .. xcd[x+1] - 1.
+__host__ __device__ inline unsigned dealt_grid(const uint16_t (&xcd)[kXcds + 1], unsigned cols) {
+    unsigned most = 0;
+    for (int x = 0; x < kXcds; ++x) most = most < (unsigned)(xcd[x + 1] - xcd[x]) ? (unsigned)(xcd[x + 1] - xcd[x]) : most;
+    return kXcds * most * cols;
+}
+
 struct ItemPos { unsigned pos, cq; };       // segment in list order; column tile + K range * column tiles
 
 // item of the list -> (segment, column).  cols = column tiles * K ranges; place(pos, in, size) hands back
@@ -76,19 +84,17 @@ __host__ __device__ inline ItemPos item_pos(unsigned item, unsigned cols, Place 
     return {first + seg, blk * wide + (rb - seg * w)};
 }
 
-// item -> (unit, column) of a launch over n units of the device's unit list, in groups of kGroupSegs
-// consecutive units.  The host does not know the units' rows here and cannot sort them, so the list goes
-// by blocks of 8 columns, all units of a block before the next block: long and short units stay mixed to
-// the end of the launch, and with 4 groups each XCD keeps to the token tiles of one.  Measured on 1531
-// tokens, 8 experts (16 units of 256 and 127 rows, 4 K ranges) enqueued as one launch, us a layer: group by
-// group 1146 against 1134 with the packets; by blocks 1147 and 1142 against 1143 and 1145 with the packets.
-__host__ __device__ inline ItemPos unit_item_pos(unsigned item, unsigned n, unsigned cols) {
+// item -> (segment, column) of n segments in blocks of 8 columns, all segments of a block before the next block.
+// For one XCD's share of a launch that deals experts to XCDs (see plan_items), and for launches over n units of the
+// device's unit list, more than kMaxSegs of them, which are not sorted by expert.  There blocks of 4 units one after
+// the other are no faster or slower: 16384 tokens on 64 experts, H 2048, F 1408, 2.35 ms, skewed 20000 tokens 3.00 ms
+// either way, 20000 tokens on 256 experts, F 512, 1.64 ms.
+__host__ __device__ inline ItemPos column_item_pos(unsigned item, unsigned n, unsigned cols) {
     constexpr unsigned W = kXcdCus / kGroupSegs;
     const unsigned blk = item / (n * W), r = item - blk * (n * W);
     const unsigned left = cols - blk * W, w = left < W ? left : W;
-    const unsigned first = r / (w * kGroupSegs) * kGroupSegs, rb = r - first * w;
-    const unsigned seg = rb / w;
-    return {first + seg, blk * W + (rb - seg * w)};
+    const unsigned pos = r / w;
+    return {pos, blk * W + (r - pos * w)};
 }
 
 // True iff every weight element of the launch is read by one workgroup only: segs are sorted by
@@ -102,7 +108,23 @@ inline bool items_stream(const Seg *segs, int n) {
 // Orders the segments (sorted by expert and row) of one launch into groups.  Where experts have several
 // segments a group holds segments of one expert only, the expert with the most rows first; else the
 // groups are cut from the list sorted by length.
-inline void plan_items(const Seg *segs, int n, bool stream, ItemSeg *out) {
+// Returns true if the launch deals its groups to the XCDs: segments xcd[x] .. xcd[x+1] - 1 are XCD x's alone.
+// With the common list all XCDs work on the same expert at a time; where an expert has few segments, an XCD that
+// keeps to its own experts fetches fewer tokens for the same columns, if the shares (their cost in token tiles, the
+// largest over the mean) come out even.  Us a layer with the list / gate-up dealt out / down dealt out / both, top-2
+// of 8 experts, H 4096, F 14336 unless stated:
+//   32 experts, top-4, H 2048, F 1536, 4000 tokens (share 1.01) 397 / 391 / 393 / 389, 4-bit weights
+//   365 / 356 / 359 / 349; 64 experts, top-8, H 2048, F 1408, 4-bit, 3000 tokens, skewed 503 / 497 / 496 / 489:
+//   dealt out up to 1.02;
+//   two segments per expert: 1100 tokens (1.10) 931 / 918 / 928 / 915, 1300 tokens (1.02) 1013 / 984 / 1013 / 987,
+//   1531 tokens (1.05) 1106 / 1095 / 1106 / 1089, enqueued 1156 / 1144 / 1154 / 1140: dealt out up to 1.10, except
+//   for 4-bit weights (1531 tokens 896 / 907 / 900 / 911);
+//   2048 tokens, two or three segments (1.03): 1553 / 1580 / 1464 / 1472: the down projection's 320 items are 1.25
+//   rounds of the chip, and the list's last quarter takes as long as a round: dealt out below two rounds up to 1.10;
+//   with 4 K ranges, 5 rounds, 1481 / 1498 / 1497 / 1508: the list.
+// Uneven shares lose: 1300 tokens, skewed (2.5) 1026 with the list / 1714.  So do more segments per expert, even
+// shares or not: 2500 tokens (3 segments, 1.05) 1742 / 1766, 3584 tokens, 4-bit (4 segments, 1.02) 1943 / 1966.
+inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool four_bit, ItemSeg *out, uint16_t (&xcd)[kXcds + 1]) {
     struct Group { int first, count, rows; };
     std::vector<Seg> s(segs, segs + n);
     std::vector<Group> groups;
@@ -123,11 +145,40 @@ inline void plan_items(const Seg *segs, int n, bool stream, ItemSeg *out) {
         std::stable_sort(groups.begin(), groups.end(), [](const Group &x, const Group &y) { return x.rows > y.rows; });
     }
     int at = 0;
-    for (const Group &g : groups)
+    auto place = [&](const Group &g) {
         for (int i = 0; i < g.count; ++i) {
             const Seg &v = s[g.first + i];
             out[at++] = ItemSeg{v.row0, v.rows, (uint8_t)v.expert, (uint8_t)(i | g.count << 4)};
         }
+    };
+    int experts = 1;
+    for (int i = 1; i < n; ++i) experts += s[i].expert != s[i - 1].expert;
+    if (!stream && 2 * n <= 5 * experts) {
+        // each group, the one of the most rows first, to the XCD with the least; up to 3 token tiles a segment takes
+        // as long as its weights
+        long load[kXcds] = {}, total = 0;
+        std::vector<int> owner;
+        for (const Group &g : groups) {
+            long cost = 0;
+            for (int i = 0; i < g.count; ++i) cost += std::max((s[g.first + i].rows + 31) / 32, 3);
+            owner.push_back((int)(std::min_element(load, load + kXcds) - load));
+            load[owner.back()] += cost;
+            total += cost;
+        }
+        const long share = 100 * kXcds * *std::max_element(load, load + kXcds);      // of the mean, in percent x total
+        const bool few = (!four_bit && n <= 2 * experts) || (unsigned)n * cols < 2 * kXcds * kXcdCus;
+        if (share <= (few ? 110 : 102) * total) {
+            for (int x = 0; x < kXcds; ++x) {
+                xcd[x] = (uint16_t)at;
+                for (size_t i = 0; i < groups.size(); ++i)
+                    if (owner[i] == x) place(groups[i]);
+            }
+            xcd[kXcds] = (uint16_t)at;
+            return true;
+        }
+    }
+    for (const Group &g : groups) place(g);
+    return false;
 }
 
 }  // namespace qmoe

@@ -146,7 +146,6 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
     b.plane = 0;
     b.nseg = a.segs ? a.nseg : 0;
     const bool stream = b.nseg > 0 && items_stream(a.segs, b.nseg);
-    if (b.nseg > 0) plan_items(a.segs, b.nseg, stream, b.seg);
     const int tiles = (a.max_rows + 31) / 32;
     const unsigned n = b.nseg > 0 ? (unsigned)b.nseg : a.nu;
     b.k = gu_in;
@@ -159,7 +158,10 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
     };
     auto launch = [&](bool gateup) {
         // segments in the arguments are one launch, a range of the unit list as many as it takes
-        const unsigned cols = (unsigned)(b.k.col_tiles * b.ksplit), most = b.nseg > 0 ? n : segs_per_launch(cols);
+        const unsigned cols = (unsigned)(b.k.col_tiles * b.ksplit);
+        if (b.nseg > 0 && (gateup || !stream))       // the order of a launch that streams does not depend on its columns
+            b.dealt = plan_items(a.segs, b.nseg, stream, cols, a.wfmt == bf16k::WF_MXFP4, b.seg, b.xcd);
+        const unsigned most = b.nseg > 0 ? n : segs_per_launch(cols);
         for (unsigned at = 0; at < n; at += (unsigned)b.k.nu) {
             b.k.u0 = a.u0 + at;
             b.k.nu = (int)std::min(most, n - at);

@@ -94,6 +94,8 @@ struct BArgs {
     long plane;          // elements between partial planes
     int nseg;            // > 0: work on seg[0..nseg); 0: on units[u0 .. u0+nu) of the device list
     unsigned items;      // (segments or units) x column tiles x K ranges
+    bool dealt;          // XCD x works on seg[xcd[x]..xcd[x+1])
+    uint16_t xcd[kXcds + 1];
     ItemSeg seg[kMaxSegs];
 };
 
@@ -440,16 +442,24 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
 
 // Workgroup id -> (unit, column tile, K range): see expert_items.h.
 __device__ __forceinline__ bool map_block(const BArgs &b, moe_unit &un, int &ct, int &kq) {
-    unsigned item;
-    if (!item_of(blockIdx.x, b.items, item)) return false;
     const unsigned cols = (unsigned)(b.k.col_tiles * b.ksplit);
+    unsigned item;
     ItemPos ip;
+    if (b.dealt) {
+        const unsigned x = blockIdx.x % kXcds, first = b.xcd[x], n = b.xcd[x + 1] - first;
+        item = blockIdx.x / kXcds;
+        if (item >= n * cols) return false;
+        ip = column_item_pos(item, n, cols);
+        ip.pos += first;
+    } else {
+        if (!item_of(blockIdx.x, b.items, item)) return false;
+        if (b.nseg == 0) ip = column_item_pos(item, (unsigned)b.k.nu, cols);
+        else ip = item_pos(item, cols, [&](unsigned q, unsigned &in, unsigned &size) { in = b.seg[q].grp & 15; size = b.seg[q].grp >> 4; });
+    }
     if (b.nseg > 0) {
-        ip = item_pos(item, cols, [&](unsigned q, unsigned &in, unsigned &size) { in = b.seg[q].grp & 15; size = b.seg[q].grp >> 4; });
         const ItemSeg g = b.seg[ip.pos];
         un.expert = g.expert; un.cls = 0; un.row0 = (int)g.row0; un.rows = g.rows;
     } else {
-        ip = unit_item_pos(item, (unsigned)b.k.nu, cols);
         un = b.k.units[b.k.u0 + ip.pos];
     }
     kq = (int)ip.cq / b.k.col_tiles;
@@ -492,7 +502,7 @@ __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
 
 template <int TCAP, bool GATEUP, int WF, bool STREAM>
 void launch1(const BArgs &b, hipStream_t s) {
-    hipLaunchKernelGGL((expert_bf16<TCAP, GATEUP, WF, STREAM>), dim3(item_grid(b.items)), dim3(256), 0, s, b);
+    hipLaunchKernelGGL((expert_bf16<TCAP, GATEUP, WF, STREAM>), dim3(b.dealt ? dealt_grid(b.xcd, (unsigned)(b.k.col_tiles * b.ksplit)) : item_grid(b.items)), dim3(256), 0, s, b);
 }
 
 template <bool GATEUP, int WF, bool STREAM>
