@@ -440,12 +440,13 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     }
 }
 
-// Workgroup id -> (unit, column tile, K range): see expert_items.h.
+// Workgroup id -> (unit, column tile, K range): see expert_items.h.  A launch that streams deals nothing to the XCDs.
+template <bool STREAM>
 __device__ __forceinline__ bool map_block(const BArgs &b, moe_unit &un, int &ct, int &kq) {
     const unsigned cols = (unsigned)(b.k.col_tiles * b.ksplit);
     unsigned item;
     ItemPos ip;
-    if (b.dealt) {
+    if (!STREAM && b.dealt) {
         const unsigned x = blockIdx.x % kXcds, first = b.xcd[x], n = b.xcd[x + 1] - first;
         item = blockIdx.x / kXcds;
         if (item >= n * cols) return false;
@@ -487,7 +488,7 @@ __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
     }
     int ct, kq;
     moe_unit un;
-    if (!map_block(b, un, ct, kq)) return;
+    if (!map_block<STREAM>(b, un, ct, kq)) return;
     const int t_cnt = (un.rows + 31) >> 5;
     // Prefetch distance of the weights: 2 iterations for the three-stage variants (their loop is unrolled by
     // a multiple of 3) and the 2-tile variant, 3 for the 1-tile variant.
