@@ -49,6 +49,18 @@ def down_bytes(cfg, counts, es, ws, ksplit):
     return int(touched * cfg.H * cfg.F * ws) + cfg.A * cfg.F * es + cfg.A * cfg.H * 4 + planes
 
 
+def k_ranges(c):
+    """K ranges of the down projection of a context with this configuration.  With down_ksplit = 0 the library
+    chooses (include/qmoe.h) and its workspace size shows what: every range but the first has a plane in it."""
+    import paper_2503_09304_amd as q
+
+    if c.down_ksplit or c.dtype != q.MOE_BF16:
+        return c.down_ksplit or 1
+    size = {ks: q.moe_workspace_bytes(q.MoeConfig(c.E, c.k, c.H, c.F, c.dtype, c.chunk_rows, c.max_tokens, ks))
+            for ks in (0, 1, 2, 4) if ks < 2 or c.F % (64 * ks) == 0}
+    return next(ks for ks in size if ks and size[ks] == size[0])
+
+
 def cpu_model() -> str:
     try:
         with open("/proc/cpuinfo") as f:
@@ -177,17 +189,7 @@ def measure(cfg, inp, dw, steps, warmup, mx, rowmajor, cuts=0, down_ksplit=0):
         with_cuts = {"cuts_at_units": cps, "ms_per_step": round(ms_cut, 4), "tokens_per_s": round(cfg.N / (ms_cut * 1e-3), 1),
                      "slowdown": round(ms_cut / ms_per_step, 4)}
 
-    # what down_ksplit = 0 picks (include/qmoe.h): the fewest K ranges that give every CU a workgroup
-    ksplit = 1
-    if cfg.N * cfg.k <= 256 * cfg.E:
-        wgs = cfg.E * ((cfg.H + 255) // 256)
-        if wgs >= 256:
-            ksplit = 1
-        elif 2 * wgs >= 256 and cfg.F % 128 == 0:
-            ksplit = 2
-        else:
-            ksplit = 4 if cfg.F % 256 == 0 else (2 if cfg.F % 128 == 0 else 1)
-    ksplit = force_ks or ksplit
+    ksplit = k_ranges(g.ctx.cfg)
     gu_ms, gu_n = prof["gate_up"]
     dn_ms, dn_n = prof["down"]
     gu_avg_ms = gu_ms / max(gu_n, 1)

@@ -29,3 +29,15 @@ def test_few_tokens_split_the_down_projection_by_the_experts_they_reach():
     assert [picks(8, 2, 4096, 14336, n) for n in (1, 2, 5, 8, 512)] == [4, 4, 4, 2, 2]
     assert [picks(64, 8, 2048, 1536, n) for n in (1, 2, 3, 8)] == [4, 4, 2, 1]
     assert picks(64, 8, 2048, 1408, 1) == 2          # F is a multiple of 128, not of 256
+
+
+def test_the_benchmark_prices_the_planes_that_the_library_chose():
+    import paper_2503_09304_amd as q
+    from bench import k_ranges
+
+    def of(tokens, ks=0, E=8, k=2, H=4096, F=14336, dtype=q.MOE_BF16):
+        return k_ranges(q.MoeConfig(E, k, H, F, dtype, 256, tokens, ks))
+
+    assert [of(n) for n in (1, 5, 8, 512, 3584)] == [4, 4, 2, 2, 1]
+    assert of(64, ks=4) == 4 and of(3584, ks=2) == 2
+    assert of(3, E=64, k=8, H=2048, F=1536) == 2 and of(64, E=4, H=128, F=256, dtype=q.MOE_F32) == 1
