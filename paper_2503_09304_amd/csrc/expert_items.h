@@ -61,9 +61,9 @@ __host__ __device__ inline bool item_of(unsigned id, unsigned items, unsigned &i
 }
 
 // The same of a launch that deals its segments to the XCDs: XCD x has segments xcd[x] .. xcd[x+1] - 1.
-__host__ __device__ inline unsigned dealt_grid(const uint16_t (&xcd)[kXcds + 1], unsigned cols) {
+__host__ __device__ inline unsigned dealt_grid(const uint32_t (&xcd)[kXcds + 1], unsigned cols) {
     unsigned most = 0;
-    for (int x = 0; x < kXcds; ++x) most = most < (unsigned)(xcd[x + 1] - xcd[x]) ? (unsigned)(xcd[x + 1] - xcd[x]) : most;
+    for (int x = 0; x < kXcds; ++x) most = most < xcd[x + 1] - xcd[x] ? xcd[x + 1] - xcd[x] : most;
     return kXcds * most * cols;
 }
 
@@ -124,7 +124,7 @@ inline bool items_stream(const Seg *segs, int n) {
 //   with 4 K ranges, 5 rounds, 1481 / 1498 / 1497 / 1508: the list.
 // Uneven shares lose: 1300 tokens, skewed (2.5) 1026 with the list / 1714.  So do more segments per expert, even
 // shares or not: 2500 tokens (3 segments, 1.05) 1742 / 1766, 3584 tokens, 4-bit (4 segments, 1.02) 1943 / 1966.
-inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool four_bit, ItemSeg *out, uint16_t (&xcd)[kXcds + 1]) {
+inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool four_bit, ItemSeg *out, uint32_t (&xcd)[kXcds + 1]) {
     struct Group { int first, count, rows; };
     std::vector<Seg> s(segs, segs + n);
     std::vector<Group> groups;
@@ -169,11 +169,11 @@ inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool 
         const bool few = (!four_bit && n <= 2 * experts) || (unsigned)n * cols < 2 * kXcds * kXcdCus;
         if (share <= (few ? 110 : 102) * total) {
             for (int x = 0; x < kXcds; ++x) {
-                xcd[x] = (uint16_t)at;
+                xcd[x] = (uint32_t)at;
                 for (size_t i = 0; i < groups.size(); ++i)
                     if (owner[i] == x) place(groups[i]);
             }
-            xcd[kXcds] = (uint16_t)at;
+            xcd[kXcds] = (uint32_t)at;
             return true;
         }
     }

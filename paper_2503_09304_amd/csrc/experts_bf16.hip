@@ -156,16 +156,17 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
         else if (a.wfmt == bf16k::WF_PACKED) bf16k::launch_expert_kernels<bf16k::WF_PACKED>(gateup, tiles, stream, b, s);
         else bf16k::launch_expert_kernels<bf16k::WF_ROWMAJOR>(gateup, tiles, stream, b, s);
     };
+    bool dealt = false;
     auto launch = [&](bool gateup) {
         // segments in the arguments are one launch, a range of the unit list as many as it takes
         const unsigned cols = (unsigned)(b.k.col_tiles * b.ksplit);
         if (b.nseg > 0 && (gateup || !stream))       // the order of a launch that streams does not depend on its columns
-            b.dealt = plan_items(a.segs, b.nseg, stream, cols, a.wfmt == bf16k::WF_MXFP4, b.seg, b.xcd);
+            dealt = plan_items(a.segs, b.nseg, stream, cols, a.wfmt == bf16k::WF_MXFP4, b.seg, b.xcd);
         const unsigned most = b.nseg > 0 ? n : segs_per_launch(cols);
         for (unsigned at = 0; at < n; at += (unsigned)b.k.nu) {
             b.k.u0 = a.u0 + at;
             b.k.nu = (int)std::min(most, n - at);
-            b.items = (unsigned)b.k.nu * cols;
+            b.items = dealt ? 0 : (unsigned)b.k.nu * cols;
             launch_one(gateup);
         }
     };

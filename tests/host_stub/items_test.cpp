@@ -31,7 +31,7 @@ static void walk(int n, unsigned cols, Pos &&pos) {
 }
 
 // The same for a launch that deals its segments to the XCDs: the shares differ by at most 10 % of the mean.
-static void walk_dealt(int n, unsigned cols, const uint16_t (&xcd)[kXcds + 1], const std::vector<ItemSeg> &it) {
+static void walk_dealt(int n, unsigned cols, const uint32_t (&xcd)[kXcds + 1], const std::vector<ItemSeg> &it) {
     std::vector<int> seen((size_t)n * cols, 0);
     long load[kXcds] = {}, total = 0;
     for (unsigned w = 0; w < dealt_grid(xcd, cols); ++w) {
@@ -60,7 +60,7 @@ int main() {
                         segs.push_back(Seg{(uint32_t)segs.size() * 256, (uint16_t)(1 + std::rand() % 256), (uint16_t)e});
                 const bool stream = items_stream(segs.data(), n);
                 std::vector<ItemSeg> it(n);
-                uint16_t xcd[kXcds + 1];
+                uint32_t xcd[kXcds + 1];
                 const bool dealt = plan_items(segs.data(), n, stream, cols, most == 1, it.data(), xcd);
                 std::vector<int> taken(n, 0);
                 for (int i = 0; i < n; ++i) {
@@ -99,7 +99,7 @@ int main() {
                 }
             }
             std::vector<ItemSeg> it(segs.size());
-            uint16_t xcd[kXcds + 1];
+            uint32_t xcd[kXcds + 1];
             const bool yes = plan_items(segs.data(), (int)segs.size(), items_stream(segs.data(), (int)segs.size()), cols, four_bit, it.data(), xcd);
             for (int x = 0; yes && x < kXcds; ++x)                                          // an expert is on one XCD
                 for (int i = 0; i < (int)it.size(); ++i)
