@@ -13,7 +13,7 @@
 // Against packets of 4 segments x 8 column tiles dealt out whether full or not (14 half-empty packets
 // are 32 workgroups on six XCDs and 16 on two; with 11 column tiles the full packets all fall on even
 // XCDs): one token on 2 of 8 experts, H 4096, F 14336: gate-up 92 -> 73 us, layer 190 -> 171 us; 32 tokens
-// on 64 experts, H 2048, F 1408: 90 -> 74 us, 170 -> 154 us; 8192 tokens on the same 1.30 -> 1.23 ms.  Where the
+// on 64 experts, H 2048, F 1408: 90 -> 74 us, 170 -> 154 us; 8192 tokens on the same 1.29 -> 1.25 ms.  Where the
 // packets kept an XCD to one expert of two segments the list was slower, by 1 % for 1531 tokens on 8 experts to 6 %
 // for 2048: those launches deal their experts out (see plan_items).
 // Other cuts, measured: a contiguous eighth of the list for each XCD: 8192 tokens on 64 experts +2 %,

@@ -15,7 +15,7 @@
 // Each output is one accumulation chain over K in an order that K alone fixes: results do not
 // depend on the segment or tile a row sits in.
 // Measured on 509 tokens x 8 experts, top-2, H 1024, F 2048 (gate-up / down): 409 / 369 us as 64x64 FMA
-// tiles with scalar loads, 98 / 57 us here (MFMA pipe 68 % busy); 64 tokens x 4 experts, H 128, F 256:
+// tiles with scalar loads, 98 / 56 us here (MFMA pipe 67 % / 53 % busy); 64 tokens x 4 experts, H 128, F 256:
 // 26 / 33 us, 5 / 5 us here.
 #include <hip/hip_runtime.h>
 
