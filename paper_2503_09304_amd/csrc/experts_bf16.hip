@@ -152,9 +152,10 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
     b.k.cw = a.wave_cols ? a.wave_cols : gate_up_wave_columns(stream, a.wfmt, tiles, (int)n, a.F);
     b.k.col_tiles = (a.F + 4 * b.k.cw - 1) / (4 * b.k.cw);
     auto launch_one = [&](bool gateup) {
-        if (a.wfmt == bf16k::WF_MXFP4) bf16k::launch_expert_kernels<bf16k::WF_MXFP4>(gateup, tiles, stream, b, s);
-        else if (a.wfmt == bf16k::WF_PACKED) bf16k::launch_expert_kernels<bf16k::WF_PACKED>(gateup, tiles, stream, b, s);
-        else bf16k::launch_expert_kernels<bf16k::WF_ROWMAJOR>(gateup, tiles, stream, b, s);
+        using namespace bf16k;
+        if (a.wfmt == WF_MXFP4) gateup ? launch_expert_kernel<WF_MXFP4, true>(tiles, stream, b, s) : launch_expert_kernel<WF_MXFP4, false>(tiles, stream, b, s);
+        else if (a.wfmt == WF_PACKED) gateup ? launch_expert_kernel<WF_PACKED, true>(tiles, stream, b, s) : launch_expert_kernel<WF_PACKED, false>(tiles, stream, b, s);
+        else gateup ? launch_expert_kernel<WF_ROWMAJOR, true>(tiles, stream, b, s) : launch_expert_kernel<WF_ROWMAJOR, false>(tiles, stream, b, s);
     };
     bool dealt = false;
     auto launch = [&](bool gateup) {

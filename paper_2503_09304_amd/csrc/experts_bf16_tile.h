@@ -1,17 +1,24 @@
 // bf16 expert kernels (gate-up with fused SwiGLU, and down projection) on MFMA: the templates.
-// Included by experts_bf16.hip (dispatch) and by experts_bf16_w<WF>.hip (one instantiation per weight
-// format).
+// Included by experts_bf16.hip (dispatch) and by experts_bf16_w<WF>_<kernel>.hip (one instantiation per weight
+// format and kernel).
 //
 // All three weight matrices are [rows_out, K] with K contiguous, and so are the activations, so
 // both MFMA operands are read 8 consecutive K-elements (16 bytes) per lane with no transposition.
-// v_mfma_f32_32x32x16_bf16: A = 32 tokens x 16 k, B = 32 weight rows x 16 k, D[token, weight row]
+// v_mfma_f32_16x16x32_bf16: A = 16 weight rows x 32 k, B = 16 tokens x 32 k, D[weight row, token]
 // in fp32.  A workgroup has 4 waves.  Each wave owns 64 weight rows (gate-up: 32 rows of W1 and the
 // same 32 of W3, so the gate and up value of one (token, f) meet in one lane and register) and every
-// token tile of the unit.  No two waves use the same weight fragment, so weights go straight from
-// global memory into MFMA operand registers (with the packed layout every wave load is one
-// contiguous KiB); only the token tile (gathered x rows, or act rows), which all 4 waves share, is
-// staged in LDS, double-buffered, its 16-byte slots XOR-swizzled by row so that the 32 rows read
-// by one ds_read_b128 fall into distinct banks.
+// 16-token fragment of the unit.  No two waves use the same weight fragment, so weights go straight from
+// global memory into MFMA operand registers (with the packed layout a wave load is a contiguous KiB or four runs
+// of 256 bytes); only the token tile (gathered x rows, or act rows), which all 4 waves share, is
+// staged in LDS, double-buffered, its 16-byte slots XOR-swizzled by row so that the 16 rows read
+// by one ds_read_b128 pass fall into distinct banks.
+//
+// Why 16x16x32.  From about 150 rows an expert on these kernels run at the clock that the power limit leaves
+// them, so what counts is energy per flop: on random operands a loop of nothing but MFMAs sustains 2.00-2.06
+// PFLOP/s with 16x16x32 and 1.79-1.82 with 32x32x16.  Fragments of 16 tokens also leave less padding than tiles of 32.  Against
+// the same kernel on 32x32x16 (us, gate-up / down): 3584 tokens on 8 experts, H 4096, F 14336 1353 / 711 and 1255 / 682,
+// with 4-bit weights 1237 / 612 and 1173 / 592; 8192 tokens on 64 experts, H 2048, F 1408 657 / 422 and 613 / 401; 512
+// tokens on 8 experts with row-major weights, where a lane's rows now come 64 contiguous bytes at a time, 816 / 382 and 510 / 256.
 //
 // Pipeline of one K-iteration (64 k), prefetch distance D: issue the global loads of the token
 // pieces and weight fragments for it+D (register rings of D+1 sets), run the MFMAs of iteration it,
@@ -26,8 +33,8 @@
 // ((p0+p1)+p2)+p3.
 //
 // A launch works on row segments: the host joins the row-adjacent units of one expert in a call (the
-// LS and BE part of its queue, consecutive chunks) and cuts each such run into segments of at most 8
-// token tiles with equal tile counts, so that one pass over the weights serves them and workgroups
+// LS and BE part of its queue, consecutive chunks) and cuts each such run into segments of at most 256
+// rows with equal counts of 32, so that one pass over the weights serves them and workgroups
 // that share weight tiles keep the same pace.
 //
 // Determinism.  Each output element is one chain of MFMA accumulations over K in ascending order
@@ -52,18 +59,15 @@ namespace bf16k {
 // MFMA-ordered blocks, turned into bf16 operands in registers (exactly: every such value is a bf16).
 enum { WF_ROWMAJOR = 0, WF_PACKED = 1, WF_MXFP4 = 2 };
 
-// Smallest number of token tiles whose variant keeps three LDS stages (see P3 in expert_tile).
-#ifndef QMOE_P3_MIN_T
-#define QMOE_P3_MIN_T 4
-#endif
-constexpr int kP3MinT = QMOE_P3_MIN_T;
+// Smallest number of 32-row pieces whose variant keeps three LDS stages (see P3 in expert_tile).
+constexpr int kP3MinT = 3;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 // silu(z) = z / (1 + e^-z) as one exponential and one reciprocal (v_exp_f32, v_rcp_f32: about 1 ulp
 // each, far below the bf16 rounding the product gets next).  An IEEE division costs three times the
@@ -87,6 +91,27 @@ __device__ __forceinline__ void static_for(F &&f) {
     static_for_impl<N>(f, std::make_integer_sequence<int, N>{});
 }
 
+// acc += weights x tokens (16 weight rows x 16 tokens x 32 k).  In assembly so that an accumulator stays
+// in its place: given the builtin, the compiler writes 16 x 16 results to other registers than it read them from and
+// moves them back (428 moves per 336 MFMAs with 7 token tiles).  It does not see the matrix unit's hazards here: a vector
+// instruction that writes an operand must stand two wait states before (the operands come from loads; swaps are followed by
+// such a wait, the conversions of 4-bit weights stand slots before), and after the last MFMA of an iteration eight wait states keep anything else off the accumulators.
+template <bool LAST>
+__device__ __forceinline__ void mma(f32x4 &c, const bf16x8 &w, const bf16x8 &x) {
+    if constexpr (LAST) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7" : "+a"(c) : "v"(w), "v"(x));
+    else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
+}
+
+// Pointers into global memory, said to be so: the compiler gives up tracing the larger kernels' pointers back to the
+// arguments and takes loads that may go to LDS too, which wait for one another (gate-up at half its speed).
+typedef const __attribute__((address_space(1))) char *gchar;
+template <class V>
+__device__ __forceinline__ V gload(gchar p) { return *reinterpret_cast<const __attribute__((address_space(1))) V *>(p); }
+template <class V>
+__device__ __forceinline__ V gload_nt(gchar p) { return __builtin_nontemporal_load(reinterpret_cast<const __attribute__((address_space(1))) V *>(p)); }
+template <class V>
+__device__ __forceinline__ void gstore_nt(const V &v, void *p) { __builtin_nontemporal_store(v, (__attribute__((address_space(1))) V *)p); }
+
 // Launch-local arguments of the bf16 kernels.
 struct BArgs {
     KArgs k;
@@ -99,270 +124,257 @@ struct BArgs {
 };
 
 // One (unit, column tile, K range) on a workgroup.
-template <int T, bool GATEUP, int WF, bool STREAM, int D>
+template <int NF, bool GATEUP, int WF, bool STREAM, int D>
 __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, const int ct, const int kq, const int ksplit,
                                             const long plane, char *lds) {
     // Stoppable launches: the workgroup leaves behind the prologue's barrier if the stop word is set or
     // (down projection) the gate-up workgroups of its rows did not all run.
     __shared__ int s_run;
     const WgProbe probe = wg_probe(p, un.row0);
+    constexpr int T = (NF + 1) / 2;        // 32-row pieces of the token tile that a thread stages
     constexpr int ROWS = T * 32;
     constexpr int STAGE = ROWS * 128;      // bytes of one LDS stage: 64 bf16 per row
-    // The variants of 4 and more token tiles keep three token-tile stages, write tile it+2 during
+    // The variants of more than 64 rows keep three token-tile stages, write tile it+2 during
     // iteration it, and so may read the first fragments of tile it+1 before the iteration's barrier;
-    // the LDS latency after the barrier disappears from the MFMA stream (8 tiles: -1.7 % on the
-    // 3584-token prefill; 4-5 tiles: gate-up -1.2 % on the 512-token batch, measured against the
-    // two-stage form on one machine).  Below 4 tiles an iteration is bound by the weight stream alone.
+    // the LDS latency after the barrier disappears from the MFMA stream (measured on 32x32x16 tiles against the two-stage
+    // form: 256 rows -1.7 % on the 3584-token prefill; 128 to 160 rows gate-up -1.2 % on the 512-token batch).
+    // Below, an iteration is bound by the weight stream alone.
     constexpr bool P3 = T >= kP3MinT;
     // Output columns per wave.  Gate-up: 32, or fewer (p.cw, a multiple of 4) on launches whose
     // workgroup count would otherwise end in a partly filled round of the chip; the wave's MFMA rows
     // beyond p.cw repeat its last weight row and are dropped in the epilogue.
     const int cpw = GATEUP ? p.cw : 64;
     const int rows = un.rows;
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-    const int lr = l & 31, lh = l >> 5;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int lr = l & 15, lg = l >> 4;
     const int Kg = p.K / ksplit;           // this workgroup's K range: [kq*Kg, (kq+1)*Kg)
     const int iters = Kg / 64;
     const int col_base = ct * (4 * cpw) + w * cpw;
-    // gate-up: the weight row of this lane, and its place in the 32-row tiles of the packed formats
-    const int grow = min(col_base + min(lr, cpw - 1), p.ncols - 1);
-    const int gnt = grow >> 5, grr = grow & 31;
 
-    // ---- weight rows of this lane (B operand) ----
-    // Row-major: lane = (row l%32, k-half l/32), 16 elements per k-step, 64 per iteration.
-    // Packed: the wave's 1 KiB block of k-step s of row tile nt starts at (nt*(K/16)+s)*512.
-    // MXFP4: per (row tile, iteration) one KiB of codes (lane l: 16 bytes = the 8 elements of each
-    // of the 4 k-steps) and 64 bytes of scales (row l%32: the two e8m0 bytes of the iteration's two
-    // 32-element blocks).
+    // ---- weight rows of this lane ----
+    // A wave has two matrices of 32 rows (gate-up: W1, W3; down: the two halves of its 64 rows of W2), each in two row
+    // halves of 16 (rt).  Of an iteration's 64 k, eight pieces of 8, MFMA step j (0, 1) takes for lane group lg piece
+    // 4j + 2*(lg%2) + lg/2, tokens and weights alike: any order does, and this one is a single swap of lane groups away
+    // from the 4-bit blocks (see dequant).
+    // A load = uniform base of the matrix + the lane's 32-bit offset + constants.
+    // Row-major: 16 bytes of the lane's row, pieces 2j apart 32 bytes.
+    // Packed: the 1 KiB block of k-step s of row tile nt starts at (nt*(K/16)+s)*1024 bytes; pieces (s, half) of the
+    // 32 rows lie 512 bytes apart: a load is four runs of 256 bytes.
+    // MXFP4: per (row tile, iteration) one KiB of codes (lane l: 16 bytes, the words of row l%32's k half l/32 in each of
+    // the 4 k-steps) and 64 bytes of scales (row l%32: the two e8m0 bytes of the iteration's two 32-element blocks).
     constexpr bool PACKED = WF == WF_PACKED;
     constexpr bool MX = WF == WF_MXFP4;
-    constexpr int BKS = PACKED ? 512 : 16;   // elements between k-steps
-    constexpr int BIT = PACKED ? 2048 : 64;  // elements between iterations
-    const uint16_t *bptr[2];
-    const char *cptr[2];                     // MXFP4 codes
-    const char *sptr[2];                     // MXFP4 scales
-    if constexpr (MX) {
+    // Gate-up launches that may have waves of fewer than 32 columns read the packed blocks whole (row l%32, half l/32) and
+    // swap lane groups into place: a wave's rows then start anywhere in a row tile, and loads of 16 rows would ask for
+    // the lines at their edges twice (64 tokens on 8 experts, 28 columns: 302 us with such loads, 293 so).
+    constexpr bool SWAP = PACKED && STREAM && GATEUP && NF <= 6;
+    constexpr int BJ = PACKED ? 2048 : 64;      // bytes between the two MFMA steps
+    constexpr int BIT = PACKED ? 4096 : (MX ? 1024 : 128);   // bytes between iterations (MXFP4: of codes)
+    gchar bbase[2], sbase[2];                   // the matrices (MXFP4: codes and scales), at this workgroup's K range
+    unsigned boff[2][2], soff[2];               // [matrix][row half]; MXFP4: [matrix][0], one load for both halves
+    {
+        gchar e0 = (gchar)p.b0, e1 = GATEUP ? (gchar)p.b1 : e0;
+        const long ebytes = MX ? p.b_estride >> 1 : p.b_estride * 2;
+        e0 += un.expert * ebytes; e1 += un.expert * ebytes;
         const int ntiles = p.ncols >> 5;
-        const int nt0 = GATEUP ? gnt : min(col_base >> 5, ntiles - 1);
-        const int nt1 = GATEUP ? gnt : min((col_base >> 5) + 1, ntiles - 1);
-        const int rr = GATEUP ? grr : lr;
-        const long kblocks = p.K >> 6;                              // iterations per row tile
-        const char *c0 = (const char *)p.b0 + (long)un.expert * (p.b_estride >> 1);
-        const char *c1 = GATEUP ? (const char *)p.b1 + (long)un.expert * (p.b_estride >> 1) : c0;
-        const char *s0 = (const char *)p.s0 + (long)un.expert * (p.b_estride >> 5);
-        const char *s1 = GATEUP ? (const char *)p.s1 + (long)un.expert * (p.b_estride >> 5) : s0;
-        const long it0 = (long)kq * (Kg >> 6);
-        cptr[0] = c0 + ((nt0 * kblocks + it0) * 64 + lh * 32 + rr) * 16;
-        cptr[1] = c1 + ((nt1 * kblocks + it0) * 64 + lh * 32 + rr) * 16;
-        sptr[0] = s0 + ((nt0 * kblocks + it0) * 32 + rr) * 2;
-        sptr[1] = s1 + ((nt1 * kblocks + it0) * 32 + rr) * 2;
-        bptr[0] = bptr[1] = nullptr;
-    } else {
-        cptr[0] = cptr[1] = sptr[0] = sptr[1] = nullptr;
-        const uint16_t *b0 = (const uint16_t *)p.b0 + (long)un.expert * p.b_estride;
-        const uint16_t *b1 = GATEUP ? (const uint16_t *)p.b1 + (long)un.expert * p.b_estride : b0;
-        if (PACKED) {
-            const int ntiles = p.ncols >> 5;
-            const long tile_elems = (long)p.K * 32;
-            const long koff = (long)kq * (Kg / 16) * 512 + (lh * 32 + (GATEUP ? grr : lr)) * 8;
-            const int nt0 = GATEUP ? gnt : min(col_base >> 5, ntiles - 1);
-            const int nt1 = GATEUP ? gnt : min((col_base >> 5) + 1, ntiles - 1);
-            bptr[0] = b0 + nt0 * tile_elems + koff;
-            bptr[1] = b1 + nt1 * tile_elems + koff;
-        } else {
-            const int c0 = GATEUP ? grow : min(col_base + lr, p.ncols - 1);
-            const int c1 = GATEUP ? c0 : min(col_base + 32 + lr, p.ncols - 1);
-            bptr[0] = b0 + (long)c0 * p.K + kq * Kg + lh * 8;
-            bptr[1] = b1 + (long)c1 * p.K + kq * Kg + lh * 8;
+        const int first = min(col_base, p.ncols - 1);          // rows from p.ncols on repeat the last one
+        const int lane_piece = PACKED ? (lg & 1) * 1024 + (lg >> 1) * 512 : (lg & 1) * 32 + (lg >> 1) * 16;
+        const long kblocks = p.K >> 6, tile_bytes = kblocks * BIT;                  // packed formats: one row tile
+        const long k0 = (long)kq * (Kg >> 6) * BIT;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            gchar e = n ? e1 : e0;
+            const int nt = GATEUP ? first >> 5 : min((col_base >> 5) + n, ntiles - 1);
+            if constexpr (PACKED || MX) bbase[n] = e + nt * tile_bytes + k0;
+            else bbase[n] = e + (long)first * p.K * 2 + k0;
+            if constexpr (MX) {
+                gchar s = (gchar)(GATEUP && n ? p.s1 : p.s0) + un.expert * (p.b_estride >> 5);
+                sbase[n] = s + (nt * kblocks + (long)kq * (Kg >> 6)) * 64;
+            } else sbase[n] = nullptr;
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                const int r = MX || SWAP ? l & 31 : rt * 16 + lr;
+                const int row = GATEUP ? min(col_base + min(r, cpw - 1), p.ncols - 1) : (PACKED || MX ? r : min(col_base + n * 32 + r, p.ncols - 1));
+                const unsigned t = GATEUP ? (unsigned)((row >> 5) - nt) : 0u;      // the row may lie in the next row tile (fewer than 32 columns a wave)
+                if constexpr (MX) {
+                    boff[n][rt] = t * (unsigned)tile_bytes + (unsigned)(((l >> 5) * 32 + (row & 31)) * 16);
+                    soff[n] = t * (unsigned)(kblocks * 64) + (unsigned)((row & 31) * 2);
+                } else if constexpr (SWAP) {
+                    boff[n][rt] = t * (unsigned)tile_bytes + (unsigned)(rt * 1024 + ((l >> 5) * 32 + (row & 31)) * 16);
+                } else if constexpr (PACKED) {
+                    boff[n][rt] = t * (unsigned)tile_bytes + (unsigned)(lane_piece + (row & 31) * 16);
+                } else {
+                    boff[n][rt] = (unsigned)(row - first) * (unsigned)(p.K * 2) + (unsigned)lane_piece;
+                }
+            }
         }
     }
     // ---- token rows this thread stages into LDS (A operand): row tid/8 + 32*j, slot tid%8 ----
     const int srow = tid >> 3, sslot = tid & 7;
     // Addressed as a wave-uniform 64-bit base plus a 32-bit offset per row in units of 16 bytes (the
     // host checks that x and act stay below 64 GiB), which halves the registers the row table costs.
-    const char *abase = (const char *)p.a_src + ((long)kq * Kg + sslot * 8) * 2;
+    gchar abase = (gchar)p.a_src + ((long)kq * Kg + sslot * 8) * 2;
     unsigned aoff[T];
     static_for<T>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         const int r = min(srow + 32 * j, rows - 1);
         unsigned src_row;
-        if (GATEUP) src_row = (unsigned)(p.perm[un.row0 + r] / p.kdiv);
+        if (GATEUP) src_row = (unsigned)(gload<int>((gchar)p.perm + 4l * (un.row0 + r)) / p.kdiv);
         else src_row = (unsigned)(un.row0 + r);
         aoff[j] = src_row * ((unsigned)p.lda >> 3);        // in 16-byte units: lda is a multiple of 64 elements
     });
 
-    f32x16 acc[T][2];
-    static_for<T>([&](auto tc) {
-        constexpr int t = decltype(tc)::value;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { acc[t][0][r] = 0.f; acc[t][1][r] = 0.f; }
-    });
+    f32x4 acc[NF * 4];                      // [fragment][matrix][row half]: 4 consecutive weight rows 4*lg .. of token lr
+    static_for<NF * 4>([&](auto tc) { acc[decltype(tc)::value] = f32x4{0.f, 0.f, 0.f, 0.f}; });
 
     // Register rings: weight fragments of iterations it .. it+D (NB sets), token pieces of
     // it+1 .. it+D (NA sets).  Ring positions are compile-time constants: the loop is unrolled NA*NB.
-    constexpr int DA = P3 ? 1 : (T >= 5 && D > 2 ? 2 : D);   // token pieces: same distance, or less where registers are scarce
+    // The token pieces, from L2, need no more than 2, and a loop unrolled less: a small launch
+    // meets its code cold (unrolled 12 instead of 4 times, one or two fragments: +1 to 2 %).
+    constexpr int DA = P3 || D == 2 ? 1 : 2;
     constexpr int NB = D + 1, NA = DA, U = (NB % NA == 0) ? NB : NA * NB;
     u32x4 a_reg[NA * T];
-    bf16x8 b_reg[NB * 8];  // [set][k-step][n-tile]; MXFP4: set 0 only, the operands of the current iteration
-    u32x4 c_reg[NB * 2];   // MXFP4: codes [set][n-tile]
-    unsigned short s_reg[NB * 2];   // MXFP4: the two scale bytes [set][n-tile]
+    bf16x8 b_reg[(MX ? 1 : NB) * 8];    // [set][step j][matrix][row half]; MXFP4: the operands of the current iteration
+    u32x4 c_reg[NB * 2];                // MXFP4: codes [set][matrix]
+    unsigned short s_reg[NB * 2];       // MXFP4: the two scale bytes
 
-    auto load_a = [&](int it, auto setc) {
-        constexpr int S = decltype(setc)::value;
-        const int itc = min(it, iters - 1);
-        static_for<T>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            a_reg[S * T + j] = *reinterpret_cast<const u32x4 *>(abase + ((unsigned long)(aoff[j] + (unsigned)itc * 8u) << 4));
-        });
+    // One load (piece j of T, piece i of 8) of iteration `it`, one LDS write of a token piece.
+    auto load_a = [&](int it, auto setc, auto jc) {
+        constexpr int S = decltype(setc)::value, j = decltype(jc)::value;
+        a_reg[S * T + j] = gload<u32x4>(abase + ((unsigned long)(aoff[j] + (unsigned)min(it, iters - 1) * 8u) << 4));
     };
-    auto store_a = [&](int stage, auto setc) {
-        constexpr int S = decltype(setc)::value;
-        static_for<T>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            const int r = srow + 32 * j;
-            *reinterpret_cast<u32x4 *>(lds + stage * STAGE + (r * 8 + (sslot ^ swz(r))) * 16) = a_reg[S * T + j];
-        });
+    auto store_a = [&](int stage, auto setc, auto jc) {
+        constexpr int S = decltype(setc)::value, j = decltype(jc)::value;
+        const int r = srow + 32 * j;
+        *reinterpret_cast<u32x4 *>(lds + stage * STAGE + (r * 8 + (sslot ^ swz(r))) * 16) = a_reg[S * T + j];
     };
-    auto load_b = [&](int it, auto setc) {
-        constexpr int S = decltype(setc)::value;
-        const int itc = min(it, iters - 1);
-        if constexpr (MX) {
-            static_for<2>([&](auto nc) {
-                constexpr int n = decltype(nc)::value;
-                const u32x4 *qc = reinterpret_cast<const u32x4 *>(cptr[n] + (long)itc * 1024);
-                const unsigned short *qs = reinterpret_cast<const unsigned short *>(sptr[n] + (long)itc * 64);
-                if constexpr (STREAM) c_reg[S * 2 + n] = __builtin_nontemporal_load(qc);
-                else c_reg[S * 2 + n] = *qc;
-                s_reg[S * 2 + n] = *qs;
-            });
-            return;
+    auto load_b = [&](int it, auto setc, auto ic) {
+        constexpr int S = decltype(setc)::value, i = decltype(ic)::value, q = i & 3, n = q >> 1, rt = q & 1;
+        const long at = (long)min(it, iters - 1) * BIT;
+        if constexpr (MX && i >= 2) {
+            s_reg[S * 2 + (i & 1)] = gload<unsigned short>(sbase[i & 1] + (at >> 4) + soff[i & 1]);
+        } else if constexpr (MX) {
+            const gchar from = bbase[i] + at + boff[i][0];
+            c_reg[S * 2 + i] = STREAM ? gload_nt<u32x4>(from) : gload<u32x4>(from);
+        } else {
+            const gchar from = bbase[n] + at + boff[n][rt] + (i >> 2) * BJ;
+            b_reg[S * 8 + i] = STREAM ? gload_nt<bf16x8>(from) : gload<bf16x8>(from);
         }
-        static_for<4>([&](auto kc) {
-            constexpr int ks = decltype(kc)::value;
-            const bf16x8 *q0 = reinterpret_cast<const bf16x8 *>(bptr[0] + (long)itc * BIT + ks * BKS);
-            const bf16x8 *q1 = reinterpret_cast<const bf16x8 *>(bptr[1] + (long)itc * BIT + ks * BKS);
-            if constexpr (STREAM) {
-                b_reg[S * 8 + ks * 2 + 0] = __builtin_nontemporal_load(q0);
-                b_reg[S * 8 + ks * 2 + 1] = __builtin_nontemporal_load(q1);
-            } else {
-                b_reg[S * 8 + ks * 2 + 0] = *q0;
-                b_reg[S * 8 + ks * 2 + 1] = *q1;
-            }
+    };
+    auto load_a_all = [&](int it, auto setc) { static_for<T>([&](auto jc) { load_a(it, setc, jc); }); };
+    auto store_a_all = [&](int stage, auto setc) { static_for<T>([&](auto jc) { store_a(stage, setc, jc); }); };
+    constexpr int BL = MX ? 4 : 8;          // weight loads of an iteration
+    auto load_b_all = [&](int it, auto setc) { static_for<BL>([&](auto ic) { load_b(it, setc, ic); }); };
+    // MXFP4: codes and scales of ring set S -> the bf16 operands of (step j, matrix n), both row halves
+    // (v_cvt_scalef32_pk_bf16_fp4: two e2m1 nibbles of one byte times a float scale, exact for a power-of-two scale).
+    // Lane groups of 16 hold (rows 0-15, half 0), (16-31, 0), (0-15, 1), (16-31, 1) of the k-steps' words; swapping the odd
+    // groups of word 2j with the even ones of word 2j + 1 leaves rows 0-15 in the one and rows 16-31 in the other.
+    auto dequant = [&](auto setc, auto jc, auto nc) {
+        constexpr int S = decltype(setc)::value, j = decltype(jc)::value, n = decltype(nc)::value;
+        const u32x2 wv = __builtin_amdgcn_permlane16_swap(c_reg[S * 2 + n][2 * j], c_reg[S * 2 + n][2 * j + 1], false, false);
+        const unsigned sb = (unsigned)(s_reg[S * 2 + n] >> (8 * j)) << 23;     // (the other byte's bits land above or are masked)
+        const u32x2 sv = __builtin_amdgcn_permlane16_swap(sb, sb, false, false);
+        static_for<2>([&](auto rc) {
+            constexpr int rt = decltype(rc)::value;
+            const float f = __builtin_bit_cast(float, sv[rt] & 0x7f800000u);
+            const bf16x2 e0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv[rt], f, 0);
+            const bf16x2 e1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv[rt], f, 1);
+            const bf16x2 e2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv[rt], f, 2);
+            const bf16x2 e3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv[rt], f, 3);
+            bf16x8 v;
+            v[0] = e0[0]; v[1] = e0[1]; v[2] = e1[0]; v[3] = e1[1];
+            v[4] = e2[0]; v[5] = e2[1]; v[6] = e3[0]; v[7] = e3[1];
+            b_reg[j * 4 + n * 2 + rt] = v;
         });
     };
-    // MFMAs of one iteration.  Token fragments are read from LDS one half-step (HT tiles of one
-    // k-step) ahead of the MFMAs that use them.
-        constexpr int HT = T >= 8 ? 4 : (T == 6 ? 3 : T), NH = T / HT, STEPS = 4 * NH;
-    bf16x8 af[2 * HT];
-    auto read_af = [&](int stage, auto hsc) {
-        constexpr int hs = decltype(hsc)::value, ks = hs / NH, h = hs % NH;
-        static_for<HT>([&](auto tc) {
-            constexpr int t = h * HT + decltype(tc)::value;
-            const int r = t * 32 + lr;
-            const int slot = (ks * 2 + lh) ^ swz(r);
-            af[(hs & 1) * HT + decltype(tc)::value] = *reinterpret_cast<const bf16x8 *>(lds + stage * STAGE + (r * 8 + slot) * 16);
-        });
+
+    // One K-iteration is 4*T slots, written out in the order in which they shall issue (nothing moves across a slot's
+    // end): slot s has the 4 MFMAs of one token fragment (step j = s / NF, fragment s % NF), one LDS fragment read (RF - 1
+    // slots before its use), and its share of the T + 8 global loads (first half of the slots, so the texture path works
+    // under the MFMAs instead of in a burst) and of the T LDS writes of the next token tile (last slots).
+    constexpr int SL = 2 * NF, RF = P3 ? 6 : (SL < 4 ? SL : 4);
+    static_assert(!P3 || U * SL % RF == 0, "the ring of fragments goes on from iteration to iteration");
+    bf16x8 af[RF];
+    const char *a_at[2];                    // this lane's piece of step 0 and 1 in a token row
+#pragma unroll
+    for (int j = 0; j < 2; ++j) a_at[j] = lds + lr * 128 + ((j * 4 + (lg & 1) * 2 + (lg >> 1)) ^ swz(lr)) * 16;
+    auto read_af = [&](int stage, auto pc, auto rc) {         // fragment of slot p into place r of the ring
+        constexpr int p = decltype(pc)::value, j = p / NF, f = p % NF;
+        af[decltype(rc)::value] = *reinterpret_cast<const bf16x8 *>(a_at[j] + stage * STAGE + f * 2048);
     };
-    // MXFP4: codes and scales of ring set S -> bf16 operands (v_cvt_scalef32_pk_bf16_fp4: two e2m1
-    // nibbles of one byte times a float scale, exact for a power-of-two scale).
-    auto dequant_b = [&](auto setc) {
-        constexpr int S = decltype(setc)::value;
-        static_for<2>([&](auto nc) {
-            constexpr int n = decltype(nc)::value;
-            const unsigned sc = s_reg[S * 2 + n];
-            const float f0 = __builtin_bit_cast(float, (sc & 0xffu) << 23);
-            const float f1 = __builtin_bit_cast(float, (sc >> 8) << 23);
-            static_for<4>([&](auto kc) {
-                constexpr int ks = decltype(kc)::value;
-                const unsigned wv = c_reg[S * 2 + n][ks];
-                const float f = ks < 2 ? f0 : f1;
-                const bf16x2 e0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv, f, 0);
-                const bf16x2 e1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv, f, 1);
-                const bf16x2 e2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv, f, 2);
-                const bf16x2 e3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv, f, 3);
-                bf16x8 v;
-                v[0] = e0[0]; v[1] = e0[1]; v[2] = e1[0]; v[3] = e1[1];
-                v[4] = e2[0]; v[5] = e2[1]; v[6] = e3[0]; v[7] = e3[1];
-                b_reg[ks * 2 + n] = v;
-            });
-        });
-    };
-    auto mfma_tile = [&](int stage, int next_stage, auto setc) {
-        constexpr int S = MX ? 0 : decltype(setc)::value;
-        if constexpr (MX) dequant_b(setc);
-        if constexpr (!P3) read_af(stage, std::integral_constant<int, 0>{});
-        static_for<STEPS>([&](auto hsc) {
-            constexpr int hs = decltype(hsc)::value, ks = hs / NH, h = hs % NH;
-            if constexpr (hs + 1 < STEPS) read_af(stage, std::integral_constant<int, hs + 1>{});
-            else if constexpr (P3) read_af(next_stage, std::integral_constant<int, 0>{});
-            static_for<HT>([&](auto tc) {
-                constexpr int t = h * HT + decltype(tc)::value;
-                const bf16x8 a = af[(hs & 1) * HT + decltype(tc)::value];
-                acc[t][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b_reg[S * 8 + ks * 2 + 0], acc[t][0], 0, 0, 0);
-                acc[t][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b_reg[S * 8 + ks * 2 + 1], acc[t][1], 0, 0, 0);
-            });
-        });
-    };
-    // The instruction mix of one iteration, handed to the scheduler as one pipeline: the MFMAs are
-    // the backbone (2 per slot); each slot also takes one LDS fragment read; the T+8 global loads
-    // are spread over the first half of the slots (so the texture path works under the MFMAs
-    // instead of in a burst), the T LDS writes of the next token tile over the last slots.
-    auto pipeline = [&]() {
-        constexpr int NS = 4 * T, NV = T + 8, HALF = NS / 2;
-        if constexpr (!P3) __builtin_amdgcn_sched_group_barrier(0x100, HT, 0);
-        static_for<NS>([&](auto sc) {
-            constexpr int sl = decltype(sc)::value;
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-            if constexpr (P3 || sl < NS - HT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if constexpr (sl < HALF) {
-                constexpr int vm = NV / HALF + (sl < NV % HALF ? 1 : 0);
-                if constexpr (vm > 0) __builtin_amdgcn_sched_group_barrier(0x020, vm, 0);
-            }
-            if constexpr (sl >= NS - T) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-        });
-    };
+    auto read_first = [&](int stage) { static_for<RF - 1>([&](auto pc) { read_af(stage, pc, pc); }); };
     // Iteration `it`, position i = it mod U in the unrolled loop: request the operands of it+D (token
     // pieces first: the wait for them must not cover the weight loads), run the MFMAs of it, move the
     // token pieces of it+1 (requested earlier) into the other LDS stage.  Loads complete in issue
     // order, so neither wait disturbs the iterations of weight loads issued after the data waited for.
     auto body = [&](int it, auto ic) {
-        constexpr int i = decltype(ic)::value;
+        constexpr int i = decltype(ic)::value, S = MX ? 0 : i % NB;
+        static_assert(!P3 || (NA == 1 && U % 3 == 0), "three stages: one token register set, loop unrolled by a multiple of 3");
+        const int stage = P3 ? i % 3 : it & 1, next = P3 ? (i + 1) % 3 : (it + 1) & 1, put = P3 ? (i + 2) % 3 : next;
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (P3) {
-            static_assert(!P3 || (NA == 1 && U % 3 == 0), "three stages: one token register set, loop unrolled by a multiple of 3");
-            load_a(it + 2, std::integral_constant<int, 0>{});
-            load_b(it + D, std::integral_constant<int, (i + D) % NB>{});
-            mfma_tile(i % 3, (i + 1) % 3, std::integral_constant<int, i % NB>{});
-            store_a((i + 2) % 3, std::integral_constant<int, 0>{});
-        } else {
-            load_a(it + DA, std::integral_constant<int, (i + DA) % NA>{});
-            load_b(it + D, std::integral_constant<int, (i + D) % NB>{});
-            mfma_tile(it & 1, 0, std::integral_constant<int, i % NB>{});
-            store_a((it + 1) & 1, std::integral_constant<int, (i + 1) % NA>{});
+        if constexpr (!P3) read_first(stage);
+        if constexpr (SWAP) {
+            // blocks 2j and 2j + 1 of a matrix -> its row halves of step j, as in dequant
+            static_for<4>([&](auto pc) {
+                constexpr int at = S * 8 + decltype(pc)::value * 2;
+                u32x4 x = __builtin_bit_cast(u32x4, b_reg[at]), y = __builtin_bit_cast(u32x4, b_reg[at + 1]);
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const u32x2 v = __builtin_amdgcn_permlane16_swap(x[d], y[d], false, false);
+                    x[d] = v[0]; y[d] = v[1];
+                }
+                b_reg[at] = __builtin_bit_cast(bf16x8, x); b_reg[at + 1] = __builtin_bit_cast(bf16x8, y);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 1");               // see mma
         }
-        pipeline();
-        __builtin_amdgcn_sched_barrier(0);
+        static_for<4 * SL>([&](auto mc) {
+            constexpr int m = decltype(mc)::value, s = m / 4, q = m % 4, j = s / NF, f = s % NF, p = s + RF - 1;
+            constexpr int ring = P3 ? i * SL : 0;              // slots before this iteration
+            mma<m == 4 * SL - 1>(acc[f * 4 + q], b_reg[S * 8 + j * 4 + q], af[(ring + s) % RF]);
+            if constexpr (q == 0 && p < SL) read_af(stage, std::integral_constant<int, p>{}, std::integral_constant<int, (ring + p) % RF>{});
+            else if constexpr (q == 0 && P3) read_af(next, std::integral_constant<int, p - SL>{}, std::integral_constant<int, (ring + p) % RF>{});
+            constexpr int NV = T + BL, HALF = 2 * SL, V0 = m * NV / HALF, V1 = (m + 1) * NV / HALF;
+            if constexpr (m < HALF) {
+                static_for<V1 - V0>([&](auto vc) {
+                    constexpr int v = V0 + decltype(vc)::value;
+                    if constexpr (v < T) load_a(it + (P3 ? 2 : DA), std::integral_constant<int, P3 ? 0 : (i + DA) % NA>{}, std::integral_constant<int, v>{});
+                    else load_b(it + D, std::integral_constant<int, (i + D) % NB>{}, std::integral_constant<int, v - T>{});
+                });
+            }
+            if constexpr (MX && (NF == 1 ? q == 0 || q == 2 : q == 1 && f < 2)) {
+                // the operands of step 1, then those of the next iteration's step 0
+                constexpr int set = j == 0 ? i % NB : (i + 1) % NB;
+                if constexpr (j == 0 || NF > 1 || q == 2)
+                    dequant(std::integral_constant<int, set>{}, std::integral_constant<int, 1 - j>{}, std::integral_constant<int, NF == 1 ? q / 2 : f>{});
+                if constexpr (j == 1 && NF == 1 && q == 2)
+                    dequant(std::integral_constant<int, set>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+            }
+            if constexpr (q == 2 && s >= SL - T) store_a(put, std::integral_constant<int, P3 ? 0 : (i + 1) % NA>{}, std::integral_constant<int, s - (SL - T)>{});
+            __builtin_amdgcn_sched_barrier(0);
+        });
         __syncthreads();
     };
 
     // prologue: operands of iterations 0 .. D-1; tile 0 into LDS stage 0
-    load_a(0, std::integral_constant<int, 0>{});
-    load_b(0, std::integral_constant<int, 0>{});
-    store_a(0, std::integral_constant<int, 0>{});
+    load_a_all(0, std::integral_constant<int, 0>{});
+    load_b_all(0, std::integral_constant<int, 0>{});
+    store_a_all(0, std::integral_constant<int, 0>{});
     if constexpr (P3) {                      // three stages: tile 1 goes into stage 1 as well
-        load_a(1, std::integral_constant<int, 0>{});
-        store_a(1, std::integral_constant<int, 0>{});
+        load_a_all(1, std::integral_constant<int, 0>{});
+        store_a_all(1, std::integral_constant<int, 0>{});
     }
     static_for<D - 1>([&](auto ic) {
         constexpr int j = decltype(ic)::value + 1;
-        if constexpr (!P3 && j < DA) load_a(j, std::integral_constant<int, j % NA>{});
-        load_b(j, std::integral_constant<int, j % NB>{});
+        if constexpr (!P3 && j < DA) load_a_all(j, std::integral_constant<int, j % NA>{});
+        load_b_all(j, std::integral_constant<int, j % NB>{});
     });
+    if constexpr (MX) static_for<2>([&](auto nc) { dequant(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, nc); });
     wg_decide(p, un.row0, 1, probe, &s_run);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     if (p.go != nullptr && s_run == 0) return;
-    if constexpr (P3) read_af(0, std::integral_constant<int, 0>{});
+    if constexpr (P3) read_first(0);
     int it = 0;
     for (; it + U <= iters; it += U) {
         static_for<U>([&](auto ic) { body(it + decltype(ic)::value, ic); });
@@ -371,19 +383,21 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
         if (it + decltype(ic)::value < iters) body(it + decltype(ic)::value, ic);
     });
 
-    // ---- epilogue.  D register r of lane l: token 8*(r/4) + 4*(l/32) + r%4, weight row l%32 ----
+    // ---- epilogue.  acc[fragment][matrix][row half]: lane (lg, lr) holds weight rows 4*lg .. 4*lg + 3 of token lr ----
     if (GATEUP) {
         // SwiGLU in fp32, one rounding to bf16; the wave's [T*32 tokens][32 f] tile goes through LDS
         // (free after the last barrier of the main loop) so that it leaves as 16-byte stores, with the
         // non-temporal hint: the next kernel reads it, nothing in this one does.
         __bf16 *st = reinterpret_cast<__bf16 *>(lds) + w * (ROWS * 32);
-        static_for<T>([&](auto tc) {
-            constexpr int t = decltype(tc)::value;
+        static_for<NF>([&](auto fc) {
+            constexpr int f = decltype(fc)::value;
+            static_for<2>([&](auto rc) {
+                constexpr int rt = decltype(rc)::value;
+                bf16x4 v;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = t * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-                st[i * 32 + lr] = (__bf16)(silu_f(acc[t][0][r]) * acc[t][1][r]);
-            }
+                for (int r = 0; r < 4; ++r) v[r] = (__bf16)(silu_f(acc[f * 4 + rt][r]) * acc[f * 4 + 2 + rt][r]);
+                *reinterpret_cast<bf16x4 *>(st + (f * 16 + lr) * 32 + rt * 16 + lg * 4) = v;
+            });
         });
         __builtin_amdgcn_s_waitcnt(0xc07f);   // this wave's LDS writes have landed (lgkmcnt 0)
         __builtin_amdgcn_wave_barrier();
@@ -394,7 +408,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
                 const int i = (l >> 2) + 16 * j;
                 if (i < rows && f0 < p.ncols) {
                     const u32x4 v = *reinterpret_cast<const u32x4 *>(st + i * 32 + (l & 3) * 8);
-                    __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>((__bf16 *)p.dst + (long)(un.row0 + i) * p.ldd + f0));
+                    gstore_nt(v, ((__bf16 *)p.dst + (long)(un.row0 + i) * p.ldd + f0));
                 }
             }
         } else {
@@ -405,33 +419,31 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
                 const int i = (l >> 3) + 8 * j;
                 if (i < rows && fo < cpw && col_base + fo < p.ncols) {
                     const u32x2 v = *reinterpret_cast<const u32x2 *>(st + i * 32 + fo);
-                    __builtin_nontemporal_store(v, reinterpret_cast<u32x2 *>((__bf16 *)p.dst + (long)(un.row0 + i) * p.ldd + col_base + fo));
+                    gstore_nt(v, ((__bf16 *)p.dst + (long)(un.row0 + i) * p.ldd + col_base + fo));
                 }
             }
         }
     } else {
-        // fp32 tile of 32 tokens x 64 columns at a time through this wave's 8 KiB of LDS, so that it
-        // leaves as 16-byte stores (256 contiguous bytes per token row).
-        float *st = reinterpret_cast<float *>(lds) + w * (32 * 64);
+        // fp32 tile of 32 tokens x 64 columns at a time through this wave's 8 KiB of LDS (16 slots of 16 bytes per token,
+        // XORed by token), so that it leaves as 16-byte stores of 256 contiguous bytes per token row.
+        char *st = lds + w * (32 * 256);
         float *obase = (float *)p.dst + kq * plane + (long)un.row0 * p.ldd + col_base + (l & 15) * 4;
         const bool col_ok = col_base + (l & 15) * 4 < p.ncols;
         static_for<T>([&](auto tc) {
             constexpr int t = decltype(tc)::value;
             if (t * 32 < rows) {
                 __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int i = 8 * (r >> 2) + 4 * lh + (r & 3);
-                    st[i * 64 + lr] = acc[t][0][r];
-                    st[i * 64 + 32 + lr] = acc[t][1][r];
-                }
+                static_for<8>([&](auto qc) {
+                    constexpr int q = decltype(qc)::value & 3, h = decltype(qc)::value >> 2;
+                    if constexpr (2 * t + h < NF) *reinterpret_cast<f32x4 *>(st + (h * 16 + lr) * 256 + ((q * 4 + lg) ^ lr) * 16) = acc[(2 * t + h) * 4 + q];
+                });
                 __builtin_amdgcn_s_waitcnt(0xc07f);
                 __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int i = (l >> 4) + 4 * j;
-                    const f32x4 v = *reinterpret_cast<const f32x4 *>(st + i * 64 + (l & 15) * 4);
-                    if (t * 32 + i < rows && col_ok) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(obase + (long)(t * 32 + i) * p.ldd));
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(st + i * 256 + ((l & 15) ^ (i & 15)) * 16);
+                    if (t * 32 + i < rows && col_ok) gstore_nt(v, (obase + (long)(t * 32 + i) * p.ldd));
                 }
                 __builtin_amdgcn_s_waitcnt(0xc07f);
             }
@@ -473,8 +485,8 @@ __device__ __forceinline__ bool map_block(const BArgs &b, moe_unit &un, int &ct,
     return true;
 }
 
-// TCAP: largest number of 32-token tiles a segment of this launch may have (1, 2, 4, 6 or 8).  A
-// workgroup takes the smallest fully unrolled variant (1, 2, 4, 5, 6, 7 or 8 tiles) that covers its unit.
+// TCAP: largest number of 32-row pieces a segment of this launch may have (1, 2, 4, 6 or 8).  A
+// workgroup takes the fully unrolled variant for as many 16-token fragments as its unit has (1 to 16).
 // STREAM: no two segments of the launch belong to one expert, so every weight element is read by
 // exactly one workgroup: the loads carry the non-temporal hint and do not displace the token tiles
 // in L2.  Where segments share an expert's weights the hint is left off so that L2 serves the re-reads.
@@ -494,16 +506,21 @@ __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
     int ct, kq;
     moe_unit un;
     if (!map_block<STREAM>(b, un, ct, kq)) return;
-    const int t_cnt = (un.rows + 31) >> 5;
+    const int nf = (un.rows + 15) >> 4;
+    // One copy for all variants: the compiler reads the arguments in place only where it finds few enough uses of them,
+    // and keeps them in scratch memory otherwise.
+    const KArgs k = b.k;
+    const int ksplit = b.ksplit;
+    const long plane = b.plane;
     // Prefetch distance of the weights: 2 iterations for the three-stage variants (their loop is unrolled by
-    // a multiple of 3) and the 2-tile variant, 3 for the 1-tile variant.
-    if (TCAP >= 8 && t_cnt > 7) expert_tile<(TCAP >= 8 ? 8 : 1), GATEUP, WF, STREAM, 2>(b.k, un, ct, kq, b.ksplit, b.plane, lds);
-    else if (TCAP >= 8 && t_cnt > 6) expert_tile<(TCAP >= 8 ? 7 : 1), GATEUP, WF, STREAM, 2>(b.k, un, ct, kq, b.ksplit, b.plane, lds);
-    else if (TCAP >= 6 && t_cnt > 5) expert_tile<(TCAP >= 6 ? 6 : 1), GATEUP, WF, STREAM, (kP3MinT <= 6 ? 2 : 3)>(b.k, un, ct, kq, b.ksplit, b.plane, lds);
-    else if (TCAP >= 6 && t_cnt > 4) expert_tile<(TCAP >= 6 ? 5 : 1), GATEUP, WF, STREAM, (kP3MinT <= 5 ? 2 : 3)>(b.k, un, ct, kq, b.ksplit, b.plane, lds);
-    else if (TCAP >= 4 && t_cnt > 2) expert_tile<(TCAP >= 4 ? 4 : 1), GATEUP, WF, STREAM, (kP3MinT <= 4 ? 2 : 3)>(b.k, un, ct, kq, b.ksplit, b.plane, lds);
-    else if (TCAP >= 2 && t_cnt > 1) expert_tile<(TCAP >= 2 ? 2 : 1), GATEUP, WF, STREAM, 2>(b.k, un, ct, kq, b.ksplit, b.plane, lds);
-    else expert_tile<1, GATEUP, WF, STREAM, 3>(b.k, un, ct, kq, b.ksplit, b.plane, lds);
+    // a multiple of 3) and up to 64 rows, 3 up to 32 rows; 4-bit iterations are short and their codes take few registers:
+    // 5 (64 tokens on 8 experts, 2 K ranges, down projection 71 -> 55 us against 2).
+#define QMOE_TILE(n, d) else if (2 * TCAP >= n && nf >= n) expert_tile<(2 * TCAP >= n ? n : 1), GATEUP, WF, STREAM, d>(k, un, ct, kq, ksplit, plane, lds)
+    constexpr int D1 = WF == WF_MXFP4 ? 5 : 3, D2 = WF == WF_MXFP4 ? 5 : 2;
+    if (false) {}
+    QMOE_TILE(16, 2); QMOE_TILE(15, 2); QMOE_TILE(14, 2); QMOE_TILE(13, 2); QMOE_TILE(12, 2); QMOE_TILE(11, 2); QMOE_TILE(10, 2); QMOE_TILE(9, 2);
+    QMOE_TILE(8, 2); QMOE_TILE(7, 2); QMOE_TILE(6, 2); QMOE_TILE(5, 2); QMOE_TILE(4, D2); QMOE_TILE(3, D2); QMOE_TILE(2, D1); QMOE_TILE(1, D1);
+#undef QMOE_TILE
 }
 
 template <int TCAP, bool GATEUP, int WF, bool STREAM>
@@ -521,23 +538,20 @@ void launch_ts(int tiles, const BArgs &b, hipStream_t s) {
     else launch1<8, GATEUP, WF, STREAM>(b, s);
 }
 
-// The expert kernels of one weight format: gate-up or down, for segments of at most `tiles` token
-// tiles.  Each format is instantiated in its own translation unit (experts_bf16_w<WF>.hip).
-template <int WF>
-void launch_expert_kernels(bool gateup, int tiles, bool stream, const BArgs &b, hipStream_t s) {
-    if (gateup) {
-        if (stream) launch_ts<true, WF, true>(tiles, b, s);
-        else launch_ts<true, WF, false>(tiles, b, s);
-    } else {
-        if (stream) launch_ts<false, WF, true>(tiles, b, s);
-        else launch_ts<false, WF, false>(tiles, b, s);
-    }
+// One expert kernel of one weight format, for segments of at most `tiles` 32-row pieces.  Each is instantiated in a
+// translation unit of its own (experts_bf16_w<WF>_<kernel>.hip).
+template <int WF, bool GATEUP>
+void launch_expert_kernel(int tiles, bool stream, const BArgs &b, hipStream_t s) {
+    if (stream) launch_ts<GATEUP, WF, true>(tiles, b, s);
+    else launch_ts<GATEUP, WF, false>(tiles, b, s);
 }
 
-
-extern template void launch_expert_kernels<WF_ROWMAJOR>(bool, int, bool, const BArgs &, hipStream_t);
-extern template void launch_expert_kernels<WF_PACKED>(bool, int, bool, const BArgs &, hipStream_t);
-extern template void launch_expert_kernels<WF_MXFP4>(bool, int, bool, const BArgs &, hipStream_t);
+extern template void launch_expert_kernel<WF_ROWMAJOR, true>(int, bool, const BArgs &, hipStream_t);
+extern template void launch_expert_kernel<WF_ROWMAJOR, false>(int, bool, const BArgs &, hipStream_t);
+extern template void launch_expert_kernel<WF_PACKED, true>(int, bool, const BArgs &, hipStream_t);
+extern template void launch_expert_kernel<WF_PACKED, false>(int, bool, const BArgs &, hipStream_t);
+extern template void launch_expert_kernel<WF_MXFP4, true>(int, bool, const BArgs &, hipStream_t);
+extern template void launch_expert_kernel<WF_MXFP4, false>(int, bool, const BArgs &, hipStream_t);
 
 }  // namespace bf16k
 }  // namespace qmoe
