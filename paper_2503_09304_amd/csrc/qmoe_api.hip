@@ -60,7 +60,7 @@ bool config_ok(const moe_config *c, const char **why) {
 
 // Offsets of the workspace regions, computed the same way for sizing and for carving.
 struct Layout {
-    size_t logits, topk_idx, topk_w, cnt, off, n_units, perm, inv, rank, blockoff, cls, done, go, prog, units, wgt, act, out, partial, total;
+    size_t logits, topk_idx, topk_w, cnt, off, n_units, perm, inv, rank, blockoff, cls, done, go, prog, units, wgt, parts, act, out, partial, total;
     bool has_partial;
     int ksplit;            // 1, 2 or 4: K ranges of the down projection, one partial plane each
     uint32_t max_units;
@@ -106,6 +106,7 @@ Layout make_layout(const moe_config &c) {
     L.prog = take((A ? 2 * A : 1) * 4);           // its progress: workgroups that ran per row range, gate-up [A] then down [A]
     L.units = take((size_t)L.max_units * sizeof(moe_unit));
     L.wgt = take(((E + 15) / 16 * 16) * (size_t)c.H * 2);
+    L.parts = take(c.dtype == MOE_BF16 ? qmoe::gate_parts_floats(c.max_tokens, c.E) * 4 : 0);
     L.act = take(A * (size_t)c.F * es);
     L.out = take(A * (size_t)c.H * 4);
     // K-split down projection: one partial plane shaped like `out` per K range
@@ -318,6 +319,7 @@ int32_t moe_route(moe_ctx *ctx, const void *x, int32_t n_tokens, const moe_weigh
         qmoe::RouteArgs a{};
         a.x = x; a.Wg = w->Wg; a.bias = logit_bias;
         a.WgT = at<void>(ctx, ctx->lay.wgt);
+        a.parts = at<float>(ctx, ctx->lay.parts);
         a.logits = at<float>(ctx, ctx->lay.logits);
         a.topk_idx = at<int32_t>(ctx, ctx->lay.topk_idx);
         a.topk_w = at<float>(ctx, ctx->lay.topk_w);

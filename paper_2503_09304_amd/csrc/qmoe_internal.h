@@ -31,6 +31,7 @@ struct RouteArgs {
     const void *x;
     const void *Wg;
     const float *bias;
+    float *parts;   // scratch of the router in two launches (gate_parts_floats), or nullptr: always one launch
     void *WgT;  // scratch: bf16 [E16][H], Wg transposed and padded to a multiple of 16 experts
     float *logits;
     int32_t *topk_idx;
@@ -38,6 +39,18 @@ struct RouteArgs {
     int N, H, E, k, dtype;
     bool packed;  // Wg already transposed and padded ([E16][H])
 };
+// The bf16 router in two launches, its GEMM dealt out in 8 K ranges to workgroups of their own: where one workgroup per
+// 16 tokens leaves CUs idle while each takes in all the weights.  Us as one launch / as two, 1, 32, 1024, 2048 tokens: top-8 of
+// 64, H 2048 11.4 / 8.5, 14.0 / 10.0, 14.5 / 12.0, 14.7 / 15.9; of 256 35.7 / 19.2, 39.4 / 24.4, 39.9 / 32.3, 40.2 / 47.0;
+// top-2 of 8, H 4096 5.8 / 6.2, 8.8 / 6.9, 9.2 / 7.1, 9.6 / 9.5; 8 tokens 7.4 / 6.6; H 1024 4.2 / 4.9, 6.0 / 5.5, 6.3 / 5.6,
+// 6.3 / 6.2; top-2 of 16, H 4096, one token 7.0 / 6.4; top-4 of 16, H 2048, one token 5.2 / 5.9.
+constexpr int kGatePartsMaxTokens = 1024;
+inline bool gate_in_parts(int N, int E, int H) { return N <= kGatePartsMaxTokens && (N > 8 || (long)E * H >= 65536); }
+// Floats of scratch for that: per 16 tokens and 16 experts, 8 partial tiles of 256.
+inline size_t gate_parts_floats(int max_tokens, int E) {
+    const size_t n = (size_t)(max_tokens < kGatePartsMaxTokens ? max_tokens : kGatePartsMaxTokens);
+    return (n + 15) / 16 * 8 * (size_t)((E + 15) / 16) * 256;
+}
 hipError_t launch_route(const RouteArgs &a, hipStream_t s);
 
 // Records the text moe_last_error() returns on this thread and hands `code` back (printf-style).

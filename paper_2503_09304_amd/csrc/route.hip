@@ -12,7 +12,8 @@
 // top-k: k rounds of a wave-wide maximum in the order (logit desc, index asc), or, where the bf16 router chooses
 // many of at most 64 experts, the rank of every expert in that order.
 //
-// These kernels are chains of latencies, 7 to 15 us of a layer of 40 to 500: what counts is their length.
+// These kernels are chains of latencies, 6 to 12 us of a layer of 40 to 500: what counts is their length, and in how many CUs
+// the weights are taken in (gate_in_parts).
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -179,56 +180,58 @@ __device__ __forceinline__ void wave_topk_rank(const float (&v)[NT][1], int l, i
 // the time on 8192 tokens x 64 experts.  NB = 8 has to be told: by itself it takes 132 registers, one workgroup
 // per CU, 44.6 us for 8192 tokens x 128 experts, top-8, H 2048; 40.1 us with 128 registers, and small batches
 // the same.  NB = 16 fills the LDS of a CU alone.
-template <int NB>
-__global__ __launch_bounds__(512, NB == 8 ? 4 : 2) void gate_topk_bf16(const uint16_t *__restrict__ x, const uint16_t *__restrict__ WgT,
-                                                      const float *__restrict__ bias, float *__restrict__ logits,
-                                                      int32_t *__restrict__ topk_idx, float *__restrict__ topk_w, int N, int H,
-                                                      int E, int nb, int k) {
-    __shared__ float red[8][NB][4][64];
+// PARTS: the partial tiles come from gate_parts_bf16 (same ranges, same chains, so the same logits) instead.
+template <int NB, bool PARTS>
+__device__ __forceinline__ void gate_topk_tile(const uint16_t *__restrict__ x, const uint16_t *__restrict__ WgT, const float *__restrict__ parts,
+                                               const float *__restrict__ bias, float *__restrict__ logits, int32_t *__restrict__ topk_idx,
+                                               float *__restrict__ topk_w, int N, int H, int E, int nb, int k) {
+    __shared__ float red[PARTS ? 1 : 8][NB][4][64];
     __shared__ float lt[16][NB * 16 + 1];
     __shared__ float sbias[NB * 16];
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int t16 = l & 15, q = l >> 4;
-    int tok = blockIdx.x * 16 + t16;
-    if (tok > N - 1) tok = N - 1;
     if (tid < NB * 16) sbias[tid] = (bias && tid < E) ? bias[tid] : 0.f;   // read after the first barrier
-    const int steps = H / 32;
-    const int per = (steps + 7) / 8;
-    const int s0 = w * per, s1 = min(steps, s0 + per);
-    f32x4 acc[NB];
+    if constexpr (!PARTS) {
+        int tok = blockIdx.x * 16 + t16;
+        if (tok > N - 1) tok = N - 1;
+        const int steps = H / 32;
+        const int per = (steps + 7) / 8;
+        const int s0 = w * per, s1 = min(steps, s0 + per);
+        f32x4 acc[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint16_t *xa = x + (long)tok * H + q * 8;
-    // Expert rows from E on are padding: their lanes read the last expert again (no bytes of their own), and
-    // nothing uses what they compute.  A CU takes 11 to 20 bytes a clock here: with 8 experts that is half
-    // of the weights' time (one token, H 4096: 7.7 -> 5.7 us; all k-steps requested at once gave nothing).
-    const uint16_t *wb[NB];
+        for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const uint16_t *xa = x + (long)tok * H + q * 8;
+        // Expert rows from E on are padding: their lanes read the last expert again (no bytes of their own), and
+        // nothing uses what they compute.  A CU takes 11 to 20 bytes a clock here: with 8 experts that is half
+        // of the weights' time (one token, H 4096: 7.7 -> 5.7 us; all k-steps requested at once gave nothing).
+        const uint16_t *wb[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) wb[b] = WgT + (long)min(b * 16 + t16, E - 1) * H + q * 8;
-    constexpr int CH = NB == 1 ? 8 : (NB == 2 ? 4 : 2);   // k-steps whose loads are issued together
-    for (int s = s0; s < s1; s += CH) {
-        bf16x8 a[CH], bv[CH][NB];
+        for (int b = 0; b < NB; ++b) wb[b] = WgT + (long)min(b * 16 + t16, E - 1) * H + q * 8;
+        constexpr int CH = NB == 1 ? 8 : (NB == 2 ? 4 : 2);   // k-steps whose loads are issued together
+        for (int s = s0; s < s1; s += CH) {
+            bf16x8 a[CH], bv[CH][NB];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int sc = min(s + c, s1 - 1);
-            a[c] = *reinterpret_cast<const bf16x8 *>(xa + sc * 32);
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-                bv[c][b] = *reinterpret_cast<const bf16x8 *>(wb[b] + sc * 32);
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            if (s + c < s1) {
+            for (int c = 0; c < CH; ++c) {
+                const int sc = min(s + c, s1 - 1);
+                a[c] = *reinterpret_cast<const bf16x8 *>(xa + sc * 32);
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
-                    if (b < nb) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], bv[c][b], acc[b], 0, 0, 0);
+                    bv[c][b] = *reinterpret_cast<const bf16x8 *>(wb[b] + sc * 32);
+            }
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                if (s + c < s1) {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        if (b < nb) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], bv[c][b], acc[b], 0, 0, 0);
+                }
             }
         }
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[w][b][r][l] = acc[b][r];
     }
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[w][b][r][l] = acc[b][r];
     __syncthreads();
     // The NB*4 (expert block, D register) pairs are dealt to the 8 waves; each sum runs over the waves'
     // partial tiles in wave order.
@@ -237,9 +240,15 @@ __global__ __launch_bounds__(512, NB == 8 ? 4 : 2) void gate_topk_bf16(const uin
         const int pr = w + 8 * j;
         const int b = pr >> 2, r = pr & 3;
         if (pr < NB * 4 && b < nb) {
-            float v = red[0][b][r][l];
+            float p[8];
 #pragma unroll
-            for (int ww = 1; ww < 8; ++ww) v += red[ww][b][r][l];
+            for (int ww = 0; ww < 8; ++ww) {
+                if constexpr (PARTS) p[ww] = parts[(((long)blockIdx.x * 8 + ww) * nb + b) * 256 + l * 4 + r];
+                else p[ww] = red[ww][b][r][l];
+            }
+            float v = p[0];
+#pragma unroll
+            for (int ww = 1; ww < 8; ++ww) v += p[ww];
             const int e = b * 16 + t16;                 // D: column = expert
             const int tl = q * 4 + r;                   // D: row = token (within the 16)
             const int t = blockIdx.x * 16 + tl;
@@ -271,6 +280,48 @@ __global__ __launch_bounds__(512, NB == 8 ? 4 : 2) void gate_topk_bf16(const uin
         }
         wave_topk<2, NS>(v, l, E, k, io, wo);
     }
+}
+
+template <int NB>
+__global__ __launch_bounds__(512, NB == 8 ? 4 : 2) void gate_topk_bf16(const uint16_t *__restrict__ x, const uint16_t *__restrict__ WgT,
+                                                      const float *__restrict__ bias, float *__restrict__ logits,
+                                                      int32_t *__restrict__ topk_idx, float *__restrict__ topk_w, int N, int H,
+                                                      int E, int nb, int k) {
+    gate_topk_tile<NB, false>(x, WgT, nullptr, bias, logits, topk_idx, topk_w, N, H, E, nb, k);
+}
+
+template <int NB>
+__global__ __launch_bounds__(512) void add_topk_bf16(const float *__restrict__ parts, const float *__restrict__ bias, float *__restrict__ logits,
+                                                     int32_t *__restrict__ topk_idx, float *__restrict__ topk_w, int N, int E, int nb, int k) {
+    gate_topk_tile<NB, true>(nullptr, nullptr, parts, bias, logits, topk_idx, topk_w, N, 0, E, nb, k);
+}
+
+// The gate GEMM alone, for batches whose token tiles are too few to fill the chip: workgroup (token tile, K range), one wave
+// per 16-expert block, its partial tile to memory where add_topk_bf16 adds them.  Each CU then
+// reads an eighth of the weights.
+__global__ __launch_bounds__(1024) void gate_parts_bf16(const uint16_t *__restrict__ x, const uint16_t *__restrict__ WgT, float *__restrict__ parts,
+                                                        int N, int H, int E) {
+    const int b = threadIdx.x >> 6, l = threadIdx.x & 63, nb = blockDim.x >> 6;
+    const int t16 = l & 15, q = l >> 4;
+    const uint16_t *xa = x + (long)min((int)blockIdx.x * 16 + t16, N - 1) * H + q * 8;
+    const uint16_t *wb = WgT + (long)min(b * 16 + t16, E - 1) * H + q * 8;
+    const int steps = H / 32, per = (steps + 7) / 8;
+    const int s0 = blockIdx.y * per, s1 = min(steps, s0 + per);
+    f32x4 acc{0.f, 0.f, 0.f, 0.f};
+    constexpr int CH = 8;
+    for (int s = s0; s < s1; s += CH) {
+        bf16x8 a[CH], w[CH];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int sc = min(s + c, s1 - 1);
+            a[c] = *reinterpret_cast<const bf16x8 *>(xa + sc * 32);
+            w[c] = *reinterpret_cast<const bf16x8 *>(wb + sc * 32);
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            if (s + c < s1) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], w[c], acc, 0, 0, 0);
+    }
+    *reinterpret_cast<f32x4 *>(parts + (((long)blockIdx.x * 8 + blockIdx.y) * nb + b) * 256 + l * 4) = acc;
 }
 
 // One wave per token: lane l sums the elements h = l, l + 64, ... of EB logits at a time (U of them
@@ -362,12 +413,16 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t s) {
                                (const uint16_t *)a.Wg, (uint16_t *)a.WgT, a.H, a.E, E16);
         const dim3 g((a.N + 15) / 16), b(512);
         const uint16_t *x = (const uint16_t *)a.x, *wt = (const uint16_t *)(a.packed ? a.Wg : a.WgT);
-#define QMOE_GATE(NBV) hipLaunchKernelGGL(gate_topk_bf16<NBV>, g, b, 0, s, x, wt, a.bias, a.logits, a.topk_idx, a.topk_w, a.N, a.H, a.E, nb, a.k)
-        if (nb <= 1) QMOE_GATE(1);
-        else if (nb <= 2) QMOE_GATE(2);
-        else if (nb <= 4) QMOE_GATE(4);
-        else if (nb <= 8) QMOE_GATE(8);
-        else QMOE_GATE(16);
+        const bool parts = a.parts != nullptr && gate_in_parts(a.N, a.E, a.H);
+        if (parts) hipLaunchKernelGGL(gate_parts_bf16, dim3(g.x, 8), dim3(64 * nb), 0, s, x, wt, a.parts, a.N, a.H, a.E);
+#define QMOE_GATE(NBV)                                                                                                                       \
+    if (parts) hipLaunchKernelGGL(add_topk_bf16<NBV>, g, b, 0, s, a.parts, a.bias, a.logits, a.topk_idx, a.topk_w, a.N, a.E, nb, a.k);      \
+    else hipLaunchKernelGGL(gate_topk_bf16<NBV>, g, b, 0, s, x, wt, a.bias, a.logits, a.topk_idx, a.topk_w, a.N, a.H, a.E, nb, a.k)
+        if (nb <= 1) { QMOE_GATE(1); }
+        else if (nb <= 2) { QMOE_GATE(2); }
+        else if (nb <= 4) { QMOE_GATE(4); }
+        else if (nb <= 8) { QMOE_GATE(8); }
+        else { QMOE_GATE(16); }
 #undef QMOE_GATE
     } else {
         const dim3 g((a.N + 3) / 4), b(256);

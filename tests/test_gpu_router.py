@@ -76,3 +76,21 @@ def test_rounds_and_ranks_choose_alike(E):
             assert np.array_equal(idx, np.broadcast_to(order[:k], (N, k))), (k, bias)
             if not np.isnan(values).any():
                 _check(logits, idx, w, k)
+
+
+@pytest.mark.parametrize("E,k,H", [(8, 2, 64), (8, 2, 8192), (16, 4, 4096), (17, 3, 320), (64, 8, 1088), (100, 5, 704), (256, 6, 512)])
+def test_two_launches_give_the_bits_of_one(E, k, H):
+    """moe_route deals the gate GEMM of up to 1024 tokens to workgroups per K range; moe_route_noalloc never does."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(E + H)
+    Wg = (torch.randn((H, E), generator=g, device=DEV) * H ** -0.5).bfloat16()
+    bias = torch.randn(E, generator=g, device=DEV)
+    dummy = torch.empty(64, dtype=torch.bfloat16, device=DEV)
+    w = q.Context.weights(Wg, dummy, dummy, dummy)
+    for N in (1, 8, 9, 16, 17, 1023, 1024, 1025):
+        x = torch.randn((N, H), generator=g, device=DEV).bfloat16()
+        ctx = q.Context(E, k, H, 64, q.MOE_BF16, 16, N, device=DEV)
+        ctx.route(x, w, bias)
+        logits, idx, wt = _route(torch.bfloat16, E, k, H, x, Wg, bias)
+        assert np.array_equal(ctx.get("logits").cpu().numpy(), logits), N
+        assert np.array_equal(ctx.get("topk_idx").cpu().numpy(), idx) and np.array_equal(ctx.get("topk_w").cpu().numpy(), wt), N
