@@ -486,7 +486,7 @@ __device__ __forceinline__ bool map_block(const BArgs &b, moe_unit &un, int &ct,
 }
 
 // TCAP: largest number of 32-row pieces a segment of this launch may have (1, 2, 4, 6 or 8).  A
-// workgroup takes the fully unrolled variant for as many 16-token fragments as its unit has (1 to 16).
+// workgroup takes the fully unrolled variant for as many 16-token fragments as its unit has (1, 2, 4 to 16).
 // STREAM: no two segments of the launch belong to one expert, so every weight element is read by
 // exactly one workgroup: the loads carry the non-temporal hint and do not displace the token tiles
 // in L2.  Where segments share an expert's weights the hint is left off so that L2 serves the re-reads.
@@ -519,7 +519,8 @@ __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
     constexpr int D1 = WF == WF_MXFP4 ? 5 : 3, D2 = WF == WF_MXFP4 ? 5 : 2;
     if (false) {}
     QMOE_TILE(16, 2); QMOE_TILE(15, 2); QMOE_TILE(14, 2); QMOE_TILE(13, 2); QMOE_TILE(12, 2); QMOE_TILE(11, 2); QMOE_TILE(10, 2); QMOE_TILE(9, 2);
-    QMOE_TILE(8, 2); QMOE_TILE(7, 2); QMOE_TILE(6, 2); QMOE_TILE(5, 2); QMOE_TILE(4, D2); QMOE_TILE(3, D2); QMOE_TILE(2, D1); QMOE_TILE(1, D1);
+    QMOE_TILE(8, 2); QMOE_TILE(7, 2); QMOE_TILE(6, 2); QMOE_TILE(5, 2); else if (TCAP >= 2 && nf >= 3) expert_tile<(TCAP >= 2 ? 4 : 1), GATEUP, WF, STREAM, D2>(k, un, ct, kq, ksplit, plane, lds);
+    QMOE_TILE(2, D1); QMOE_TILE(1, D1);
 #undef QMOE_TILE
 }
 
@@ -531,8 +532,10 @@ void launch1(const BArgs &b, hipStream_t s) {
 
 template <bool GATEUP, int WF, bool STREAM>
 void launch_ts(int tiles, const BArgs &b, hipStream_t s) {
+    // The kernel for up to 64 rows is of use to 4-bit weights alone (two workgroups of it share a CU); 160 tokens on 8 experts
+    // with bf16 weights: gate-up 306 us in one of their own, 296 in the kernel for up to 128 rows.
     if (tiles <= 1) launch1<1, GATEUP, WF, STREAM>(b, s);
-    else if (tiles <= 2) launch1<2, GATEUP, WF, STREAM>(b, s);
+    else if (WF == WF_MXFP4 && tiles <= 2) launch1<(WF == WF_MXFP4 ? 2 : 4), GATEUP, WF, STREAM>(b, s);
     else if (tiles <= 4) launch1<4, GATEUP, WF, STREAM>(b, s);
     else if (tiles <= 6) launch1<6, GATEUP, WF, STREAM>(b, s);
     else launch1<8, GATEUP, WF, STREAM>(b, s);
