@@ -112,6 +112,16 @@ hipError_t launch_pack(const void *src, void *dst, int E, int R, int K, hipStrea
     return hipGetLastError();
 }
 
+static long cu_count() {
+    static int cus = 0;
+    if (cus == 0) {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
+        cus = v;
+    }
+    return cus;
+}
+
 // Columns per wave of a gate-up launch.  A workgroup stays on its CU for the whole of K, so a launch
 // costs whole rounds of the chip's CUs, and a weight-streaming launch moves bytes in proportion to
 // rounds x columns per workgroup.  Narrower waves (28 .. 16 columns on the 32-wide MFMA; the idle MFMA
@@ -123,12 +133,7 @@ hipError_t launch_pack(const void *src, void *dst, int E, int R, int K, hipStrea
 // conversions, not its bytes, set the pace (decode gate-up 0.109 -> 0.112 ms); those keep 32.
 static int gate_up_wave_columns(bool stream, int wfmt, int tiles, int nseg, int F) {
     if (!stream || tiles > 3 || wfmt == bf16k::WF_MXFP4) return 32;
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
-        cus = v;
-    }
+    const long cus = cu_count();
     int best = 32;
     long best_cost = 0;
     for (int cw = 32; cw >= 16; cw -= 4) {
@@ -183,6 +188,15 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
         b.ksplit = a.ksplit;
         b.plane = a.plane;
         b.k.dst = a.partial;
+    }
+    // Streaming launches of at most 32 rows a segment in 128 columns a workgroup where that takes fewer whole rounds of the CUs.  Us, 256 /
+    // 128 columns (workgroups): one token on 8 experts (128 / 256) 46.7 / 39.7, 32 tokens on 64 experts, skewed (304 / 608) 47.4 /
+    // 42.7; not: two tokens on 8 experts (192 / 384) 56.3 / 60.6, 8 on 64 (about 184 / 368) 26.3 / 28.8, 32 on 64 (504 / 1008)
+    // 59.1 / 59.7, 16 on 8, 4-bit (512 / 1024) 40.5 / 42.7.  Stoppable launches count workgroups of 256 columns.
+    if (stream && tiles == 1 && a.go == nullptr) {
+        auto rounds = [&](int cols) { return ((long)n * ((a.H + cols - 1) / cols) * b.ksplit + cu_count() - 1) / cu_count(); };
+        b.narrow = rounds(128) < 2 * rounds(256);
+        if (b.narrow) b.k.col_tiles = (a.H + 127) / 128;
     }
     { Scope sc(a.prof, MOE_PROF_DOWN, s); launch(false); }
 }

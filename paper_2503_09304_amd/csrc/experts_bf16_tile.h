@@ -117,6 +117,7 @@ struct BArgs {
     KArgs k;
     int ksplit;          // 1, or 2 or 4: K ranges, one workgroup each, partial planes in k.dst
     long plane;          // elements between partial planes
+    int narrow;          // down projection in the narrow form
     int nseg;            // > 0: work on seg[0..nseg); 0: on units[u0 .. u0+nu) of the device list
     unsigned items;      // (segments or units) x column tiles x K ranges of a list; 0: XCD x works on seg[xcd[x]..xcd[x+1])
     uint32_t xcd[kXcds + 1];
@@ -124,7 +125,8 @@ struct BArgs {
 };
 
 // One (unit, column tile, K range) on a workgroup.
-template <int NF, bool GATEUP, int WF, bool STREAM, int D>
+// NM: 32-row matrices per wave (gate-up: W1, W3; down: its 64 rows of W2, or 32 of them in the narrow form).
+template <int NF, bool GATEUP, int WF, bool STREAM, int D, int NM = 2>
 __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, const int ct, const int kq, const int ksplit,
                                             const long plane, char *lds) {
     // Stoppable launches: the workgroup leaves behind the prologue's barrier if the stop word is set or
@@ -143,7 +145,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     // Output columns per wave.  Gate-up: 32, or fewer (p.cw, a multiple of 4) on launches whose
     // workgroup count would otherwise end in a partly filled round of the chip; the wave's MFMA rows
     // beyond p.cw repeat its last weight row and are dropped in the epilogue.
-    const int cpw = GATEUP ? p.cw : 64;
+    const int cpw = GATEUP ? p.cw : 32 * NM;
     const int rows = un.rows;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int lr = l & 15, lg = l >> 4;
@@ -224,8 +226,9 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
         aoff[j] = src_row * ((unsigned)p.lda >> 3);        // in 16-byte units: lda is a multiple of 64 elements
     });
 
-    f32x4 acc[NF * 4];                      // [fragment][matrix][row half]: 4 consecutive weight rows 4*lg .. of token lr
-    static_for<NF * 4>([&](auto tc) { acc[decltype(tc)::value] = f32x4{0.f, 0.f, 0.f, 0.f}; });
+    constexpr int NQ = 2 * NM;              // (matrix, row half) pairs
+    f32x4 acc[NF * NQ];                     // [fragment][matrix][row half]: 4 consecutive weight rows 4*lg .. of token lr
+    static_for<NF * NQ>([&](auto tc) { acc[decltype(tc)::value] = f32x4{0.f, 0.f, 0.f, 0.f}; });
 
     // Register rings: weight fragments of iterations it .. it+D (NB sets), token pieces of
     // it+1 .. it+D (NA sets).  Ring positions are compile-time constants: the loop is unrolled NA*NB.
@@ -234,11 +237,11 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     constexpr int DA = P3 || D == 2 ? 1 : 2;
     constexpr int NB = D + 1, NA = DA, U = (NB % NA == 0) ? NB : NA * NB;
     u32x4 a_reg[NA * T];
-    bf16x8 b_reg[(MX ? 1 : NB) * 8];    // [set][step j][matrix][row half]; MXFP4: the operands of the current iteration
-    u32x4 c_reg[NB * 2];                // MXFP4: codes [set][matrix]
-    unsigned short s_reg[NB * 2];       // MXFP4: the two scale bytes
+    bf16x8 b_reg[(MX ? 1 : NB) * 2 * NQ];    // [set][step j][matrix][row half]; MXFP4: the operands of the current iteration
+    u32x4 c_reg[NB * NM];                // MXFP4: codes [set][matrix]
+    unsigned short s_reg[NB * NM];       // MXFP4: the two scale bytes
 
-    // One load (piece j of T, piece i of 8) of iteration `it`, one LDS write of a token piece.
+    // One load (piece j of T, piece i of BL) of iteration `it`, one LDS write of a token piece.
     auto load_a = [&](int it, auto setc, auto jc) {
         constexpr int S = decltype(setc)::value, j = decltype(jc)::value;
         a_reg[S * T + j] = gload<u32x4>(abase + ((unsigned long)(aoff[j] + (unsigned)min(it, iters - 1) * 8u) << 4));
@@ -249,21 +252,21 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
         *reinterpret_cast<u32x4 *>(lds + stage * STAGE + (r * 8 + (sslot ^ swz(r))) * 16) = a_reg[S * T + j];
     };
     auto load_b = [&](int it, auto setc, auto ic) {
-        constexpr int S = decltype(setc)::value, i = decltype(ic)::value, q = i & 3, n = q >> 1, rt = q & 1;
+        constexpr int S = decltype(setc)::value, i = decltype(ic)::value, q = i % NQ, n = q >> 1, rt = q & 1;
         const long at = (long)min(it, iters - 1) * BIT;
-        if constexpr (MX && i >= 2) {
-            s_reg[S * 2 + (i & 1)] = gload<unsigned short>(sbase[i & 1] + (at >> 4) + soff[i & 1]);
+        if constexpr (MX && i >= NM) {
+            s_reg[S * NM + i - NM] = gload<unsigned short>(sbase[i - NM] + (at >> 4) + soff[i - NM]);
         } else if constexpr (MX) {
             const gchar from = bbase[i] + at + boff[i][0];
-            c_reg[S * 2 + i] = STREAM ? gload_nt<u32x4>(from) : gload<u32x4>(from);
+            c_reg[S * NM + i] = STREAM ? gload_nt<u32x4>(from) : gload<u32x4>(from);
         } else {
-            const gchar from = bbase[n] + at + boff[n][rt] + (i >> 2) * BJ;
-            b_reg[S * 8 + i] = STREAM ? gload_nt<bf16x8>(from) : gload<bf16x8>(from);
+            const gchar from = bbase[n] + at + boff[n][rt] + (i / NQ) * BJ;
+            b_reg[S * 2 * NQ + i] = STREAM ? gload_nt<bf16x8>(from) : gload<bf16x8>(from);
         }
     };
     auto load_a_all = [&](int it, auto setc) { static_for<T>([&](auto jc) { load_a(it, setc, jc); }); };
     auto store_a_all = [&](int stage, auto setc) { static_for<T>([&](auto jc) { store_a(stage, setc, jc); }); };
-    constexpr int BL = MX ? 4 : 8;          // weight loads of an iteration
+    constexpr int BL = MX ? 2 * NM : 2 * NQ;       // weight loads of an iteration
     auto load_b_all = [&](int it, auto setc) { static_for<BL>([&](auto ic) { load_b(it, setc, ic); }); };
     // MXFP4: codes and scales of ring set S -> the bf16 operands of (step j, matrix n), both row halves
     // (v_cvt_scalef32_pk_bf16_fp4: two e2m1 nibbles of one byte times a float scale, exact for a power-of-two scale).
@@ -271,8 +274,8 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     // groups of word 2j with the even ones of word 2j + 1 leaves rows 0-15 in the one and rows 16-31 in the other.
     auto dequant = [&](auto setc, auto jc, auto nc) {
         constexpr int S = decltype(setc)::value, j = decltype(jc)::value, n = decltype(nc)::value;
-        const u32x2 wv = __builtin_amdgcn_permlane16_swap(c_reg[S * 2 + n][2 * j], c_reg[S * 2 + n][2 * j + 1], false, false);
-        const unsigned sb = (unsigned)(s_reg[S * 2 + n] >> (8 * j)) << 23;     // (the other byte's bits land above or are masked)
+        const u32x2 wv = __builtin_amdgcn_permlane16_swap(c_reg[S * NM + n][2 * j], c_reg[S * NM + n][2 * j + 1], false, false);
+        const unsigned sb = (unsigned)(s_reg[S * NM + n] >> (8 * j)) << 23;     // (the other byte's bits land above or are masked)
         const u32x2 sv = __builtin_amdgcn_permlane16_swap(sb, sb, false, false);
         static_for<2>([&](auto rc) {
             constexpr int rt = decltype(rc)::value;
@@ -284,7 +287,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
             bf16x8 v;
             v[0] = e0[0]; v[1] = e0[1]; v[2] = e1[0]; v[3] = e1[1];
             v[4] = e2[0]; v[5] = e2[1]; v[6] = e3[0]; v[7] = e3[1];
-            b_reg[j * 4 + n * 2 + rt] = v;
+            b_reg[j * NQ + n * 2 + rt] = v;
         });
     };
 
@@ -316,7 +319,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
         if constexpr (SWAP) {
             // blocks 2j and 2j + 1 of a matrix -> its row halves of step j, as in dequant
             static_for<4>([&](auto pc) {
-                constexpr int at = S * 8 + decltype(pc)::value * 2;
+                constexpr int at = S * 2 * NQ + decltype(pc)::value * 2;
                 u32x4 x = __builtin_bit_cast(u32x4, b_reg[at]), y = __builtin_bit_cast(u32x4, b_reg[at + 1]);
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
@@ -328,13 +331,13 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
             __builtin_amdgcn_sched_barrier(0);
             asm volatile("s_nop 1");               // see mma
         }
-        static_for<4 * SL>([&](auto mc) {
-            constexpr int m = decltype(mc)::value, s = m / 4, q = m % 4, j = s / NF, f = s % NF, p = s + RF - 1;
+        static_for<NQ * SL>([&](auto mc) {
+            constexpr int m = decltype(mc)::value, s = m / NQ, q = m % NQ, j = s / NF, f = s % NF, p = s + RF - 1;
             constexpr int ring = P3 ? i * SL : 0;              // slots before this iteration
-            mma<m == 4 * SL - 1>(acc[f * 4 + q], b_reg[S * 8 + j * 4 + q], af[(ring + s) % RF]);
+            mma<m == NQ * SL - 1>(acc[f * NQ + q], b_reg[S * 2 * NQ + j * NQ + q], af[(ring + s) % RF]);
             if constexpr (q == 0 && p < SL) read_af(stage, std::integral_constant<int, p>{}, std::integral_constant<int, (ring + p) % RF>{});
             else if constexpr (q == 0 && P3) read_af(next, std::integral_constant<int, p - SL>{}, std::integral_constant<int, (ring + p) % RF>{});
-            constexpr int NV = T + BL, HALF = 2 * SL, V0 = m * NV / HALF, V1 = (m + 1) * NV / HALF;
+            constexpr int NV = T + BL, HALF = NQ * SL / 2, V0 = m * NV / HALF, V1 = (m + 1) * NV / HALF;
             if constexpr (m < HALF) {
                 static_for<V1 - V0>([&](auto vc) {
                     constexpr int v = V0 + decltype(vc)::value;
@@ -342,15 +345,17 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
                     else load_b(it + D, std::integral_constant<int, (i + D) % NB>{}, std::integral_constant<int, v - T>{});
                 });
             }
-            if constexpr (MX && (NF == 1 ? q == 0 || q == 2 : q == 1 && f < 2)) {
-                // the operands of step 1, then those of the next iteration's step 0
-                constexpr int set = j == 0 ? i % NB : (i + 1) % NB;
-                if constexpr (j == 0 || NF > 1 || q == 2)
-                    dequant(std::integral_constant<int, set>{}, std::integral_constant<int, 1 - j>{}, std::integral_constant<int, NF == 1 ? q / 2 : f>{});
-                if constexpr (j == 1 && NF == 1 && q == 2)
-                    dequant(std::integral_constant<int, set>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+            if constexpr (MX) {
+                // the operands of step 1, then those of the next iteration's step 0: matrix n after the MFMAs of fragment n (or
+                // all after a step's one fragment), at an MFMA that is not the step's last
+                constexpr int set = j == 0 ? i % NB : (i + 1) % NB, QD = NF == 1 ? NQ - 2 : 1;
+                if constexpr (q == QD && f < NM) {
+                    static_for<(NF == 1 ? NM : 1)>([&](auto nc) {
+                        dequant(std::integral_constant<int, set>{}, std::integral_constant<int, 1 - j>{}, std::integral_constant<int, f + decltype(nc)::value>{});
+                    });
+                }
             }
-            if constexpr (q == 2 && s >= SL - T) store_a(put, std::integral_constant<int, P3 ? 0 : (i + 1) % NA>{}, std::integral_constant<int, s - (SL - T)>{});
+            if constexpr (q == NQ - 2 && s >= SL - T) store_a(put, std::integral_constant<int, P3 ? 0 : (i + 1) % NA>{}, std::integral_constant<int, s - (SL - T)>{});
             __builtin_amdgcn_sched_barrier(0);
         });
         __syncthreads();
@@ -369,7 +374,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
         if constexpr (!P3 && j < DA) load_a_all(j, std::integral_constant<int, j % NA>{});
         load_b_all(j, std::integral_constant<int, j % NB>{});
     });
-    if constexpr (MX) static_for<2>([&](auto nc) { dequant(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, nc); });
+    if constexpr (MX) static_for<NM>([&](auto nc) { dequant(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, nc); });
     wg_decide(p, un.row0, 1, probe, &s_run);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
@@ -395,7 +400,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
                 constexpr int rt = decltype(rc)::value;
                 bf16x4 v;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = (__bf16)(silu_f(acc[f * 4 + rt][r]) * acc[f * 4 + 2 + rt][r]);
+                for (int r = 0; r < 4; ++r) v[r] = (__bf16)(silu_f(acc[f * NQ + rt][r]) * acc[f * NQ + NQ - 2 + rt][r]);
                 *reinterpret_cast<bf16x4 *>(st + (f * 16 + lr) * 32 + rt * 16 + lg * 4) = v;
             });
         });
@@ -424,25 +429,26 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
             }
         }
     } else {
-        // fp32 tile of 32 tokens x 64 columns at a time through this wave's 8 KiB of LDS (16 slots of 16 bytes per token,
-        // XORed by token), so that it leaves as 16-byte stores of 256 contiguous bytes per token row.
-        char *st = lds + w * (32 * 256);
-        float *obase = (float *)p.dst + kq * plane + (long)un.row0 * p.ldd + col_base + (l & 15) * 4;
-        const bool col_ok = col_base + (l & 15) * 4 < p.ncols;
+        // fp32 tile of 32 tokens x 64 (narrow: 32) columns at a time through this wave's part of LDS (slots of 16 bytes,
+        // XORed by token), so that it leaves as 16-byte stores of 256 (128) contiguous bytes per token row.
+        constexpr int SR = 8 * NM;              // slots of a token
+        char *st = lds + w * (32 * SR * 16);
+        float *obase = (float *)p.dst + kq * plane + (long)un.row0 * p.ldd + col_base + (l % SR) * 4;
+        const bool col_ok = col_base + (l % SR) * 4 < p.ncols;
         static_for<T>([&](auto tc) {
             constexpr int t = decltype(tc)::value;
             if (t * 32 < rows) {
                 __builtin_amdgcn_wave_barrier();
-                static_for<8>([&](auto qc) {
-                    constexpr int q = decltype(qc)::value & 3, h = decltype(qc)::value >> 2;
-                    if constexpr (2 * t + h < NF) *reinterpret_cast<f32x4 *>(st + (h * 16 + lr) * 256 + ((q * 4 + lg) ^ lr) * 16) = acc[(2 * t + h) * 4 + q];
+                static_for<2 * NQ>([&](auto qc) {
+                    constexpr int q = decltype(qc)::value % NQ, h = decltype(qc)::value / NQ;
+                    if constexpr (2 * t + h < NF) *reinterpret_cast<f32x4 *>(st + ((h * 16 + lr) * SR + ((q * 4 + lg) ^ (lr % SR))) * 16) = acc[(2 * t + h) * NQ + q];
                 });
                 __builtin_amdgcn_s_waitcnt(0xc07f);
                 __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int i = (l >> 4) + 4 * j;
-                    const f32x4 v = *reinterpret_cast<const f32x4 *>(st + i * 256 + ((l & 15) ^ (i & 15)) * 16);
+                for (int j = 0; j < 4 * NM; ++j) {
+                    const int i = l / SR + 64 / SR * j;
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(st + (i * SR + ((l % SR) ^ (i % SR))) * 16);
                     if (t * 32 + i < rows && col_ok) gstore_nt(v, (obase + (long)(t * 32 + i) * p.ldd));
                 }
                 __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -524,6 +530,20 @@ __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
 #undef QMOE_TILE
 }
 
+// The down projection of at most 32 rows in the narrow form: 128 columns a workgroup, for launches of few workgroups.
+template <int WF>
+__global__ __launch_bounds__(256) void expert_down_narrow(const BArgs b) {
+    __shared__ __attribute__((aligned(16))) char lds[16384];
+    int ct, kq;
+    moe_unit un;
+    if (!map_block<true>(b, un, ct, kq)) return;
+    const KArgs k = b.k;
+    const int ksplit = b.ksplit;
+    const long plane = b.plane;
+    if (un.rows > 16) expert_tile<2, false, WF, true, 5, 1>(k, un, ct, kq, ksplit, plane, lds);
+    else expert_tile<1, false, WF, true, 5, 1>(k, un, ct, kq, ksplit, plane, lds);
+}
+
 template <int TCAP, bool GATEUP, int WF, bool STREAM>
 void launch1(const BArgs &b, hipStream_t s) {
     const unsigned grid = b.items ? item_grid(b.items) : dealt_grid(b.xcd, (unsigned)(b.k.col_tiles * b.ksplit));
@@ -545,6 +565,12 @@ void launch_ts(int tiles, const BArgs &b, hipStream_t s) {
 // translation unit of its own (experts_bf16_w<WF>_<kernel>.hip).
 template <int WF, bool GATEUP>
 void launch_expert_kernel(int tiles, bool stream, const BArgs &b, hipStream_t s) {
+    if constexpr (!GATEUP) {
+        if (b.narrow) {
+            hipLaunchKernelGGL(expert_down_narrow<WF>, dim3(item_grid(b.items)), dim3(256), 0, s, b);
+            return;
+        }
+    }
     if (stream) launch_ts<GATEUP, WF, true>(tiles, b, s);
     else launch_ts<GATEUP, WF, false>(tiles, b, s);
 }

@@ -60,3 +60,42 @@ def test_every_fragment_count(fmt, H, F, ksplit):
     for c in sorted({1, 15} | {16 * i + d for i in range(1, 16) for d in (0, 1)} | {255}):
         print("case", fmt, "rows", c, flush=True)
         assert torch.equal(run(c, 1), whole), (fmt, c)
+
+
+@pytest.mark.parametrize("fmt,E,H,F,rows", [("rowmajor", 1, 192, 320, 1), ("packed", 2, 320, 256, 17), ("packed", 3, 64, 512, 32), ("packed", 1, 2048, 256, 16)])
+def test_narrow_down_projection(fmt, E, H, F, rows):
+    """Small launches put 128 columns of the down projection in a workgroup: `rows` rows per expert (k = E, every token on
+    every expert) against plain products, and against the enqueued form, which keeps 256."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows + H)
+
+    def t(shape, std):
+        return (torch.randn(shape, generator=gen, device=DEV) * std).bfloat16()
+
+    x, Wg = t((rows, H), 1.0), t((H, E), 0.02)
+    src = [t((E, F, H), H ** -0.5), t((E, F, H), H ** -0.5), t((E, H, F), F ** -0.5)]
+    w = q.Context.weights(Wg, *src)
+    if fmt == "packed":
+        hold = [torch.empty((16, H), dtype=torch.bfloat16, device=DEV)] + [torch.empty_like(v) for v in src]
+        p = q.Context.weights(*hold)
+        q.moe_pack_weights(q.MoeConfig(E, 1, H, F, q.MOE_BF16, 1, 0), w, p)
+        w = p
+    prio = torch.zeros(rows, dtype=torch.uint8, device=DEV)
+    outs = []
+    for enqueued in (False, True):
+        ctx = q.Context(E, E, H, F, q.MOE_BF16, 256, rows, device=DEV)
+        ctx.route(x, w)
+        ctx.permute(prio)
+        if enqueued:
+            ctx.expert_enqueue(x, w, q.UINT32_MAX)
+            assert ctx.expert_collect() == q.MOE_DONE
+        else:
+            assert ctx.expert_run(x, w) == q.MOE_DONE
+        outs.append(ctx.get("expert_out").clone())
+        torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+    for e in range(E):                                  # sorted order: expert by expert, tokens ascending
+        g, u = x.double() @ src[0][e].double().t(), x.double() @ src[1][e].double().t()
+        ref = (g / (1 + torch.exp(-g)) * u) @ src[2][e].double().t()
+        got = outs[0][e * rows: (e + 1) * rows].double()
+        assert ((got - ref).abs().max() / ref.pow(2).mean().sqrt()).item() <= bar("bf16", H, F)
