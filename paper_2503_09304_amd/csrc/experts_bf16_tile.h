@@ -498,7 +498,7 @@ __device__ __forceinline__ bool map_block(const BArgs &b, moe_unit &un, int &ct,
 // in L2.  Where segments share an expert's weights the hint is left off so that L2 serves the re-reads.
 template <int TCAP, bool GATEUP, int WF, bool STREAM>
 __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
-    // two token-tile stages (three from 4 token tiles on); at least 8 KiB per wave for the
+    // two token-tile stages (three from 65 rows on, kP3MinT); at least 8 KiB per wave for the
     // epilogue's store staging
     __shared__ __attribute__((aligned(16))) char lds[((TCAP >= kP3MinT ? 3 : 2) * TCAP * 32 * 128) > 32768 ? ((TCAP >= kP3MinT ? 3 : 2) * TCAP * 32 * 128) : 32768];
     // A closed gate: the sequence was stopped before this launch, or an earlier workgroup of it saw
