@@ -291,7 +291,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
         });
     };
 
-    // One K-iteration is 4*T slots, written out in the order in which they shall issue (nothing moves across a slot's
+    // One K-iteration is 2*NF slots, written out in the order in which they shall issue (nothing moves across a slot's
     // end): slot s has the 4 MFMAs of one token fragment (step j = s / NF, fragment s % NF), one LDS fragment read (RF - 1
     // slots before its use), and its share of the T + 8 global loads (first half of the slots, so the texture path works
     // under the MFMAs instead of in a burst) and of the T LDS writes of the next token tile (last slots).

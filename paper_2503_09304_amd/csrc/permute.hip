@@ -79,15 +79,20 @@ __device__ int block_excl_scan(int32_t *v, int32_t *tmp, int n) {
 }
 
 // The engine's report to the scheduler after the router stage (Sec. 3.2): the queue lengths and the
-// unit count go straight into host memory as soon as they are known, before the ranking work, and the
+// number of units they imply go straight into host memory as soon as they are known, before the scans and the ranking, and the
 // sequence word is stored last, after a system-scope fence, so a host that sees the sequence number
-// sees the report.  Called by every thread of the one workgroup that knows the totals.
-__device__ __forceinline__ void report_to_host(int32_t *__restrict__ report, int32_t seq, const int32_t *tot, int nb, int nu) {
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) report[b] = tot[b];
-    if (threadIdx.x == 0) report[nb] = nu;
+// sees the report.  Called by one wave (lane l), behind the barrier that completes tot.
+__device__ __forceinline__ void report_to_host(int32_t *__restrict__ report, int32_t seq, const int32_t *tot, int nb, int C, int l) {
+    int nu = 0;
+    for (int b = l; b < nb; b += 64) {
+        report[b] = tot[b];
+        nu += (tot[b] + C - 1) / C;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) nu += __shfl_xor(nu, o, 64);
+    if (l == 0) report[nb] = nu;
     __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(report + nb + 1, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (l == 0) __hip_atomic_store(report + nb + 1, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ __launch_bounds__(1024) void perm_scan(int32_t *__restrict__ blockcnt, int nblocks, int E, int C,
@@ -102,38 +107,40 @@ __global__ __launch_bounds__(1024) void perm_scan(int32_t *__restrict__ blockcnt
     // Per bucket, the exclusive prefix over the blocks.  The 1024 threads cut the blocks into
     // `slices` ranges per bucket (thread = (slice, bucket)): sums of the ranges, their prefix through
     // LDS, then each thread rewrites its range; the loads of a range do not depend on one another.
+    // The report leaves between the two, so that the host's launch of the expert kernels travels while the offsets, the
+    // unit list and perm_scatter are on their way (sent behind the unit list, layer of 1100 tokens, top-8 of 64 experts, 335 -> 330 us; 4000
+    // tokens, top-8 of 128, 281 -> 275; 8192 tokens on 64 the same within a run's spread).
+    static_assert(2 * kMaxExperts <= 1024, "a thread per bucket");
     __shared__ int32_t part[1024];
-    const int slices = blockDim.x / nb > 0 ? blockDim.x / nb : 1;
+    const int slices = blockDim.x / nb;
     const int per = (nblocks + slices - 1) / slices;
-    for (int b0 = 0; b0 < nb; b0 += blockDim.x) {            // one pass unless there are more buckets than threads
-        const int sl = slices > 1 ? tid / nb : 0;
-        const int b = b0 + (slices > 1 ? tid - sl * nb : tid);
-        const bool active = b < nb && sl < slices;
-        const int blk0 = sl * per, blk1 = min(nblocks, blk0 + per);
-        int sum = 0;
-        if (active)
-            for (int blk = blk0; blk < blk1; ++blk) sum += blockcnt[(long)blk * nb + b];
-        if (active && slices > 1) part[sl * nb + (b - b0)] = sum;
-        __syncthreads();
-        int run = 0;
-        if (active && slices > 1) {
-            int total = 0;
-            for (int q = 0; q < slices; ++q) {
-                const int v = part[q * nb + (b - b0)];
-                if (q < sl) run += v;
-                total += v;
-            }
-            sum = total;
+    const int sl = tid / nb, mine = tid - sl * nb;
+    const bool active = sl < slices;
+    const int blk0 = sl * per, blk1 = min(nblocks, blk0 + per);
+    int sum = 0;
+    if (active) {
+        for (int blk = blk0; blk < blk1; ++blk) sum += blockcnt[(long)blk * nb + mine];
+        part[sl * nb + mine] = sum;
+    }
+    __syncthreads();
+    int run = 0;
+    if (active) {
+        int all = 0;
+        for (int q = 0; q < slices; ++q) {
+            const int v = part[q * nb + mine];
+            if (q < sl) run += v;
+            all += v;
         }
-        if (active) {
-            for (int blk = blk0; blk < blk1; ++blk) {
-                const int c = blockcnt[(long)blk * nb + b];
-                blockcnt[(long)blk * nb + b] = run;
-                run += c;
-            }
-            if (sl == 0) { tot[b] = sum; boff[b] = sum; }
+        if (sl == 0) { tot[mine] = all; boff[mine] = all; }
+    }
+    __syncthreads();
+    if (tid < 64) report_to_host(report, seq, tot, nb, C, tid);
+    if (active) {
+        for (int blk = blk0; blk < blk1; ++blk) {
+            const int c = blockcnt[(long)blk * nb + mine];
+            blockcnt[(long)blk * nb + mine] = run;
+            run += c;
         }
-        __syncthreads();
     }
     const int total = block_excl_scan(boff, tmp, nb);
     for (int b = tid; b < nb; b += blockDim.x) {
@@ -149,7 +156,6 @@ __global__ __launch_bounds__(1024) void perm_scan(int32_t *__restrict__ blockcnt
     __syncthreads();
     const int nu = block_excl_scan(ustart, tmp, nb);
     if (tid == 0) *n_units = nu;
-    report_to_host(report, seq, tot, nb, nu);
     for (int q = tid; q < nb; q += blockDim.x) {
         const int cl = q / E, e = q - cl * E;
         const int len = tot[2 * e + cl], first = boff[2 * e + cl];
@@ -201,20 +207,8 @@ __global__ __launch_bounds__(kPermBlock) void perm_fused(const int32_t *__restri
         if (a - n * k == 0) cls[n] = (uint8_t)c;
     }
     __syncthreads();
-    // The report leaves as soon as the histogram is complete: wave 0 writes the counts and the number
-    // of units they imply, fences, and stores the sequence word, while the other waves go on.
-    if (w == 0) {
-        int nu_part = 0;
-        for (int b = l; b < nb; b += 64) {
-            report[b] = tot[b];
-            nu_part += (tot[b] + C - 1) / C;
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) nu_part += __shfl_xor(nu_part, o, 64);
-        if (l == 0) report[nb] = nu_part;
-        __threadfence_system();
-        if (l == 0) __hip_atomic_store(report + nb + 1, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    // The report leaves as soon as the histogram is complete, while the other waves go on.
+    if (w == 0) report_to_host(report, seq, tot, nb, C, l);
     for (int b = tid; b < nb; b += kPermBlock) boff[b] = tot[b];
     __syncthreads();
     const int total = block_excl_scan(boff, tmp, nb);
