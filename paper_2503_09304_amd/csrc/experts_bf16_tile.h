@@ -157,7 +157,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     // A wave has two matrices of 32 rows (gate-up: W1, W3; down: the two halves of its 64 rows of W2), each in two row
     // halves of 16 (rt).  Of an iteration's 64 k, eight pieces of 8, MFMA step j (0, 1) takes for lane group lg piece
     // 4j + 2*(lg%2) + lg/2, tokens and weights alike: any order does, and this one is a single swap of lane groups away
-    // from the 4-bit blocks (see dequant).
+    // from the 4-bit blocks (see dequant_piece).
     // A load = uniform base of the matrix + the lane's 32-bit offset + constants.
     // Row-major: 16 bytes of the lane's row, pieces 2j apart 32 bytes.
     // Packed: the 1 KiB block of k-step s of row tile nt starts at (nt*(K/16)+s)*1024 bytes; pieces (s, half) of the
@@ -272,22 +272,29 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     // (v_cvt_scalef32_pk_bf16_fp4: two e2m1 nibbles of one byte times a float scale, exact for a power-of-two scale).
     // Lane groups of 16 hold (rows 0-15, half 0), (16-31, 0), (0-15, 1), (16-31, 1) of the k-steps' words; swapping the odd
     // groups of word 2j with the even ones of word 2j + 1 leaves rows 0-15 in the one and rows 16-31 in the other.
-    auto dequant = [&](auto setc, auto jc, auto nc) {
-        constexpr int S = decltype(setc)::value, j = decltype(jc)::value, n = decltype(nc)::value;
-        const u32x2 wv = __builtin_amdgcn_permlane16_swap(c_reg[S * NM + n][2 * j], c_reg[S * NM + n][2 * j + 1], false, false);
-        const unsigned sb = (unsigned)(s_reg[S * NM + n] >> (8 * j)) << 23;     // (the other byte's bits land above or are masked)
-        const u32x2 sv = __builtin_amdgcn_permlane16_swap(sb, sb, false, false);
-        static_for<2>([&](auto rc) {
-            constexpr int rt = decltype(rc)::value;
-            const float f = __builtin_bit_cast(float, sv[rt] & 0x7f800000u);
-            const bf16x2 e0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv[rt], f, 0);
-            const bf16x2 e1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv[rt], f, 1);
-            const bf16x2 e2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv[rt], f, 2);
-            const bf16x2 e3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(wv[rt], f, 3);
-            bf16x8 v;
-            v[0] = e0[0]; v[1] = e0[1]; v[2] = e1[0]; v[3] = e1[1];
-            v[4] = e2[0]; v[5] = e2[1]; v[6] = e3[0]; v[7] = e3[1];
-            b_reg[j * NQ + n * 2 + rt] = v;
+    // In kPieces pieces, so that they can be dealt out among MFMAs (see body): the swaps, then two conversions each.
+    constexpr int kPieces = 5;
+    u32x2 dq_w[NM], dq_s[NM];            // words and scales of a matrix, by row half
+    auto dequant_piece = [&](auto setc, auto jc, auto nc, auto pc) {
+        constexpr int S = decltype(setc)::value, j = decltype(jc)::value, n = decltype(nc)::value, p = decltype(pc)::value;
+        if constexpr (p == 0) {
+            dq_w[n] = __builtin_amdgcn_permlane16_swap(c_reg[S * NM + n][2 * j], c_reg[S * NM + n][2 * j + 1], false, false);
+            const unsigned sb = ((unsigned)(s_reg[S * NM + n] >> (8 * j)) << 23) & 0x7f800000u;     // (the other byte's bits go)
+            dq_s[n] = __builtin_amdgcn_permlane16_swap(sb, sb, false, false);
+        } else {
+            constexpr int rt = (p - 1) / 2, h = (p - 1) % 2;
+            const unsigned sb = dq_s[n][rt];     // (a bit cast of a vector's element itself takes element 0)
+            const float f = __builtin_bit_cast(float, sb);
+            const bf16x2 e0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(dq_w[n][rt], f, 2 * h);
+            const bf16x2 e1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(dq_w[n][rt], f, 2 * h + 1);
+            bf16x8 &v = b_reg[j * NQ + n * 2 + rt];
+            v[4 * h] = e0[0]; v[4 * h + 1] = e0[1]; v[4 * h + 2] = e1[0]; v[4 * h + 3] = e1[1];
+        }
+    };
+    auto dequant_all = [&](auto setc, auto jc) {
+        static_for<NM * kPieces>([&](auto vc) {
+            constexpr int v = decltype(vc)::value;
+            dequant_piece(setc, jc, std::integral_constant<int, v / kPieces>{}, std::integral_constant<int, v % kPieces>{});
         });
     };
 
@@ -317,7 +324,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (!P3) read_first(stage);
         if constexpr (SWAP) {
-            // blocks 2j and 2j + 1 of a matrix -> its row halves of step j, as in dequant
+            // blocks 2j and 2j + 1 of a matrix -> its row halves of step j, as in dequant_piece
             static_for<4>([&](auto pc) {
                 constexpr int at = S * 2 * NQ + decltype(pc)::value * 2;
                 u32x4 x = __builtin_bit_cast(u32x4, b_reg[at]), y = __builtin_bit_cast(u32x4, b_reg[at + 1]);
@@ -346,12 +353,20 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
                 });
             }
             if constexpr (MX) {
-                // the operands of step 1, then those of the next iteration's step 0: matrix n after the MFMAs of fragment n (or
-                // all after a step's one fragment), at an MFMA that is not the step's last
-                constexpr int set = j == 0 ? i % NB : (i + 1) % NB, QD = NF == 1 ? NQ - 2 : 1;
-                if constexpr (q == QD && f < NM) {
-                    static_for<(NF == 1 ? NM : 1)>([&](auto nc) {
-                        dequant(std::integral_constant<int, set>{}, std::integral_constant<int, 1 - j>{}, std::integral_constant<int, f + decltype(nc)::value>{});
+                // The operands of step 1, then those of the next iteration's step 0, their pieces dealt out behind the step's first SP
+                // MFMAs (never its last: see mma).  An MFMA of 16 cycles hides three or four vector instructions; a matrix converted in
+                // one go behind one MFMA leaves the matrix unit idle where no other wave has MFMAs to issue.  Us in one go / dealt out:
+                // 308 tokens on 64 experts, 16 units a launch, 177 / 166; 60 tokens, top-8 of 16, H 1344, F 10816, down projection
+                // 83.4 / 77.7; 500 tokens on 8 experts 359 / 345, 3584 tokens 1854 / 1798.  With 4 fragments a step's second half is
+                // better left to the LDS writes: that down projection 78.6 with pieces up to the step's end.
+                constexpr int set = j == 0 ? i % NB : (i + 1) % NB, t = m - j * NF * NQ, NP = NM * kPieces;
+                constexpr int SP = NF == 4 ? NF * NQ / 2 : NF * NQ - 1;
+                if constexpr (t < SP) {
+                    constexpr int P0 = t * NP / SP, P1 = (t + 1) * NP / SP;
+                    static_for<P1 - P0>([&](auto vc) {
+                        constexpr int v = P0 + decltype(vc)::value;
+                        dequant_piece(std::integral_constant<int, set>{}, std::integral_constant<int, 1 - j>{}, std::integral_constant<int, v / kPieces>{},
+                                      std::integral_constant<int, v % kPieces>{});
                     });
                 }
             }
@@ -374,7 +389,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
         if constexpr (!P3 && j < DA) load_a_all(j, std::integral_constant<int, j % NA>{});
         load_b_all(j, std::integral_constant<int, j % NB>{});
     });
-    if constexpr (MX) static_for<NM>([&](auto nc) { dequant(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, nc); });
+    if constexpr (MX) dequant_all(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
     wg_decide(p, un.row0, 1, probe, &s_run);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();

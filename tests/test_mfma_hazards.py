@@ -78,3 +78,19 @@ def test_mfma_wait_states(name, tmp_path):
                 assert not regs(y) & dst, (kernel, x, y)
                 left -= waits(y)
                 i += 1
+
+
+@pytest.mark.parametrize("name", ["experts_bf16_w2_gate_up", "experts_bf16_w2_down"])
+def test_conversions_stand_between_mfmas(name, tmp_path):
+    """4-bit weights: at most 12 conversions between one MFMA and the next.  16 of them in a row (all of an MFMA step's, as in
+    front of a variant's first iteration) leave the matrix unit idle where a workgroup has a CU to itself."""
+    for kernel, ins in kernels(name, tmp_path):
+        tcap = re.search(r"expert_bf16ILi(\d)E", kernel)
+        variants = {1: 2, 2: 3, 4: 7, 6: 11, 8: 15}[int(tcap.group(1))] if tcap else 2      # copies of the loop: 1, 2, 4, 5 .. 2 * tcap fragments
+        gaps, run = [], 0
+        for x in ins:
+            if x.startswith("v_mfma"):
+                gaps.append(run)
+                run = 0
+            run += x.startswith("v_cvt_scalef32_pk_bf16_fp4")
+        assert max(gaps) <= 16 and sum(g > 12 for g in gaps) <= variants, (kernel, sorted(gaps)[-variants - 3:])
