@@ -155,6 +155,9 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
     const unsigned n = b.nseg > 0 ? (unsigned)b.nseg : a.nu;
     b.k = gu_in;
     b.k.cw = a.wave_cols ? a.wave_cols : gate_up_wave_columns(stream, a.wfmt, tiles, (int)n, a.F);
+    // A lane's place in a packed row tile is a 32-bit offset from the tile of the wave's first row (64 * H bytes each): rows so
+    // long keep waves of 32 columns, which lie in one tile.
+    if (a.H >= 1 << 26) b.k.cw = 32;
     b.k.col_tiles = (a.F + 4 * b.k.cw - 1) / (4 * b.k.cw);
     auto launch_one = [&](bool gateup) {
         using namespace bf16k;

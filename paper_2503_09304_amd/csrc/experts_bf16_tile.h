@@ -173,7 +173,9 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     constexpr int BJ = PACKED ? 2048 : 64;      // bytes between the two MFMA steps
     constexpr int BIT = PACKED ? 4096 : (MX ? 1024 : 128);   // bytes between iterations (MXFP4: of codes)
     gchar bbase[2], sbase[2];                   // the matrices (MXFP4: codes and scales), at this workgroup's K range
-    unsigned boff[2][2], soff[2];               // [matrix][row half]; MXFP4: [matrix][0], one load for both halves
+    // Row-major rows lie 2*K bytes apart, and 64 of them pass 4 GiB from K of 34 million on.
+    std::conditional_t<WF == WF_ROWMAJOR, unsigned long, unsigned> boff[2][2];      // [matrix][row half]; MXFP4: [matrix][0], one load for both halves
+    unsigned soff[2];
     {
         gchar e0 = (gchar)p.b0, e1 = GATEUP ? (gchar)p.b1 : e0;
         const long ebytes = MX ? p.b_estride >> 1 : p.b_estride * 2;
@@ -206,7 +208,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
                 } else if constexpr (PACKED) {
                     boff[n][rt] = t * (unsigned)tile_bytes + (unsigned)(lane_piece + (row & 31) * 16);
                 } else {
-                    boff[n][rt] = (unsigned)(row - first) * (unsigned)(p.K * 2) + (unsigned)lane_piece;
+                    boff[n][rt] = (unsigned long)(row - first) * ((unsigned long)p.K * 2) + (unsigned)lane_piece;
                 }
             }
         }
