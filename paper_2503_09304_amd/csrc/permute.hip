@@ -78,10 +78,11 @@ __device__ int block_excl_scan(int32_t *v, int32_t *tmp, int n) {
     return total;
 }
 
-// The engine's report to the scheduler after the router stage (Sec. 3.2): the queue lengths and the
-// number of units they imply go straight into host memory as soon as they are known, before the scans and the ranking, and the
-// sequence word is stored last, after a system-scope fence, so a host that sees the sequence number
-// sees the report.  Called by one wave (lane l), behind the barrier that completes tot.
+// The engine's report to the scheduler after the router stage (Sec. 3.2): the queue lengths go straight into host memory as
+// soon as they are known, before the scans and the ranking, with the number of units that they imply (by which the host
+// sees that the report arrived whole; it says nothing of the unit list, which is built later and counted in *n_units), and
+// the sequence word is stored last, after a system-scope fence, so a host that sees the sequence number sees the report.
+// Called by one wave (lane l), behind the barrier that completes tot.
 __device__ __forceinline__ void report_to_host(int32_t *__restrict__ report, int32_t seq, const int32_t *tot, int nb, int C, int l) {
     int nu = 0;
     for (int b = l; b < nb; b += 64) {
@@ -108,8 +109,8 @@ __global__ __launch_bounds__(1024) void perm_scan(int32_t *__restrict__ blockcnt
     // `slices` ranges per bucket (thread = (slice, bucket)): sums of the ranges, their prefix through
     // LDS, then each thread rewrites its range; the loads of a range do not depend on one another.
     // The report leaves between the two, so that the host's launch of the expert kernels travels while the offsets, the
-    // unit list and perm_scatter are on their way (sent behind the unit list, layer of 1100 tokens, top-8 of 64 experts, 335 -> 330 us; 4000
-    // tokens, top-8 of 128, 281 -> 275; 8192 tokens on 64 the same within a run's spread).
+    // unit list and perm_scatter are on their way (sent behind the scans, in front of the unit list, layer of 1100 tokens, top-8 of 64
+    // experts, 335 -> 330 us; 4000 tokens, top-8 of 128, 281 -> 275; 8192 tokens on 64 the same within a run's spread).
     static_assert(2 * kMaxExperts <= 1024, "a thread per bucket");
     __shared__ int32_t part[1024];
     const int slices = blockDim.x / nb;

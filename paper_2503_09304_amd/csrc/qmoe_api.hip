@@ -93,7 +93,7 @@ Layout make_layout(const moe_config &c) {
     L.logits = take(N * E * 4);
     L.topk_idx = take(A * 4);
     L.topk_w = take(A * 4);
-    L.cnt = take((2 * E + 1) * 4);      // counts [E][2], then the unit count: read back in one copy
+    L.cnt = take((2 * E + 1) * 4);      // counts [E][2], then the length of the device's unit list
     L.n_units = L.cnt + 2 * E * 4;
     L.off = take((2 * E + 1) * 4);
     L.perm = take(A * 4);
@@ -369,9 +369,9 @@ int32_t moe_permute(moe_ctx *ctx, const uint8_t *prio, moe_cursor *cursor, void 
         a.seq = ctx->seq;
         hipError_t e = qmoe::launch_permute(a, s);
         if (e != hipSuccess) return hip_fail(e, "moe_permute: launch");
-        // The kernel stores the counts, the unit count and then the sequence word into host memory as
-        // soon as it knows them; wait for that word (bounded: after kReportSpinMs fall back to waiting
-        // for the stream, which also surfaces a failed launch).
+        // The kernel stores the counts, the number of units they imply and then the sequence word into host
+        // memory as soon as it knows them; wait for that word (bounded: after kReportSpinMs fall back to
+        // waiting for the stream, which also surfaces a failed launch).
         volatile int32_t *word = ctx->pinned + 2 * E + 1;
         const auto t0 = std::chrono::steady_clock::now();
         bool seen = false;
@@ -399,7 +399,7 @@ int32_t moe_permute(moe_ctx *ctx, const uint8_t *prio, moe_cursor *cursor, void 
     if (rc != MOE_OK) return rc;
     if (n > ctx->lay.max_units) return fail(MOE_E_HIP, "moe_permute: %u units exceed the bound %u", n, ctx->lay.max_units);
     if (ctx->N > 0 && (int32_t)n != ctx->pinned[2 * E])
-        return fail(MOE_E_HIP, "moe_permute: device built %d units, host %u", ctx->pinned[2 * E], n);
+        return fail(MOE_E_HIP, "moe_permute: damaged report of the queue lengths: they make %u units, reported with them %d", n, ctx->pinned[2 * E]);
     ctx->units.resize(n);
     ctx->n_units = n;
     ctx->n_ls_units = 0;

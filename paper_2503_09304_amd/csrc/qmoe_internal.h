@@ -68,9 +68,9 @@ struct PermuteArgs {
     int32_t *blockoff;  // scratch [nblocks][2E]
     uint8_t *cls;       // [N] 0 = LS, 1 = BE
     moe_unit *units;    // device unit list
-    int32_t *n_units;   // device scalar
+    int32_t *n_units;   // units in the list (device scalar, for tests)
     int32_t max_units;
-    int32_t *report;    // host memory mapped into the device: counts [2E], unit count, sequence word
+    int32_t *report;    // host memory mapped into the device: counts [2E], number of units they imply, sequence word
     int32_t seq;        // value the kernel stores into the sequence word once the report is written
 };
 hipError_t launch_permute(const PermuteArgs &a, hipStream_t s);

@@ -1,5 +1,6 @@
-"""The permutation in three kernels (more than 8192 assignments): bucket order, queue lengths and unit list against a stable
-sort, at the smallest such batches, a last block of one assignment, and one to 256 experts (2 to 512 ranges of blocks per bucket)."""
+"""The permutation in three kernels (more than 8192 assignments): bucket order, queue lengths and the unit list, the host's and
+the device's, against a stable sort, at the smallest such batches, a last block of one assignment, and one to 256 experts (2 to
+512 ranges of blocks per bucket); the same of the kernel for fewer."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +11,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("E,k,N", [(1, 1, 8193), (3, 3, 2731), (64, 8, 1025), (256, 8, 1025), (255, 5, 4096), (8, 2, 8192)])
+@pytest.mark.parametrize("E,k,N", [(1, 1, 8193), (3, 3, 2731), (64, 8, 1025), (256, 8, 1025), (255, 5, 4096), (8, 2, 8192),
+                                   (1, 1, 1), (64, 8, 1024), (256, 2, 1000)])
 def test_three_kernels_sort_like_one(E, k, N):
     gen = torch.Generator(device=DEV)
     gen.manual_seed(E + N)
@@ -32,3 +34,7 @@ def test_three_kernels_sort_like_one(E, k, N):
         units = [(e, c, int(first[2 * e + c]) + r, min(100, int(lens[2 * e + c]) - r))
                  for c in (0, 1) for e in range(E) for r in range(0, int(lens[2 * e + c]), 100)]
         assert [tuple(int(v) for v in u) for u in ctx.units()] == units
+        # nothing reports what the device's list holds, the host makes its own from the reported lengths: the list, and its length behind the counts
+        assert [tuple(u) for u in ctx.get("units").cpu().tolist()] == units
+        at = ctx.get("counts").data_ptr() - ctx.ws.data_ptr() + 8 * E
+        assert int(ctx.ws[at: at + 4].view(torch.int32)) == len(units)
