@@ -189,7 +189,8 @@ int32_t moe_route(moe_ctx *ctx, const void *x, int32_t n_tokens, const moe_weigh
  * buffer the bf16 router needs (Wg transposed and padded, ceil16(E)*H bf16) lives in a 2 MiB array in
  * the library's device image, one copy per GPU, held until the process ends.  Always the router in one
  * launch: moe_route, which has scratch in its workspace, deals the gate GEMM of up to 1024 bf16 tokens
- * to several CUs in a launch of its own (32 tokens on 64 experts, H 2048: 10 us instead of 14).
+ * to several CUs in a launch of its own where that is faster (32 tokens on 64 experts, H 2048: 10 us
+ * instead of 14).
  *   cfg: E, k, H and dtype are used.  x [device] [n_tokens,H]; Wg [device] [H,E] row-major;
  *   logit_bias [device] float[E] or NULL; outputs [device]: logits float[n_tokens,E], topk_idx
  *   int32[n_tokens,k], topk_w float[n_tokens,k].

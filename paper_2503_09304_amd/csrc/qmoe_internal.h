@@ -40,12 +40,22 @@ struct RouteArgs {
     bool packed;  // Wg already transposed and padded ([E16][H])
 };
 // The bf16 router in two launches, its GEMM dealt out in 8 K ranges to workgroups of their own: where one workgroup per
-// 16 tokens leaves CUs idle while each takes in all the weights.  Us as one launch / as two, 1, 32, 1024, 2048 tokens: top-8 of
-// 64, H 2048 11.4 / 8.5, 14.0 / 10.0, 14.5 / 12.0, 14.7 / 15.9; of 256 35.7 / 19.2, 39.4 / 24.4, 39.9 / 32.3, 40.2 / 47.0;
-// top-2 of 8, H 4096 5.8 / 6.2, 8.8 / 6.9, 9.2 / 7.1, 9.6 / 9.5; 8 tokens 7.4 / 6.6; H 1024 4.2 / 4.9, 6.0 / 5.5, 6.3 / 5.6,
-// 6.3 / 6.2; top-2 of 16, H 4096, one token 7.0 / 6.4; top-4 of 16, H 2048, one token 5.2 / 5.9.
+// 16 tokens leaves CUs idle while each takes in all the weights.  One launch takes a wave's share of K (H / 256 MFMA steps)
+// in rounds of 8 steps up to 16 experts, 4 up to 32, else 2; what a second launch costs grows with the experts, what it
+// saves with the rounds.  Us as one launch / as two, back to back in a graph:
+//   more than 32 experts: one round, 128 experts, H 512, 16 tokens 10.8 / 12.0, 256, H 256 17.5 / 18.4; two, 64, H 640 (1 token) 7.2 / 7.6,
+//   H 768 7.8 / 7.6, 128, H 768 12.8 / 10.6, 256, H 1024 22.2 / 16.6; 64, H 2048, 1, 32, 1024 tokens 11.6 / 8.3, 13.9 / 9.8, 14.1 / 11.7
+//   (2048 tokens 14.7 / 15.9: at most 1024);
+//   up to 32 experts, two rounds and more: 8, H 4096, 1, 2, 4, 8, 32 tokens 5.8 / 6.0, 6.1 / 6.1, 6.5 / 6.3, 7.2 / 6.3, 9.0 / 6.9;
+//   4, 6 and 8 tokens 6.0 / 6.1, 6.6 / 6.3; 2, 8 and 16 tokens 6.1 / 6.2, 7.6 / 6.5; 24, H 1600, one token 6.4 / 6.1;
+//   one round: 16, H 2048, 1, 8, 16 tokens 5.2 / 5.4, 6.1 / 5.8, 7.0 / 6.1; 32, H 1024, 8, 16 tokens 5.8 / 6.1, 6.5 / 6.5; 8, H 256, 9
+//   tokens 5.0 / 4.7, H 128 4.1 / 4.7.
 constexpr int kGatePartsMaxTokens = 1024;
-inline bool gate_in_parts(int N, int E, int H) { return N <= kGatePartsMaxTokens && (N > 8 || (long)E * H >= 65536); }
+inline bool gate_in_parts(int N, int E, int H) {
+    if (N > kGatePartsMaxTokens) return false;
+    if (E > 32) return H > 512 && (long)E * H >= 49152;
+    return H > (E > 16 ? 1024 : 2048) ? N + E > 9 : N > 8 && H >= 256;
+}
 // Floats of scratch for that: per 16 tokens and 16 experts, 8 partial tiles of 256.
 inline size_t gate_parts_floats(int max_tokens, int E) {
     const size_t n = (size_t)(max_tokens < kGatePartsMaxTokens ? max_tokens : kGatePartsMaxTokens);

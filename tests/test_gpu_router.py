@@ -78,16 +78,17 @@ def test_rounds_and_ranks_choose_alike(E):
                 _check(logits, idx, w, k)
 
 
-@pytest.mark.parametrize("E,k,H", [(8, 2, 64), (8, 2, 8192), (16, 4, 4096), (17, 3, 320), (64, 8, 1088), (100, 5, 704), (256, 6, 512)])
+@pytest.mark.parametrize("E,k,H", [(8, 2, 64), (8, 2, 8192), (16, 4, 4096), (17, 3, 320), (64, 8, 1088), (100, 5, 704), (256, 6, 512),
+                                   (256, 6, 576), (24, 3, 1088), (4, 2, 2112)])
 def test_two_launches_give_the_bits_of_one(E, k, H):
-    """moe_route deals the gate GEMM of up to 1024 tokens to workgroups per K range; moe_route_noalloc never does."""
+    """moe_route deals the gate GEMM of up to 1024 tokens to workgroups per K range where that is faster; moe_route_noalloc never does."""
     g = torch.Generator(device=DEV)
     g.manual_seed(E + H)
     Wg = (torch.randn((H, E), generator=g, device=DEV) * H ** -0.5).bfloat16()
     bias = torch.randn(E, generator=g, device=DEV)
     dummy = torch.empty(64, dtype=torch.bfloat16, device=DEV)
     w = q.Context.weights(Wg, dummy, dummy, dummy)
-    for N in (1, 8, 9, 16, 17, 1023, 1024, 1025):
+    for N in (1, 2, 5, 6, 8, 9, 16, 17, 1023, 1024, 1025):
         x = torch.randn((N, H), generator=g, device=DEV).bfloat16()
         ctx = q.Context(E, k, H, 64, q.MOE_BF16, 16, N, device=DEV)
         ctx.route(x, w, bias)
