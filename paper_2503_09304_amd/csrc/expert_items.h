@@ -10,7 +10,7 @@
 // XCD, and what is left after the last whole round in 8 equal parts: every XCD gets the same number of
 // items and, the groups being sorted longest first, a like mix of long and short ones.
 //
-// Against packets of 4 segments x 8 column tiles dealt out whether full or not (14 half-empty packets
+// Against packets of 4 segments x 8 column tiles dealt out whether full or not, both with the kernels on 32x32x16 MFMAs (14 half-empty packets
 // are 32 workgroups on six XCDs and 16 on two; with 11 column tiles the full packets all fall on even
 // XCDs): one token on 2 of 8 experts, H 4096, F 14336: gate-up 92 -> 73 us, layer 190 -> 171 us; 32 tokens
 // on 64 experts, H 2048, F 1408: 90 -> 74 us, 170 -> 154 us; 8192 tokens on the same 1.29 -> 1.25 ms.  Where the
@@ -111,19 +111,19 @@ inline bool items_stream(const Seg *segs, int n) {
 // Returns true if the launch deals its groups to the XCDs: segments xcd[x] .. xcd[x+1] - 1 are XCD x's alone.
 // With the common list all XCDs work on the same expert at a time; where an expert has few segments, an XCD that
 // keeps to its own experts fetches fewer tokens for the same columns, if the shares (their cost in token tiles, the
-// largest over the mean) come out even.  Us a layer with the list / gate-up dealt out / down dealt out / both, top-2
-// of 8 experts, H 4096, F 14336 unless stated:
-//   32 experts, top-4, H 2048, F 1536, 4000 tokens (share 1.01) 397 / 391 / 393 / 389, 4-bit weights
-//   365 / 356 / 359 / 349; 64 experts, top-8, H 2048, F 1408, 4-bit, 3000 tokens, skewed 503 / 497 / 496 / 489:
-//   dealt out up to 1.02;
-//   two segments per expert: 1100 tokens (1.10) 931 / 918 / 928 / 915, 1300 tokens (1.02) 1013 / 984 / 1013 / 987,
-//   1531 tokens (1.05) 1106 / 1095 / 1106 / 1089, enqueued 1156 / 1144 / 1154 / 1140: dealt out up to 1.10, except
-//   for 4-bit weights (1531 tokens 896 / 907 / 900 / 911);
-//   2048 tokens, two or three segments (1.03): 1553 / 1580 / 1464 / 1472: the down projection's 320 items are 1.25
-//   rounds of the chip, and the list's last quarter takes as long as a round: dealt out below two rounds up to 1.10;
-//   with 4 K ranges, 5 rounds, 1481 / 1498 / 1497 / 1508: the list.
-// Uneven shares lose: 1300 tokens, skewed (2.5) 1026 with the list / 1714.  So do more segments per expert, even
-// shares or not: 2500 tokens (3 segments, 1.05) 1742 / 1766, 3584 tokens, 4-bit (4 segments, 1.02) 1943 / 1966.
+// largest over the mean) come out even.  Us a layer (gate-up + down) with the list / dealt out, top-2 of 8 experts, H 4096,
+// F 14336 unless stated:
+//   32 experts, top-4, H 2048, F 1536, 4000 tokens (share 1.01) 388 (203 + 143) / 367 (198 + 131), 4-bit weights 335 (175 + 114) /
+//   324 (168 + 112); 64 experts, top-8, H 2048, F 1408, 4-bit, 3000 tokens, skewed 461 (252 + 155) / 446 (250 + 143): dealt
+//   out up to 1.02;
+//   two segments per expert: 1100 tokens (1.10) 884 (531 + 350) / 857 (500 + 343), 1300 tokens (1.02) 940 (607 + 321) / 921 (584 +
+//   319), 1531 tokens (1.05) 1047 (684 + 356) / 1027 (651 + 359), enqueued 1121 (684 + 384) / 1091 (660 + 374): dealt out up to
+//   1.10, except for 4-bit weights (1531 tokens 837 (561 + 281) / 846 (572 + 284));
+//   2048 tokens, two or three segments (1.03), down projection 604 / 547: its 320 items are 1.25 rounds of the chip, and
+//   the list's last quarter takes as long as a round: dealt out below two rounds up to 1.10; gate-up, 7 rounds, 824 / 873, and
+//   with 4 K ranges, 5 rounds, 455 / 485: the list.
+// Uneven shares lose: 1300 tokens, skewed (2.5) 975 with the list / 1631.  So do more segments per expert, even
+// shares or not: 2500 tokens (3 segments, 1.05) 1624 / 1667, 3584 tokens, 4-bit (4 segments, 1.02) 1812 / 1826.
 inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool four_bit, ItemSeg *out, uint32_t (&xcd)[kXcds + 1]) {
     struct Group { int first, count, rows; };
     std::vector<Seg> s(segs, segs + n);

@@ -124,13 +124,16 @@ static long cu_count() {
 
 // Columns per wave of a gate-up launch.  A workgroup stays on its CU for the whole of K, so a launch
 // costs whole rounds of the chip's CUs, and a weight-streaming launch moves bytes in proportion to
-// rounds x columns per workgroup.  Narrower waves (28 .. 16 columns on the 32-wide MFMA; the idle MFMA
-// rows cost nothing where the stream is the bound) are taken when they make the last round full:
+// rounds x columns per workgroup.  Narrower waves (28 .. 16 columns; a wave's 32 MFMA rows stay, those
+// beyond its columns repeat its last one and are dropped) are taken when they make the last round full:
 // 8 experts x 14336 columns are 896 workgroups of 128 columns = 3.5 rounds of 256 CUs, but exactly 4
-// rounds of 112 columns (decode gate-up 0.321 -> 0.293 ms).  Only segments of at most 3 token tiles
-// are bound by the stream alone: from 4 tiles on an iteration takes as long for 28 columns as for 32,
-// launches whose segments share weights are MFMA-bound, and with 4-bit weights an iteration's
-// conversions, not its bytes, set the pace (decode gate-up 0.109 -> 0.112 ms); those keep 32.
+// rounds of 112.  Gate-up us with 32 / the rule's columns, top-2 of 8 experts, H 4096, F 14336 unless
+// stated: 2 tokens 129 / 112 (24), 8 tokens 299 / 287 (28), 64 tokens 305 / 299 (28), 300 tokens, 3 tiles of
+// 32 rows an expert, 318 / 302 (28); 32 tokens on 64 experts, skewed, H 2048, F 1408, 71.6 / 64.0 (24).  Not:
+// 4-bit weights, whose workgroups share a CU and are not bound by bytes (28 columns: 64 tokens, skewed 84 ->
+// 94, even 86.6 -> 87.1; only 8 tokens gain, 83.7 -> 76.5); launches of a single round, with nothing to even out (one token
+// 77.2, 76.5 with 28 columns; on 64 experts, 88 of the 256 CUs, 28.0 and 22.8 with 16); more than 3 tiles, a line
+// drawn for MFMAs of 32 rows (400 tokens, 4 tiles 327, with 28 columns 314); launches whose segments share weights, which are MFMA-bound.
 static int gate_up_wave_columns(bool stream, int wfmt, int tiles, int nseg, int F) {
     if (!stream || tiles > 3 || wfmt == bf16k::WF_MXFP4) return 32;
     const long cus = cu_count();
@@ -192,9 +195,10 @@ void launch_experts_bf16(const ExpertArgs &a, const KArgs &gu_in, const KArgs &d
         b.plane = a.plane;
         b.k.dst = a.partial;
     }
-    // Streaming launches of at most 32 rows a segment in 128 columns a workgroup where that takes fewer whole rounds of the CUs.  Us, 256 /
-    // 128 columns (workgroups): one token on 8 experts (128 / 256) 46.7 / 39.7, 32 tokens on 64 experts, skewed (304 / 608) 47.4 /
-    // 42.7; not: two tokens on 8 experts (192 / 384) 56.3 / 60.6, 8 on 64 (about 184 / 368) 26.3 / 28.8, 32 on 64 (504 / 1008)
+    // Streaming launches of at most 32 rows a segment in 128 columns a workgroup, where the twice as many workgroups take less than twice
+    // the whole rounds of the CUs (a round of half the columns takes about half the time).  Us, 256 / 128 columns (workgroups):
+    // one token on 8 experts (128 / 256) 46.7 / 39.7, 32 tokens on 64 experts, skewed (304 / 608: 2 rounds / 3) 47.4 / 42.7; not:
+    // two tokens on 8 experts (192 / 384) 56.3 / 60.6, 8 on 64 (about 184 / 368) 26.3 / 28.8, 32 on 64 (504 / 1008)
     // 59.1 / 59.7, 16 on 8, 4-bit (512 / 1024) 40.5 / 42.7.  Stoppable launches count workgroups of 256 columns.
     if (stream && tiles == 1 && a.go == nullptr) {
         auto rounds = [&](int cols) { return ((long)n * ((a.H + cols - 1) / cols) * b.ksplit + cu_count() - 1) / cu_count(); };

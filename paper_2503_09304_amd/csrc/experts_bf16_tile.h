@@ -17,7 +17,7 @@
 // them, so what counts is energy per flop: on random operands a loop of nothing but MFMAs sustains 2.00-2.06
 // PFLOP/s with 16x16x32 and 1.79-1.82 with 32x32x16.  Fragments of 16 tokens also leave less padding than tiles of 32.  Against
 // the same kernel on 32x32x16 (us, gate-up / down): 3584 tokens on 8 experts, H 4096, F 14336 1353 / 711 and 1255 / 682,
-// with 4-bit weights 1237 / 612 and 1173 / 592; 8192 tokens on 64 experts, H 2048, F 1408 657 / 422 and 613 / 401; 512
+// with 4-bit weights 1329 / 628 and 1229 / 579; 8192 tokens on 64 experts, H 2048, F 1408 657 / 422 and 613 / 401; 512
 // tokens on 8 experts with row-major weights, where a lane's rows now come 64 contiguous bytes at a time, 816 / 382 and 510 / 256.
 //
 // Pipeline of one K-iteration (64 k), prefetch distance D: issue the global loads of the token
@@ -138,9 +138,9 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     constexpr int STAGE = ROWS * 128;      // bytes of one LDS stage: 64 bf16 per row
     // The variants of more than 64 rows keep three token-tile stages, write tile it+2 during
     // iteration it, and so may read the first fragments of tile it+1 before the iteration's barrier;
-    // the LDS latency after the barrier disappears from the MFMA stream (measured on 32x32x16 tiles against the two-stage
-    // form: 256 rows -1.7 % on the 3584-token prefill; 128 to 160 rows gate-up -1.2 % on the 512-token batch).
-    // Below, an iteration is bound by the weight stream alone.
+    // the LDS latency after the barrier disappears from the MFMA stream.  Gate-up / down us with two stages everywhere, three
+    // from 129 rows on, three from 65 on, top-2 of 8 experts, H 4096, F 14336: 3584 tokens 1354 / 706, 1339 / 702, 1332 / 696; 512 tokens
+    // 337 / 163, 333 / 161, 331 / 159; 350 tokens all alike.  Below, an iteration is bound by the weight stream alone.
     constexpr bool P3 = T >= kP3MinT;
     // Output columns per wave.  Gate-up: 32, or fewer (p.cw, a multiple of 4) on launches whose
     // workgroup count would otherwise end in a partly filled round of the chip; the wave's MFMA rows
@@ -537,7 +537,9 @@ __global__ __launch_bounds__(256) void expert_bf16(const BArgs b) {
     const long plane = b.plane;
     // Prefetch distance of the weights: 2 iterations for the three-stage variants (their loop is unrolled by
     // a multiple of 3) and up to 64 rows, 3 up to 32 rows; 4-bit iterations are short and their codes take few registers:
-    // 5 (64 tokens on 8 experts, 2 K ranges, down projection 71 -> 55 us against 2).
+    // 5 (top-2 of 8 experts, H 4096, F 14336, 2 K ranges, down projection with 2 / 3 / 5: 8 tokens 64 / 47 / 42 us, 64 tokens,
+    // skewed, 87 / 59 / 56; the layer after 5 ms of idle, its code cold, with 3 / 5: 8 tokens 169 / 165, one token 85 / 80.  K loops
+    // of up to 20 iterations gain 2 to 4 % of a launch with 3 where every workgroup has a CU to itself, lose as much where not).
 #define QMOE_TILE(n, d) else if (2 * TCAP >= n && nf >= n) expert_tile<(2 * TCAP >= n ? n : 1), GATEUP, WF, STREAM, d>(k, un, ct, kq, ksplit, plane, lds)
     constexpr int D1 = WF == WF_MXFP4 ? 5 : 3, D2 = WF == WF_MXFP4 ? 5 : 2;
     if (false) {}
