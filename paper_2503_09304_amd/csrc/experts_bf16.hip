@@ -113,12 +113,10 @@ hipError_t launch_pack(const void *src, void *dst, int E, int R, int K, hipStrea
 }
 
 static long cu_count() {
-    static int cus = 0;
-    if (cus == 0) {
+    static const long cus = [] {       // (once, by whichever thread launches first)
         int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
-        cus = v;
-    }
+        return hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1 ? 256 : v;
+    }();
     return cus;
 }
 
