@@ -57,3 +57,5 @@ def test_long_rows(fmt, H, F, N, cols, monkeypatch):
         g, u = (product(x, v[0, f: f + (1 << 22)]) for v in W[:2])
         assert close(act[:, f: f + (1 << 22)], g / (1 + torch.exp(-g)) * u, H, 2.0 ** -8)
     assert close(out, product(act, W[2][0]), F, 0.0)
+    del x, Wg, W, w, ctx, act, out, g, u
+    torch.cuda.empty_cache()
