@@ -302,8 +302,13 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
 
     // One K-iteration is 2*NF slots, written out in the order in which they shall issue (nothing moves across a slot's
     // end): slot s has the 4 MFMAs of one token fragment (step j = s / NF, fragment s % NF), one LDS fragment read (RF - 1
-    // slots before its use), and its share of the T + 8 global loads (first half of the slots, so the texture path works
-    // under the MFMAs instead of in a burst) and of the T LDS writes of the next token tile (last slots).
+    // slots before its use), and its share of the T + 8 global loads and of the T LDS writes of the next token tile (last slots).
+    // The loads of the four waves keep the texture path busy for about 16 clocks each, 960 of an iteration's 2048 clocks of MFMA with
+    // 256 rows: dealt out over the first half of the slots they queue, and a wave that cannot issue its load issues no MFMA either.
+    // With more than 64 rows and bf16 weights they are dealt out over all slots: down projection us with the first half / all, top-2 of
+    // 8 experts, H 4096, F 14336: 3584 tokens 694 / 640, 1531 tokens in 4 K ranges 355 / 335, 700 tokens 188 / 184; 8192 tokens on 64 experts
+    // 410 / 394; gate-up, at the clock that the power limit leaves, alike within 1 %.  4-bit weights have 4 loads where bf16 has 8, which makes the
+    // token pieces arrive too late for their LDS writes (3584 tokens, down 580 / 611); up to 64 rows the stream of weights is the bound.
     constexpr int SL = 2 * NF, RF = P3 ? 6 : (SL < 4 ? SL : 4);
     static_assert(!P3 || U * SL % RF == 0, "the ring of fragments goes on from iteration to iteration");
     bf16x8 af[RF];
@@ -346,8 +351,8 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
             mma<m == NQ * SL - 1>(acc[f * NQ + q], b_reg[S * 2 * NQ + j * NQ + q], af[(ring + s) % RF]);
             if constexpr (q == 0 && p < SL) read_af(stage, std::integral_constant<int, p>{}, std::integral_constant<int, (ring + p) % RF>{});
             else if constexpr (q == 0 && P3) read_af(next, std::integral_constant<int, p - SL>{}, std::integral_constant<int, (ring + p) % RF>{});
-            constexpr int NV = T + BL, HALF = NQ * SL / 2, V0 = m * NV / HALF, V1 = (m + 1) * NV / HALF;
-            if constexpr (m < HALF) {
+            constexpr int NV = T + BL, SPAN = P3 && !MX ? NQ * SL : NQ * SL / 2, V0 = m * NV / SPAN, V1 = (m + 1) * NV / SPAN;
+            if constexpr (m < SPAN) {
                 static_for<V1 - V0>([&](auto vc) {
                     constexpr int v = V0 + decltype(vc)::value;
                     if constexpr (v < T) load_a(it + (P3 ? 2 : DA), std::integral_constant<int, P3 ? 0 : (i + DA) % NA>{}, std::integral_constant<int, v>{});
