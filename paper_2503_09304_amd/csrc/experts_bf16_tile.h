@@ -301,10 +301,10 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     };
 
     // One K-iteration is 2*NF slots, written out in the order in which they shall issue (nothing moves across a slot's
-    // end): slot s has the 4 MFMAs of one token fragment (step j = s / NF, fragment s % NF; its (matrix, row half) pairs in turn
+    // end): slot s has the 4 MFMAs of one token fragment (step j = s / NF, fragment s % NF; with CHAIN two slots have the 8 of one; its (matrix, row half) pairs in turn
     // upwards and downwards, so that one operand at a time changes between MFMAs: fewer bits toggle, and the clock of the power-limited
     // launches rises; a loop of nothing but MFMAs on random operands 2.06 -> 2.10 PFLOP/s, gate-up of 3584 tokens on 8 experts 1367 -> 1351 us, with
-    // 4-bit weights 1251 -> 1238, 8192 tokens on 64 experts 674 -> 667), one LDS fragment read (RF - 1
+    // 4-bit weights 1251 -> 1238, 8192 tokens on 64 experts 674 -> 667), one LDS fragment read (LA
     // slots before its use), and its share of the T + 8 global loads and of the T LDS writes of the next token tile (last slots).
     // The loads of the four waves keep the texture path busy for about 16 clocks each, 960 of an iteration's 2048 clocks of MFMA with
     // 256 rows: dealt out over the first half of the slots they queue, and a wave that cannot issue its load issues no MFMA either.
@@ -312,17 +312,25 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     // 8 experts, H 4096, F 14336: 3584 tokens 694 / 640, 1531 tokens in 4 K ranges 355 / 335, 700 tokens 188 / 184; 8192 tokens on 64 experts
     // 410 / 394; gate-up, at the clock that the power limit leaves, alike within 1 %.  4-bit weights have 4 loads where bf16 has 8, which makes the
     // token pieces arrive too late for their LDS writes (3584 tokens, down 580 / 611); up to 64 rows the stream of weights is the bound.
-    constexpr int SL = 2 * NF, RF = P3 ? 6 : (SL < 4 ? SL : 4);
+    // CHAIN: the two steps of an accumulator stand back to back (fragment by fragment, step innermost), so that the matrix unit hands
+    // the sum on instead of writing and reading it: a loop of nothing but MFMAs on random operands 2.12 -> 2.21 PFLOP/s (two steps
+    // with another accumulator's in between: no gain; four in a row 2.25, but that takes two iterations' operands at a time).
+    // 3584 tokens on 8 experts, layer 1912 -> 1890 us, 8192 tokens on 64 experts 1158 -> 1143.  It wants the operands of step 1 half an
+    // iteration earlier, so not where the weight stream is the bound (128 tokens on 8 experts, 4 K ranges 540 -> 544 us), and not for 4-bit
+    // weights, whose operands of step 1 are made during step 0.  An accumulator's sums run in the same order either way.
+    constexpr bool CHAIN = !MX && P3 && !STREAM;
+    constexpr int SL = 2 * NF, RF = CHAIN ? 2 * (P3 ? 3 : (NF < 3 ? NF : 3)) : P3 ? 6 : (SL < 4 ? SL : 4);
+    constexpr int LA = CHAIN ? 2 * (NF < 2 ? NF : 2) : RF - 1;     // slots read ahead
     static_assert(!P3 || U * SL % RF == 0, "the ring of fragments goes on from iteration to iteration");
     bf16x8 af[RF];
     const char *a_at[2];                    // this lane's piece of step 0 and 1 in a token row
 #pragma unroll
     for (int j = 0; j < 2; ++j) a_at[j] = lds + lr * 128 + ((j * 4 + (lg & 1) * 2 + (lg >> 1)) ^ swz(lr)) * 16;
     auto read_af = [&](int stage, auto pc, auto rc) {         // fragment of slot p into place r of the ring
-        constexpr int p = decltype(pc)::value, j = p / NF, f = p % NF;
+        constexpr int p = decltype(pc)::value, j = CHAIN ? p % 2 : p / NF, f = CHAIN ? p / 2 : p % NF;
         af[decltype(rc)::value] = *reinterpret_cast<const bf16x8 *>(a_at[j] + stage * STAGE + f * 2048);
     };
-    auto read_first = [&](int stage) { static_for<RF - 1>([&](auto pc) { read_af(stage, pc, pc); }); };
+    auto read_first = [&](int stage) { static_for<LA>([&](auto pc) { read_af(stage, pc, pc); }); };
     // Iteration `it`, position i = it mod U in the unrolled loop: request the operands of it+D (token
     // pieces first: the wait for them must not cover the weight loads), run the MFMAs of it, move the
     // token pieces of it+1 (requested earlier) into the other LDS stage.  Loads complete in issue
@@ -349,11 +357,14 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
             asm volatile("s_nop 1");               // see mma
         }
         static_for<NQ * SL>([&](auto mc) {
-            constexpr int m = decltype(mc)::value, s = m / NQ, q = m % NQ, j = s / NF, f = s % NF, p = s + RF - 1, qz = f % 2 ? NQ - 1 - q : q;
+            constexpr int m = decltype(mc)::value, s = m / NQ, q = m % NQ;
+            constexpr int j = CHAIN ? m % 2 : s / NF, f = CHAIN ? s / 2 : s % NF, qu = CHAIN ? m % (2 * NQ) / 2 : q, qz = f % 2 ? NQ - 1 - qu : qu;
             constexpr int ring = P3 ? i * SL : 0;              // slots before this iteration
-            mma<m == NQ * SL - 1>(acc[f * NQ + qz], b_reg[S * 2 * NQ + j * NQ + qz], af[(ring + s) % RF]);
-            if constexpr (q == 0 && p < SL) read_af(stage, std::integral_constant<int, p>{}, std::integral_constant<int, (ring + p) % RF>{});
-            else if constexpr (q == 0 && P3) read_af(next, std::integral_constant<int, p - SL>{}, std::integral_constant<int, (ring + p) % RF>{});
+            mma<m == NQ * SL - 1>(acc[f * NQ + qz], b_reg[S * 2 * NQ + j * NQ + qz], af[(ring + (CHAIN ? 2 * f + j : s)) % RF]);
+            constexpr bool reads = CHAIN ? m % (2 * NQ) < 2 : q == 0;
+            constexpr int p = (CHAIN ? 2 * f + m % 2 : s) + LA;
+            if constexpr (reads && p < SL) read_af(stage, std::integral_constant<int, p>{}, std::integral_constant<int, (ring + p) % RF>{});
+            else if constexpr (reads && P3) read_af(next, std::integral_constant<int, p - SL>{}, std::integral_constant<int, (ring + p) % RF>{});
             constexpr int NV = T + BL, SPAN = P3 && !MX ? NQ * SL : NQ * SL / 2, V0 = m * NV / SPAN, V1 = (m + 1) * NV / SPAN;
             if constexpr (m < SPAN) {
                 static_for<V1 - V0>([&](auto vc) {
