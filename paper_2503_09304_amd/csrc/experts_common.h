@@ -23,7 +23,7 @@ struct KArgs {
     // Launches of an enqueued, stoppable sequence (nullptr / 0 otherwise): see wg_may_run.
     int32_t *go;              // [device] gate word of the launch: 0 = the sequence was stopped (before this launch, or by a
                               // workgroup of it that saw the stop word: the ones that start later leave at once)
-    const int32_t *stop;      // [host memory mapped into the device] the context's stop word
+    const int32_t *stop;      // [host memory mapped into the device] the context's stop word, kStopCopies of it
     int32_t *cnt_self;        // [device] workgroups of this kernel that ran, per row range, indexed by its first sorted row
     const int32_t *cnt_need;  // down projection: the gate-up kernel's counters (the activation rows must be complete)
     int need;                 // gate-up workgroups per 32-row tile (fp32) or per row range (bf16) that make them complete
@@ -40,11 +40,14 @@ struct KArgs {
 // overlaps with the loads of their prologue: wg_probe issues the reads at the start of the
 // workgroup, wg_decide turns them into the decision in front of the prologue's barrier, and the
 // workgroup leaves behind that barrier if *s_run is 0 (nothing has been stored by then).
+__device__ __forceinline__ int wg_stop(const KArgs &p) {
+    return __hip_atomic_load(p.stop + (blockIdx.x % kStopCopies) * kStopStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 struct WgProbe { int stop, have; };
 __device__ __forceinline__ WgProbe wg_probe(const KArgs &p, int row0) {
     WgProbe v{0, 0};
     if (p.go != nullptr && threadIdx.x == 0) {
-        v.stop = __hip_atomic_load(p.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        v.stop = wg_stop(p);
         v.have = p.cnt_need != nullptr ? p.cnt_need[row0] : 0;
     }
     return v;
@@ -62,7 +65,7 @@ __device__ __forceinline__ bool wg_may_run(const KArgs &p, int row0, int tiles, 
     if (p.go == nullptr) return true;
     if (threadIdx.x == 0) {
         bool ok = __hip_atomic_load(p.go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-        if (ok && __hip_atomic_load(p.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0) {
+        if (ok && wg_stop(p) != 0) {
             __hip_atomic_store(p.go, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // close the launch for the rest
             ok = false;
         }

@@ -12,6 +12,7 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -149,10 +150,12 @@ struct moe_ctx {
     std::vector<uint32_t> plan;                // the units of that sequence
     std::vector<qmoe::Seg> plan_ranges;        // the row ranges its launches worked on, in the order of the device's report
     std::vector<int32_t> cnt;
-    int32_t *pinned;  // 2E counts, unit count, sequence word, stop word, a spare word, then one completion flag per row
-                      // range of an enqueued sequence (at most max_units): pinned host memory mapped into the device
+    int32_t *pinned;  // 2E counts, unit count, sequence word, two spare words, then one completion flag per row range of an
+                      // enqueued sequence (at most max_units), then the copies of the stop word (stop_word): pinned host
+                      // memory mapped into the device
                       // (allocated at first route); the permutation and report kernels write it directly
     int32_t *pinned_dev;   // the device's address of the same memory
+    std::mutex stop_mu;    // held while the copies of the stop word are written
     int32_t seq;           // sequence number of the last report asked for
     int spin_ms;           // how long moe_permute polls for the report before it waits for the stream
     int wave_cols;         // 0: the launch policy picks the gate-up wave width; else forced (tests)
@@ -165,6 +168,17 @@ struct moe_ctx {
 namespace {
 template <class T>
 T *at(moe_ctx *c, size_t off) { return reinterpret_cast<T *>(c->ws + off); }
+
+// First copy of the stop word in the pinned buffer, on a line of its own.
+size_t stop_word(const moe_ctx *c) {
+    const size_t used = 2 * (size_t)c->cfg.E + 4 + c->lay.max_units;       // counts, unit count, sequence word, spare, range flags
+    return (used + qmoe::kStopStride - 1) / qmoe::kStopStride * qmoe::kStopStride;
+}
+void set_stop(moe_ctx *c, int32_t v) {
+    std::lock_guard<std::mutex> lk(c->stop_mu);      // a stop from another thread leaves no mixture with a clear
+    for (int i = 0; i < qmoe::kStopCopies; ++i) __atomic_store_n(c->pinned + stop_word(c) + (size_t)i * qmoe::kStopStride, v, __ATOMIC_RELAXED);
+    std::atomic_thread_fence(std::memory_order_seq_cst);
+}
 }  // namespace
 
 extern "C" {
@@ -304,7 +318,7 @@ int32_t moe_route(moe_ctx *ctx, const void *x, int32_t n_tokens, const moe_weigh
     if (w->layout == MOE_W_MXFP4 && (!w->S1 || !w->S3 || !w->S2)) return fail(MOE_E_ARG, "moe_route: 4-bit weights need the scale pointers S1, S3, S2");
     if (n_tokens > 0 && !x) return fail(MOE_E_ARG, "moe_route: null x");
     if (!ctx->pinned) {
-        const size_t words = 2 * (size_t)ctx->cfg.E + 4 + ctx->lay.max_units;   // counts, unit count, sequence word, stop word, spare, range flags
+        const size_t words = stop_word(ctx) + (size_t)qmoe::kStopCopies * qmoe::kStopStride;
         hipError_t e = hipHostMalloc((void **)&ctx->pinned, words * sizeof(int32_t), hipHostMallocMapped | hipHostMallocCoherent);
         if (e != hipSuccess) { ctx->pinned = nullptr; return hip_fail(e, "moe_route: hipHostMalloc"); }
         e = hipHostGetDevicePointer((void **)&ctx->pinned_dev, ctx->pinned, 0);
@@ -427,7 +441,7 @@ static int32_t launch_unit_list(moe_ctx *ctx, const void *x, const moe_weights *
     qmoe::ExpertArgs a{};
     a.go = go;
     if (go != nullptr) {
-        a.stop = ctx->pinned_dev + 2 * ctx->cfg.E + 2;
+        a.stop = ctx->pinned_dev + stop_word(ctx);
         a.cnt_gu = at<int32_t>(ctx, ctx->lay.prog);
         a.cnt_dn = a.cnt_gu + (size_t)ctx->N * ctx->cfg.k;
     }
@@ -589,8 +603,8 @@ int32_t moe_expert_enqueue(moe_ctx *ctx, const void *x, const moe_weights *w, ui
     // No kernel of an earlier sequence is left (it was collected): clear the range flags the report
     // kernel will set, so that a sequence cut short by an error reports nothing, and the stop word.
     memset(ctx->pinned + 2 * E + 4, 0, (size_t)ctx->lay.max_units * sizeof(int32_t));
-    __atomic_store_n(ctx->pinned + 2 * E + 2, 0, __ATOMIC_SEQ_CST);
-    const int32_t *stop_dev = ctx->pinned_dev + 2 * E + 2;
+    set_stop(ctx, 0);
+    const int32_t *stop_dev = ctx->pinned_dev + stop_word(ctx);
     int32_t *go = at<int32_t>(ctx, ctx->lay.go);
     ctx->plan.clear();
     ctx->plan_ranges.clear();
@@ -618,7 +632,7 @@ int32_t moe_expert_enqueue(moe_ctx *ctx, const void *x, const moe_weights *w, ui
 int32_t moe_expert_stop(moe_ctx *ctx) {
     if (!ctx) return fail(MOE_E_ARG, "moe_expert_stop: null context");
     if (!ctx->pinned) return fail(MOE_E_STATE, "moe_expert_stop: nothing has been routed on this context");
-    __atomic_store_n(ctx->pinned + 2 * ctx->cfg.E + 2, 1, __ATOMIC_SEQ_CST);
+    set_stop(ctx, 1);
     return MOE_OK;
 }
 
@@ -650,7 +664,7 @@ int32_t moe_expert_collect(moe_ctx *ctx, moe_cursor *cursor, void *stream) {
         ctx->plan.clear();
         ctx->plan_ranges.clear();
         ctx->pending = false;
-        __atomic_store_n(ctx->pinned + 2 * ctx->cfg.E + 2, 0, __ATOMIC_SEQ_CST);
+        set_stop(ctx, 0);
     }
     cursor->next_unit = ctx->next_unit;
     cursor->n_units = ctx->n_units;

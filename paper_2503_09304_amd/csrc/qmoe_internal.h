@@ -119,9 +119,17 @@ struct ExpertArgs {
     long plane;                 // elements per plane
     // launches of an enqueued, stoppable sequence (all nullptr otherwise; see launch_gate, launch_report)
     int32_t *go;                // [device] gate word of this launch
-    const int32_t *stop;        // [host, mapped] the context's stop word
+    const int32_t *stop;        // [host, mapped] the context's stop word (kStopCopies of it)
     int32_t *cnt_gu, *cnt_dn;   // [device] workgroups that ran per row range (indexed by first sorted row): gate-up, down
 };
+
+// The stop word of a context is kept in copies on lines of their own, kStopStride words apart: reads of one word of host memory
+// are answered one after the other, about 0.06 us each.  All 256 workgroups that a round of a launch starts read it: 1.5 to 20 us with one
+// copy, half of them more than 8; 1.3 to 1.6 us with words of their own, and up to 16 readers of a word.  1531 tokens on 8 experts
+// enqueued: the starts of gate-up and down workgroups took 17 and 21 thousand clocks on average, one in ten more than 46 thousand,
+// where launches that cannot be stopped take 7 to 8 thousand; the layer 1021 -> 978 us, 8 smaller ones of 107 to 512 us
+// 1.07 to 1.52 times as fast.
+constexpr int kStopCopies = 64, kStopStride = 16;
 
 constexpr int kF32RowTile = 32, kF32ColTile = 32;   // rows and output columns of a workgroup of the fp32 expert kernels
 
