@@ -138,3 +138,32 @@ def test_narrow_down_projection(fmt, E, H, F, rows):
     assert torch.equal(outs[0], outs[1])
     for e in range(E):                                  # sorted order: expert by expert, tokens ascending
         assert error(outs[0][e * rows: (e + 1) * rows], x, W, e) <= bar("bf16", H, F)
+
+
+# one round of the CUs, in which the narrowest waves are taken; two rounds of 28 columns for 32 (8 experts x 36 or 42 workgroups),
+# row-major also beyond 96 rows; equal cost, where row-major of few rows goes to 16 columns
+@pytest.mark.parametrize("fmt,E,H,F,rows", [("packed", 3, 128, 512, 1), ("packed", 8, 64, 2176, 33), ("rowmajor", 3, 128, 192, 97), ("rowmajor", 8, 64, 4608, 129),
+                                            ("rowmajor", 8, 64, 4608, 256), ("packed", 8, 64, 4608, 96), ("rowmajor", 64, 64, 1408, 5)])
+def test_wave_columns_of_the_rule(fmt, E, H, F, rows, monkeypatch):
+    """Narrower gate-up waves than 32 columns, as the launch rule takes them, give the bits of 32 columns, and plain products."""
+    print("case", fmt, E, H, F, rows, flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows + F)
+    x, Wg = torch.randn((rows, H), generator=gen, device=DEV).bfloat16(), (torch.randn((H, E), generator=gen, device=DEV) * 0.02).bfloat16()
+    k = min(E, 32)
+    w, W, hold = make(fmt, Wg, E, H, F, gen)
+    prio = torch.zeros(rows, dtype=torch.uint8, device=DEV)
+    outs = []
+    for cols in (None, "32"):
+        if cols:
+            monkeypatch.setenv("QMOE_GATE_UP_WAVE_COLUMNS", cols)
+        ctx = q.Context(E, k, H, F, q.MOE_BF16, 256, rows, device=DEV)
+        ctx.route(x, w)
+        ctx.permute(prio)
+        assert ctx.expert_run(x, w) == q.MOE_DONE
+        outs.append((ctx.get("act").clone(), ctx.get("expert_out").clone()))
+        torch.cuda.synchronize()
+    assert torch.equal(outs[0][0].view(torch.int16), outs[1][0].view(torch.int16)) and torch.equal(outs[0][1], outs[1][1])
+    if k == E:
+        for e in range(E):                              # sorted order: expert by expert, tokens ascending
+            assert error(outs[0][1][e * rows: (e + 1) * rows], x, W, e) <= bar("bf16", H, F)
