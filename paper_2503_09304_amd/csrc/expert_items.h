@@ -177,6 +177,24 @@ inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool 
             return true;
         }
     }
+    // A workgroup of one of several segments is bound by the matrix units, one of an expert's only segment more by the stream of its
+    // weights.  Sorted by rows all of the latter came last, with the matrix units idle; now three quarters of them go out between the others
+    // and the rest make the end.  Us a layer sorted / mixed, Zipf-skewed: 4096 tokens on 64 experts, top-8, H 2048, F 1408 657 / 632, 6000
+    // tokens 884 / 874, 8192 tokens 1121 / 1124; 3000 tokens on 16 experts, top-2, F 4096 391 / 379; 4000 tokens on 32, top-4, F 2048
+    // 460 / 454; 1500 tokens on 8 experts, H 4096, F 14336 959 / 949.  With half of them between the others the first five 643, 868, 1124,
+    // 379, 464, with all of them 644, -, 1126, -, 459.  Least favourable of 14 drawn: 1085 tokens on 32, top-8, H 1664, F 3584 406 / 408.  4-bit weights, a quarter of the bytes, stay sorted (6000 tokens on 64 experts 793 / 796).
+    if (!stream && !four_bit) {
+        std::vector<Group> mixed;
+        const size_t heavy = (size_t)(std::find_if(groups.begin(), groups.end(), [](const Group &g) { return g.rows <= 256; }) - groups.begin());
+        long all[2] = {0, 0}, out_segs[2] = {0, 0};                 // segments of the groups before and from `heavy` on
+        for (size_t i = 0; i < groups.size(); ++i) all[i >= heavy] += groups[i].count;
+        for (size_t i = 0, j = heavy; i < heavy || j < groups.size();) {
+            const bool light = j < groups.size() && (i == heavy || 4 * (out_segs[1] + groups[j].count) * all[0] <= 3 * out_segs[0] * all[1]);
+            mixed.push_back(groups[light ? j++ : i++]);
+            out_segs[light] += mixed.back().count;
+        }
+        groups.swap(mixed);
+    }
     for (const Group &g : groups) place(g);
     return false;
 }
