@@ -37,8 +37,8 @@ struct KArgs {
 // row0: first sorted row of the row range; tiles: how many `need`-sized groups of gate-up workgroups
 // cover it.
 // The bf16 kernels split it in two so that the read of the host's stop word (a trip over the bus)
-// overlaps with the loads of their prologue: wg_probe issues the reads at the start of the
-// workgroup, wg_decide turns them into the decision in front of the prologue's barrier, and the
+// overlaps with the loads of their prologue: wg_probe issues the reads behind the loads that the first LDS stores
+// wait for, wg_decide turns them into the decision in front of the prologue's barrier, and the
 // workgroup leaves behind that barrier if *s_run is 0 (nothing has been stored by then).
 __device__ __forceinline__ int wg_stop(const KArgs &p) {
     return __hip_atomic_load(p.stop + (blockIdx.x % kStopCopies) * kStopStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
