@@ -186,8 +186,12 @@ __global__ __launch_bounds__(256) void perm_scatter(const int32_t *__restrict__ 
 
 // The whole sort in one workgroup, for batches of at most kPermFusedMax assignments (latency
 // matters more than parallelism there): LDS-atomic histogram, bucket scan and unit list, then the
-// blocks of 1024 assignments ranked one after the other with running per-bucket counters.
-constexpr int kPermFusedMax = 8192;
+// blocks of 1024 assignments ranked one after the other with running per-bucket counters, 2 to 3 us each.  Up to some
+// 4000 it ends before the host's launch of the expert kernels arrives, and two launches more only delay the report; beyond, that launch waits for it.
+// Layer us in one kernel / three: 1600 assignments, 64 experts 208 / 211; 2400, 32 experts 92.5 / 95.0 and 128 experts 142.6 / 144.9; 4000, 16 experts 90.8 /
+// 92.0; 4800, 64 experts 228.3 / 226.1; 6400, 64 experts 243.9 / 239.0; 7200, 32 experts 136.8 / 130.8; 8000, 16, 64 and 128 experts 118.1 / 112.5,
+// 251.8 / 244.7 and 169.5 / 161.3; 7168, 8 experts 1896 / 1895.
+constexpr int kPermFusedMax = 4096;
 
 __global__ __launch_bounds__(kPermBlock) void perm_fused(const int32_t *__restrict__ topk_idx, const uint8_t *__restrict__ prio,
                                                          int A, int k, int E, int C, int nbits, int32_t *__restrict__ cnt,

@@ -1,4 +1,4 @@
-"""The permutation in three kernels (more than 8192 assignments): bucket order, queue lengths and the unit list, the host's and
+"""The permutation in three kernels (more than 4096 assignments): bucket order, queue lengths and the unit list, the host's and
 the device's, against a stable sort, at the smallest such batches, a last block of one assignment, and one to 256 experts (2 to
 512 ranges of blocks per bucket); the same of the kernel for fewer."""
 import numpy as np
@@ -38,3 +38,9 @@ def test_three_kernels_sort_like_one(E, k, N):
         assert [tuple(u) for u in ctx.get("units").cpu().tolist()] == units
         at = ctx.get("counts").data_ptr() - ctx.ws.data_ptr() + 8 * E
         assert int(ctx.ws[at: at + 4].view(torch.int32)) == len(units)
+
+
+@pytest.mark.parametrize("E,k,N", [(1, 1, 4096), (1, 1, 4097), (256, 8, 512), (256, 3, 1366), (64, 1, 5121), (8, 2, 3584)])
+def test_either_side_of_4096_assignments(E, k, N):
+    """The line between the kernel for few assignments and the three for more."""
+    test_three_kernels_sort_like_one(E, k, N)
