@@ -248,8 +248,8 @@ int32_t moe_expert_run_units(moe_ctx *ctx, const void *x, const moe_weights *w, 
  * (Discussion, Sec. 6, paragraph on overlapping preemption with execution: named there as future work).
  * moe_expert_enqueue puts ALL units that have not run yet on the stream, as launches of
  * units_per_launch units each, and returns without waiting.  moe_expert_stop sets the context's stop
- * word (stores to host memory that is mapped into the device; they may come from another thread
- * than the one that enqueued).  Every workgroup of the sequence looks at that word when it starts:
+ * word (stores to host memory that is mapped into the device, without a lock; they may come from another thread
+ * than the one that enqueued, or from a signal handler).  Every workgroup of the sequence looks at that word when it starts:
  * once it is set, workgroups that have not started yet do nothing, so the sequence ends as soon as
  * the workgroups in flight have finished their tiles (a fraction of one unit's duration), whatever
  * units_per_launch is; the launches behind the stop are closed as a whole by a one-thread gate kernel

@@ -12,7 +12,6 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -155,7 +154,7 @@ struct moe_ctx {
                       // memory mapped into the device
                       // (allocated at first route); the permutation and report kernels write it directly
     int32_t *pinned_dev;   // the device's address of the same memory
-    std::mutex stop_mu;    // held while the copies of the stop word are written
+    int32_t stop_want;     // the value last asked for of the stop word (set_stop)
     int32_t seq;           // sequence number of the last report asked for
     int spin_ms;           // how long moe_permute polls for the report before it waits for the stream
     int wave_cols;         // 0: the launch policy picks the gate-up wave width; else forced (tests)
@@ -174,10 +173,18 @@ size_t stop_word(const moe_ctx *c) {
     const size_t used = 2 * (size_t)c->cfg.E + 4 + c->lay.max_units;       // counts, unit count, sequence word, spare, range flags
     return (used + qmoe::kStopStride - 1) / qmoe::kStopStride * qmoe::kStopStride;
 }
+// Sets every copy.  Takes no lock: a stop may come from another thread, or from a signal handler in the middle of a clear.
+// Whoever finds, behind its stores, that another value has been asked for meanwhile stores that one as well, so that the
+// copies are alike, and what was asked for last, once all calls have returned.
 void set_stop(moe_ctx *c, int32_t v) {
-    std::lock_guard<std::mutex> lk(c->stop_mu);      // a stop from another thread leaves no mixture with a clear
-    for (int i = 0; i < qmoe::kStopCopies; ++i) __atomic_store_n(c->pinned + stop_word(c) + (size_t)i * qmoe::kStopStride, v, __ATOMIC_RELAXED);
-    std::atomic_thread_fence(std::memory_order_seq_cst);
+    __atomic_store_n(&c->stop_want, v, __ATOMIC_SEQ_CST);
+    for (int32_t asked;; v = asked) {
+        std::atomic_thread_fence(std::memory_order_seq_cst);
+        for (int i = 0; i < qmoe::kStopCopies; ++i) __atomic_store_n(c->pinned + stop_word(c) + (size_t)i * qmoe::kStopStride, v, __ATOMIC_RELAXED);
+        std::atomic_thread_fence(std::memory_order_seq_cst);
+        asked = __atomic_load_n(&c->stop_want, __ATOMIC_SEQ_CST);
+        if (asked == v) return;
+    }
 }
 }  // namespace
 
@@ -276,6 +283,7 @@ int32_t moe_create(const moe_config *cfg, void *workspace, size_t workspace_byte
     c->pinned = nullptr;
     c->pinned_dev = nullptr;
     c->seq = 0;
+    c->stop_want = 0;
     c->spin_ms = kReportSpinMs;
     if (const char *v = getenv("QMOE_REPORT_SPIN_MS")) {      // for tests of the fall-back: 0 = do not poll at all
         const long ms = strtol(v, nullptr, 10);

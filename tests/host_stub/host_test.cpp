@@ -1,15 +1,22 @@
 // Host-logic test driver, built with -fsanitize=address,undefined against the recording stubs: the
 // context state machine, the unit planner, the segment builder of moe_expert_run, policy-chosen unit
 // order, the bookkeeping of an enqueued sequence (including: no other call, moe_destroy included,
-// while it is pending) and the scheduler's queues under a random trace.  Exits 0 when every check holds.
+// while it is pending), the copies of its stop word and the scheduler's queues under a random trace.  Exits 0 when every check holds.
+#include <pthread.h>
+#include <signal.h>
+
+#include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <random>
 #include <set>
+#include <thread>
 #include <vector>
 
 #include "qmoe.h"
+#include "qmoe_internal.h"
 #include "qsched.h"
 #include "stub_hooks.h"
 
@@ -233,6 +240,79 @@ static void test_enqueued_sequence_bookkeeping(int dtype) {
     CHECK(e.n_units == 0 && moe_expert_run(c.h, c.x, &c.w, 5, &e, nullptr) == MOE_DONE);
 }
 
+// How many of the copies of the stop word are set.
+static int stops_set() {
+    int n = 0;
+    for (int i = 0; i < qmoe::kStopCopies; ++i) n += stub_stop_words()[i * qmoe::kStopStride] != 0;
+    return n;
+}
+
+static void test_every_copy_of_the_stop_word() {
+    Ctx c(3, 2, 128, 256, MOE_BF16, 64, 1024);
+    moe_cursor cur = start(c, {10, 300, 0, 200, 64, 26});
+    stub_complete_first(0);                          // nothing runs: the sequence can be enqueued again and again
+    CHECK(moe_expert_enqueue(c.h, c.x, &c.w, 4, nullptr) == MOE_OK && stops_set() == 0);
+    CHECK(moe_expert_stop(c.h) == MOE_OK && stops_set() == qmoe::kStopCopies);
+    CHECK(moe_expert_collect(c.h, &cur, nullptr) == MOE_OK && stops_set() == 0);
+    CHECK(moe_expert_stop(c.h) == MOE_OK && stops_set() == qmoe::kStopCopies);
+    CHECK(moe_expert_enqueue(c.h, c.x, &c.w, 4, nullptr) == MOE_OK && stops_set() == 0);
+    CHECK(moe_expert_collect(c.h, &cur, nullptr) == MOE_OK);
+    stub_complete_first(-1);
+}
+
+// moe_expert_stop from a signal handler that interrupts the calls that clear the stop words, and from another thread beside
+// them: nobody waits for ever, and the copies are alike once all calls have returned.
+static moe_ctx *g_stop_ctx;
+static std::atomic<int> g_stops{0};
+static void stop_handler(int) {
+    moe_expert_stop(g_stop_ctx);
+    g_stops.fetch_add(1);
+}
+static void test_stops_beside_clears() {
+    Ctx c(3, 2, 128, 256, MOE_BF16, 64, 1024);
+    moe_cursor cur = start(c, {10, 300, 0, 200, 64, 26});
+    stub_complete_first(0);
+    CHECK(moe_expert_enqueue(c.h, c.x, &c.w, 4, nullptr) == MOE_OK && moe_expert_collect(c.h, &cur, nullptr) == MOE_OK);
+    std::atomic<bool> over{false};
+    std::thread watch([&] {
+        for (int i = 0; i < 400 && !over; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(100));
+        if (!over) { printf("FAILED: a stop and a clear wait for one another\n"); fflush(stdout); _Exit(1); }
+    });
+    sigset_t alarm;
+    sigemptyset(&alarm);
+    sigaddset(&alarm, SIGALRM);
+    pthread_sigmask(SIG_BLOCK, &alarm, nullptr);     // inherited: the signals below are this thread's alone
+    for (int mode = 0; mode < 2; ++mode) {           // 0: signal handler, 1: another thread
+        g_stop_ctx = c.h;
+        std::atomic<bool> done{false};
+        std::thread other;
+        if (mode == 0) {
+            signal(SIGALRM, stop_handler);
+            other = std::thread([&, self = pthread_self()] { while (!done) { pthread_kill(self, SIGALRM); std::this_thread::sleep_for(std::chrono::microseconds(20)); } });
+            pthread_sigmask(SIG_UNBLOCK, &alarm, nullptr);
+        } else {
+            other = std::thread([&] { while (!done) stop_handler(0); });
+        }
+        g_stops = 0;
+        int mixed = 0;
+        for (int it = 0; it < 20000 || g_stops < 5000; ++it) {
+            if (moe_expert_enqueue(c.h, c.x, &c.w, 4, nullptr) != MOE_OK || moe_expert_collect(c.h, &cur, nullptr) != MOE_OK) { CHECK(false); break; }
+            if (mode == 0 && it % 16 == 0) {         // (handlers run to their end: nothing is under way here)
+                pthread_sigmask(SIG_BLOCK, &alarm, nullptr);
+                mixed += stops_set() != 0 && stops_set() != qmoe::kStopCopies;
+                pthread_sigmask(SIG_UNBLOCK, &alarm, nullptr);
+            }
+        }
+        done = true;
+        other.join();
+        pthread_sigmask(SIG_BLOCK, &alarm, nullptr);
+        CHECK(mixed == 0 && (stops_set() == 0 || stops_set() == qmoe::kStopCopies));
+    }
+    over = true;
+    watch.join();
+    stub_complete_first(-1);
+}
+
 static void test_config_and_workspace_errors() {
     moe_config bad = {0, 1, 64, 64, MOE_BF16, 16, 8, 0};
     CHECK(moe_workspace_bytes(&bad) == 0);
@@ -296,6 +376,8 @@ int main() {
     test_policy_order_and_errors();
     test_enqueued_sequence_bookkeeping(MOE_BF16);
     test_enqueued_sequence_bookkeeping(MOE_F32);
+    test_every_copy_of_the_stop_word();
+    test_stops_beside_clears();
     test_scheduler_random_trace();
     printf(g_fail ? "%d checks failed\n" : "all host-logic checks passed\n", g_fail);
     return g_fail ? 1 : 0;

@@ -22,6 +22,7 @@ void stub_reset_launches(void);
 int stub_n_launches(void);
 const StubLaunch *stub_launch(int i);
 void stub_complete_first(int n);                       /* the next reports mark ranges [0,n) complete; -1 = all */
+const int32_t *stub_stop_words(void);                  /* the stop words that the last gate was given */
 #ifdef __cplusplus
 }
 #endif

@@ -12,6 +12,7 @@ namespace {
 std::vector<int32_t> g_counts;                 // [E][2], planted by the test
 std::vector<StubLaunch> g_launches;            // every expert launch since the last reset
 int g_complete_first = -1;                     // report: ranges [0, n) complete; -1 = all
+const int32_t *g_stop = nullptr;               // the stop words that the last gate was given
 }  // namespace
 
 extern "C" {
@@ -20,6 +21,7 @@ void stub_reset_launches(void) { g_launches.clear(); }
 int stub_n_launches(void) { return (int)g_launches.size(); }
 const StubLaunch *stub_launch(int i) { return &g_launches[(size_t)i]; }
 void stub_complete_first(int n) { g_complete_first = n; }
+const int32_t *stub_stop_words(void) { return g_stop; }
 }
 
 namespace qmoe {
@@ -78,7 +80,7 @@ hipError_t launch_pack_mxfp4(const void *, const void *, void *, void *, int, in
 hipError_t launch_pack_gate(const void *, void *, int, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_reduce_planes(const Seg *, int, const float *, float *, int, int, long, hipStream_t) { return hipSuccess; }
 hipError_t launch_combine(const CombineArgs &, hipStream_t) { return hipSuccess; }
-hipError_t launch_gate(const int32_t *, int32_t *go, int g, hipStream_t) { go[g] = 1; return hipSuccess; }
+hipError_t launch_gate(const int32_t *stop, int32_t *go, int g, hipStream_t) { g_stop = stop; go[g] = 1; return hipSuccess; }
 hipError_t launch_report(const Seg *, int n, const int32_t *, int32_t *ok_host, int, int, int, hipStream_t) {
     for (int i = 0; i < n; ++i) ok_host[i] = (g_complete_first < 0 || i < g_complete_first) ? 1 : 0;
     return hipSuccess;

@@ -20,7 +20,7 @@ def test_host_logic_under_asan_and_ubsan(tmp_path):
     cmd = ["g++", "-std=c++17", "-g", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
            "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
            "-x", "c++", os.path.join(CSRC, "qmoe_api.hip"), os.path.join(CSRC, "qsched.hip"),
-           os.path.join(STUB, "stub_launches.cpp"), os.path.join(STUB, "host_test.cpp"), "-o", exe]
+           os.path.join(STUB, "stub_launches.cpp"), os.path.join(STUB, "host_test.cpp"), "-pthread", "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0 and "sanitizer" in r.stderr.lower() and "cannot find" in r.stderr.lower():
         pytest.skip("no sanitizer runtime for g++ on this machine")
