@@ -13,9 +13,8 @@
 // Against packets of 4 segments x 8 column tiles dealt out whether full or not, both with the kernels on 32x32x16 MFMAs (14 half-empty packets
 // are 32 workgroups on six XCDs and 16 on two; with 11 column tiles the full packets all fall on even
 // XCDs): one token on 2 of 8 experts, H 4096, F 14336: gate-up 92 -> 73 us, layer 190 -> 171 us; 32 tokens
-// on 64 experts, H 2048, F 1408: 90 -> 74 us, 170 -> 154 us; 8192 tokens on the same 1.29 -> 1.25 ms.  Where the
-// packets kept an XCD to one expert of two segments the list was slower, by 1 % for 1531 tokens on 8 experts to 6 %
-// for 2048: those launches deal their experts out (see plan_items).
+// on 64 experts, H 2048, F 1408: 90 -> 74 us, 170 -> 154 us; 8192 tokens on the same 1.29 -> 1.25 ms.  Where it
+// is better that an XCD keeps to its own experts, as with the packets, a launch deals them out (see plan_items).
 // Other cuts, measured: a contiguous eighth of the list for each XCD: 8192 tokens on 64 experts +2 %,
 // 4-bit decode down projection 48 -> 64 us (four XCDs get all the long segments); eighths of equal cost
 // instead of equal count: 3584 tokens on 8 experts +9 % (a few more short items add a round); segments
@@ -97,6 +96,37 @@ __host__ __device__ inline ItemPos column_item_pos(unsigned item, unsigned n, un
     return {pos, blk * W + (r - pos * w)};
 }
 
+// A run of row-adjacent units of one expert, and the segments of at most 256 rows that the runs of a launch are cut into, equal
+// within one tile: workgroups that share an expert's weight tiles then advance through K at the same pace and meet in L2, which a
+// 256/256/256/128 cut does not give them.
+struct Run { uint32_t row0, rows; uint16_t expert; };
+// Tiles are of 32 rows, from when the kernels' were.  Up to 8 runs that make two bf16 segments each are cut between fragments of 16
+// rows, which makes both nearly equal.  Layer us with 32 / 16, top-2 of 8 experts, H 4096, F 14336, in the common list (see plan_items):
+// 1293 tokens 850 / 838, 1400 tokens 905 / 885, 1531 tokens 950 / 927, the last two enqueued in 4 K ranges 961 / 939 and 995 / 986; of 6 experts 1200
+// tokens 796 / 784; 4-bit within 1 % either way; with a hot expert 1200 tokens on 6 experts 818 / 810, 1365 on 8 979 / 968, 1500 1144 / 1155.
+// With more experts or segments longer and shorter ones mix on an XCD, and it costs up to 1 % (1199 tokens, top-8 of 32, H 2048, F 7040, 846 -> 854).
+inline std::vector<Seg> cut_runs(const std::vector<Run> &runs, bool bf16) {
+    std::vector<Seg> segs;
+    const bool few = runs.size() <= kXcds;
+    for (const Run &r : runs) {
+        const uint32_t nseg = (r.rows + 255) / 256, tile = nseg == 2 && few && bf16 ? 16 : 32, tiles = (r.rows + tile - 1) / tile;
+        const uint32_t base = tiles / nseg, extra = tiles % nseg;
+        uint32_t row = r.row0, left = r.rows;
+        for (uint32_t j = 0; j < nseg; ++j) {
+            const uint32_t want = (base + (j < extra ? 1 : 0)) * tile;
+            const uint32_t take = want < left ? want : left;
+            segs.push_back(Seg{row, (uint16_t)take, r.expert});
+            row += take;
+            left -= take;
+        }
+    }
+    return segs;
+}
+
+// What a segment costs the XCD that it is dealt to, in fragments of 16 rows, the kernels' unit, whatever it was cut in; up to
+// 6 of them it takes as long as its weights.
+inline long seg_cost(int rows) { return std::max((rows + 15) / 16, 6); }
+
 // True iff every weight element of the launch is read by one workgroup only: segs are sorted by
 // expert and no two belong to the same one.
 inline bool items_stream(const Seg *segs, int n) {
@@ -109,21 +139,20 @@ inline bool items_stream(const Seg *segs, int n) {
 // segments a group holds segments of one expert only, the expert with the most rows first; else the
 // groups are cut from the list sorted by length.
 // Returns true if the launch deals its groups to the XCDs: segments xcd[x] .. xcd[x+1] - 1 are XCD x's alone.
-// With the common list all XCDs work on the same expert at a time; where an expert has few segments, an XCD that
-// keeps to its own experts fetches fewer tokens for the same columns, if the shares (their cost in token tiles, the
-// largest over the mean) come out even.  Us a layer (gate-up + down) with the list / dealt out, top-2 of 8 experts, H 4096,
-// F 14336 unless stated:
-//   32 experts, top-4, H 2048, F 1536, 4000 tokens (share 1.01) 388 (203 + 143) / 367 (198 + 131), 4-bit weights 335 (175 + 114) /
-//   324 (168 + 112); 64 experts, top-8, H 2048, F 1408, 4-bit, 3000 tokens, skewed 461 (252 + 155) / 446 (250 + 143): dealt
-//   out up to 1.02;
-//   two segments per expert: 1100 tokens (1.10) 884 (531 + 350) / 857 (500 + 343), 1300 tokens (1.02) 940 (607 + 321) / 921 (584 +
-//   319), 1531 tokens (1.05) 1047 (684 + 356) / 1027 (651 + 359), enqueued 1121 (684 + 384) / 1091 (660 + 374): dealt out up to
-//   1.10, except for 4-bit weights (1531 tokens 837 (561 + 281) / 846 (572 + 284));
-//   2048 tokens, two or three segments (1.03), down projection 604 / 547: its 320 items are 1.25 rounds of the chip, and
-//   the list's last quarter takes as long as a round: dealt out below two rounds up to 1.10; gate-up, 7 rounds, 824 / 873, and
-//   with 4 K ranges, 5 rounds, 455 / 485: the list.
-// Uneven shares lose: 1300 tokens, skewed (2.5) 975 with the list / 1631.  So do more segments per expert, even
-// shares or not: 2500 tokens (3 segments, 1.05) 1624 / 1667, 3584 tokens, 4-bit (4 segments, 1.02) 1812 / 1826.
+// With the common list all XCDs work on the same expert at a time, and its last round is partly filled; an XCD that keeps to
+// its own experts fetches fewer tokens for the same columns and ends with them, if the shares (seg_cost, the largest over the
+// mean) come out even.  Us a layer with the list / dealt out, top-2 of 8 experts, H 4096, F 14336 unless stated:
+//   some experts of one segment: 1130 tokens, 15 segments (share 1.11) 866 / 810, enqueued in 4 K ranges 891 / 844, 1100 tokens, 14
+//   segments (1.09) 859 / 813, 16 experts, F 4096, 2100 tokens (1.01) 554 / 528, 64 experts, top-8, H 2048, F 1408, 2100 tokens (1.00)
+//   432 / 403.  25 layouts of 1040 to 1250 tokens by share, dealt out over list on average, bf16 whole and enqueued, 4-bit whole and
+//   enqueued: up to 1.06 0.96, 0.96, 0.94, 0.94; to 1.09 0.96, 1.00, 0.95, 0.97; to 1.12 0.96, 0.97, 0.97, 0.96; to 1.15 0.99, 1.00,
+//   0.98, 0.98; beyond 0.99, 1.01, 1.00, 1.01, and 1.4 to 1.8 with a hot expert: dealt out up to 1.15;
+//   launches below two rounds of the chip, where the list's last quarter takes as long as a round: down projection of 2010 tokens
+//   (1.10) 1353 / 1292, 4-bit 1205 / 1134, 1960 tokens (1.13) 1277 / 1244 and 1141 / 1090, (1.19) 1247 / 1258 and 1142 / 1085: up to 1.15;
+//   two or more segments for every expert: 32 experts, top-4, H 2048, F 1536, 4000 tokens (1.01) 370 / 353, 4-bit 332 / 319; 16 experts,
+//   F 4096, 3000 tokens (1.01) 590 / 570; 58 layouts of 8 experts, 1100 to 1850 tokens, as above: up to 1.03 1.00, 1.01, 1.01, 1.01; to
+//   1.09 1.01, 1.01, 1.00, 1.01; to 1.15 1.01, 1.03, 1.01, 1.03; to 1.2 1.03, 1.04, 1.03, 1.05: up to 1.02.
+// More segments per expert: 2300 tokens (three, 1.05) 1440 / 1451, 4-bit 1276 / 1267, 3584 tokens (four, 1.03) 1912 / 1926: the list.
 inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool four_bit, ItemSeg *out, uint32_t (&xcd)[kXcds + 1]) {
     struct Group { int first, count, rows; };
     std::vector<Seg> s(segs, segs + n);
@@ -154,20 +183,19 @@ inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool 
     int experts = 1;
     for (int i = 1; i < n; ++i) experts += s[i].expert != s[i - 1].expert;
     if (!stream && 2 * n <= 5 * experts) {
-        // each group, the one of the most rows first, to the XCD with the least; up to 3 token tiles a segment takes
-        // as long as its weights
+        // each group, the one of the most rows first, to the XCD with the least
         long load[kXcds] = {}, total = 0;
         std::vector<int> owner;
         for (const Group &g : groups) {
             long cost = 0;
-            for (int i = 0; i < g.count; ++i) cost += std::max((s[g.first + i].rows + 31) / 32, 3);
+            for (int i = 0; i < g.count; ++i) cost += seg_cost(s[g.first + i].rows);
             owner.push_back((int)(std::min_element(load, load + kXcds) - load));
             load[owner.back()] += cost;
             total += cost;
         }
         const long share = 100 * kXcds * *std::max_element(load, load + kXcds);      // of the mean, in percent x total
-        const bool few = (!four_bit && n <= 2 * experts) || (unsigned)n * cols < 2 * kXcds * kXcdCus;
-        if (share <= (few ? 110 : 102) * total) {
+        const bool uneven = n < 2 * experts || (unsigned)n * cols < 2 * kXcds * kXcdCus;
+        if (share <= (uneven ? 115 : 102) * total) {
             for (int x = 0; x < kXcds; ++x) {
                 xcd[x] = (uint32_t)at;
                 for (size_t i = 0; i < groups.size(); ++i)

@@ -15,6 +15,7 @@
 #include <new>
 #include <vector>
 
+#include "expert_items.h"
 #include "qmoe_internal.h"
 
 namespace {
@@ -479,36 +480,16 @@ static int32_t launch_unit_list(moe_ctx *ctx, const void *x, const moe_weights *
         if (un[p].expert != un[q].expert) return un[p].expert < un[q].expert;
         return un[p].row0 < un[q].row0;
     });
-    // First the runs of row-adjacent units of one expert, then each run cut into ceil(rows/256)
-    // segments of (nearly) equal numbers of 32-row tiles: workgroups that share an expert's weight
-    // tiles then advance through K at the same pace and meet in L2, which a 256/256/256/128 cut
-    // does not give them.  Up to 8 runs, at most one for each XCD, are cut between fragments of 16 rows where they make two
-    // bf16 segments: the longer one is what its XCD takes (top-2 of 8 experts, H 4096, F 14336: 1293 tokens 837 -> 819 us, 1531 enqueued 980 -> 962,
-    // 1595 tokens 951 -> 937; 1365 with a hot expert 934 -> 938).  With more experts or segments longer and shorter ones mix on an
-    // XCD, and it costs up to 1 % (1199 tokens, top-8 of 32, H 2048, F 7040, 846 -> 854; 2770 on 8 experts, skewed, 4-bit, 1454 -> 1463).
-    struct Run { uint32_t row0, rows; uint16_t expert; };
-    std::vector<Run> runs;
+    // First the runs of row-adjacent units of one expert, then each run cut into segments (cut_runs).
+    std::vector<qmoe::Run> runs;
     for (uint32_t i : idx) {
         const moe_unit &u = un[i];
         if (!runs.empty() && runs.back().expert == (uint16_t)u.expert && runs.back().row0 + runs.back().rows == (uint32_t)u.row0)
             runs.back().rows += (uint32_t)u.rows;
         else
-            runs.push_back(Run{(uint32_t)u.row0, (uint32_t)u.rows, (uint16_t)u.expert});
+            runs.push_back(qmoe::Run{(uint32_t)u.row0, (uint32_t)u.rows, (uint16_t)u.expert});
     }
-    std::vector<qmoe::Seg> segs;
-    const bool few = runs.size() <= 8;
-    for (const Run &r : runs) {
-        const uint32_t nseg = (r.rows + 255) / 256, tile = nseg == 2 && few && ctx->cfg.dtype == MOE_BF16 ? 16 : 32, tiles = (r.rows + tile - 1) / tile;
-        const uint32_t base = tiles / nseg, extra = tiles % nseg;
-        uint32_t row = r.row0, left = r.rows;
-        for (uint32_t j = 0; j < nseg; ++j) {
-            const uint32_t want = (base + (j < extra ? 1 : 0)) * tile;
-            const uint32_t take = want < left ? want : left;
-            segs.push_back(qmoe::Seg{row, (uint16_t)take, r.expert});
-            row += take;
-            left -= take;
-        }
-    }
+    const std::vector<qmoe::Seg> segs = qmoe::cut_runs(runs, ctx->cfg.dtype == MOE_BF16);
     if (segs.size() > (size_t)qmoe::kMaxSegs && contiguous) {
         // too many segments for the kernel arguments: the launch reads the device unit list
         if (ranges)

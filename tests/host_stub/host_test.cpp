@@ -240,6 +240,16 @@ static void test_enqueued_sequence_bookkeeping(int dtype) {
     CHECK(e.n_units == 0 && moe_expert_run(c.h, c.x, &c.w, 5, &e, nullptr) == MOE_DONE);
 }
 
+// The cut of two segments (cut_runs) as a launch gets it: between fragments of 16 rows in bf16, in tiles of 32 in fp32.
+static void test_two_segments_of_an_expert(int dtype) {
+    Ctx c(8, 2, 128, 256, dtype, 256, 2048);
+    moe_cursor cur = start(c, {100, 240, 0, 340, 340, 0, 170, 170, 0, 340, 1, 339, 0, 340, 0, 340});
+    stub_reset_launches();
+    CHECK(moe_expert_run(c.h, c.x, &c.w, UINT32_MAX, &cur, nullptr) == MOE_DONE);
+    CHECK(stub_n_launches() == 1 && stub_launch(0)->nseg == 16);
+    for (int i = 0; i < 16; ++i) CHECK(stub_launch(0)->rows[i] == (dtype == MOE_BF16 ? (i % 2 ? 164u : 176u) : (i % 2 ? 148u : 192u)));
+}
+
 // How many of the copies of the stop word are set.
 static int stops_set() {
     int n = 0;
@@ -376,6 +386,8 @@ int main() {
     test_policy_order_and_errors();
     test_enqueued_sequence_bookkeeping(MOE_BF16);
     test_enqueued_sequence_bookkeeping(MOE_F32);
+    test_two_segments_of_an_expert(MOE_BF16);
+    test_two_segments_of_an_expert(MOE_F32);
     test_every_copy_of_the_stop_word();
     test_stops_beside_clears();
     test_scheduler_random_trace();

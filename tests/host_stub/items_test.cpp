@@ -30,7 +30,7 @@ static void walk(int n, unsigned cols, Pos &&pos) {
     CHECK(*std::max_element(share, share + kXcds) - *std::min_element(share, share + kXcds) <= 1);
 }
 
-// The same for a launch that deals its segments to the XCDs: the shares differ by at most 10 % of the mean.
+// The same for a launch that deals its segments to the XCDs: no share is more than 15 % above the mean.
 static void walk_dealt(int n, unsigned cols, const uint32_t (&xcd)[kXcds + 1], const std::vector<ItemSeg> &it) {
     std::vector<int> seen((size_t)n * cols, 0);
     long load[kXcds] = {}, total = 0;
@@ -40,12 +40,12 @@ static void walk_dealt(int n, unsigned cols, const uint32_t (&xcd)[kXcds + 1], c
         const ItemPos p = column_item_pos(item, m, cols);
         CHECK(p.pos < m && p.cq < cols);
         ++seen[(size_t)(first + p.pos) * cols + p.cq];
-        const long cost = std::max((it[first + p.pos].rows + 31) / 32, 3);
+        const long cost = seg_cost(it[first + p.pos].rows);
         load[x] += cost;
         total += cost;
     }
     for (int v : seen) CHECK(v == 1);
-    CHECK(kXcds * *std::max_element(load, load + kXcds) <= total * 1.1);
+    CHECK(kXcds * *std::max_element(load, load + kXcds) <= total * 1.15);
 }
 
 int main() {
@@ -86,18 +86,15 @@ int main() {
             walk(n, cols, [&](unsigned item) { return column_item_pos(item, (unsigned)n, cols); });
         }
     {   // which launches deal their experts to the XCDs
-        auto deals = [](const std::vector<int> &rows, unsigned cols, bool four_bit) {      // one entry per expert
-            std::vector<Seg> segs;
+        auto runs_of = [](const std::vector<int> &rows) {                                      // one entry per expert
+            std::vector<Run> runs;
             uint32_t row = 0;
-            for (size_t e = 0; e < rows.size(); ++e) {
-                const int parts = (rows[e] + 255) / 256, tiles = (rows[e] + 31) / 32;
-                for (int p = 0, left = rows[e]; p < parts; ++p) {
-                    const int take = std::min(left, (tiles / parts + (p < tiles % parts)) * 32);
-                    segs.push_back(Seg{row, (uint16_t)take, (uint16_t)e});
-                    row += take;
-                    left -= take;
-                }
-            }
+            for (size_t e = 0; e < rows.size(); row += (uint32_t)rows[e++]) runs.push_back(Run{row, (uint32_t)rows[e], (uint16_t)e});
+            return runs;
+        };
+        // fine: cut as a bf16 launch is, between fragments of 16 rows where it is of up to 8 experts; else in tiles of 32
+        auto deals = [&](const std::vector<int> &rows, unsigned cols, bool four_bit, bool fine = true) {
+            const std::vector<Seg> segs = cut_runs(runs_of(rows), fine);
             std::vector<ItemSeg> it(segs.size());
             uint32_t xcd[kXcds + 1];
             const bool yes = plan_items(segs.data(), (int)segs.size(), items_stream(segs.data(), (int)segs.size()), cols, four_bit, it.data(), xcd);
@@ -111,11 +108,59 @@ int main() {
         CHECK(n_dealt > 50);
         const std::vector<int> two = {402, 380, 385, 370, 391, 384, 377, 373}, even(32, 500);
         const std::vector<int> three = {530, 520, 515, 500, 510, 505, 506, 510}, skewed = {1280, 300, 300, 300, 300, 300, 260, 258};
-        CHECK(deals(two, 112, false) == 1 && deals(two, 112, true) == 0 && deals(two, 64, false) == 1);
+        const std::vector<int> ones = {276, 296, 256, 304, 286, 306, 254, 282}, uneven = {227, 300, 284, 280, 353, 304, 233, 279};
+        CHECK(deals(two, 112, false) == 0 && deals(two, 112, true) == 0 && deals(two, 64, false) == 0 && deals(two, 16, false) == 1);
+        CHECK(deals(ones, 112, false) == 1 && deals(ones, 112, true) == 1 && deals(ones, 64, false) == 1 && deals(uneven, 112, false) == 0);
         CHECK(deals(three, 112, false) == 0 && deals(three, 16, false) == 1 && deals(three, 64, false) == 0);
         CHECK(deals(even, 12, false) == 1 && deals(even, 12, true) == 1);
         CHECK(deals(skewed, 112, false) == 0 && deals(skewed, 16, false) == 0);
+        CHECK(deals(even, 12, false, false) == 1);
         CHECK(deals(std::vector<int>(8, 896), 112, false) == 0 && deals(std::vector<int>(8, 250), 112, false) == 0);
+    }
+    {   // a run costs its fragments however it is cut, so whether a launch is dealt out does not hang on the cut
+        int dealt[2] = {0, 0};
+        const unsigned cols = 112;
+        for (int draw = 0; draw < 4000; ++draw) {
+            std::vector<Run> runs;
+            uint32_t row = 0;
+            const int mean = 255 + draw % 150;
+            for (int e = 0; e < 8; ++e) {
+                runs.push_back(Run{row, (uint32_t)(mean - 40 + std::rand() % 81), (uint16_t)e});
+                row += runs.back().rows;
+            }
+            long cost[2] = {0, 0};
+            bool yes[2];
+            for (int fine = 0; fine < 2; ++fine) {
+                const std::vector<Seg> segs = cut_runs(runs, fine);
+                const int n = (int)segs.size();
+                uint32_t at = 0;
+                for (const Seg &s : segs) {
+                    CHECK(s.row0 == at && s.rows >= 1 && s.rows <= 256);
+                    at += s.rows;
+                    cost[fine] += seg_cost(s.rows);
+                }
+                CHECK(at == row);
+                std::vector<ItemSeg> it(segs.size());
+                uint32_t xcd[kXcds + 1];
+                yes[fine] = plan_items(segs.data(), n, items_stream(segs.data(), n), cols, draw % 2, it.data(), xcd);
+                dealt[fine] += yes[fine];
+            }
+            const int n = draw;
+            CHECK(cost[0] == cost[1] && yes[0] == yes[1]);
+        }
+        const int n = dealt[0];
+        CHECK(dealt[0] > 400 && dealt[0] < 3600);
+    }
+    {   // cuts: two bf16 segments of up to 8 runs between fragments, anything else in tiles of 32
+        const int n = 0;
+        const unsigned cols = 0;
+        auto first = [](int runs, uint32_t rows, bool bf16) {
+            std::vector<Run> r;
+            for (int e = 0; e < runs; ++e) r.push_back(Run{(uint32_t)e * rows, rows, (uint16_t)e});
+            return (int)cut_runs(r, bf16)[0].rows;
+        };
+        CHECK(first(8, 340, true) == 176 && first(8, 340, false) == 192 && first(9, 340, true) == 192 && first(1, 257, true) == 144);
+        CHECK(first(8, 512, true) == 256 && first(8, 256, true) == 256 && first(8, 530, true) == 192);
     }
     // pieces of an fp32 launch: never 2^32 threads, and never more pieces than that needs
     for (uint64_t wgs : {uint64_t(1), uint64_t(3), uint64_t(256), uint64_t(512), uint64_t(4096), uint64_t(65535), (uint64_t(1) << 24) - 8}) {
