@@ -8,7 +8,7 @@
 // segments share every weight tile in L2 (when they belong to one expert), its column tiles the token
 // tiles.  The list is dealt out in rounds of one item per CU of the chip, 32 consecutive items to each
 // XCD, and what is left after the last whole round in 8 equal parts: every XCD gets the same number of
-// items and, the groups being sorted longest first, a like mix of long and short ones.
+// items and, by the order of the groups (see plan_items), a like mix of long and short ones.
 //
 // Against packets of 4 segments x 8 column tiles dealt out whether full or not, both with the kernels on 32x32x16 MFMAs (14 half-empty packets
 // are 32 workgroups on six XCDs and 16 on two; with 11 column tiles the full packets all fall on even
@@ -136,8 +136,8 @@ inline bool items_stream(const Seg *segs, int n) {
 }
 
 // Orders the segments (sorted by expert and row) of one launch into groups.  Where experts have several
-// segments a group holds segments of one expert only, the expert with the most rows first; else the
-// groups are cut from the list sorted by length.
+// segments a group holds segments of one expert only, the expert with the most rows first, in the common list of bf16 launches
+// with most of the experts of one short segment between the others; else the groups are cut from the list sorted by length.
 // Returns true if the launch deals its groups to the XCDs: segments xcd[x] .. xcd[x+1] - 1 are XCD x's alone.
 // With the common list all XCDs work on the same expert at a time, and its last round is partly filled; an XCD that keeps to
 // its own experts fetches fewer tokens for the same columns and ends with them, if the shares (seg_cost, the largest over the
@@ -205,17 +205,27 @@ inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool 
             return true;
         }
     }
-    // A workgroup of one of several segments is bound by the matrix units, one of an expert's only segment more by the stream of its
-    // weights.  Sorted by rows all of the latter came last, with the matrix units idle; now three quarters of them go out between the others
-    // and the rest make the end.  Us a layer sorted / mixed, Zipf-skewed: 4096 tokens on 64 experts, top-8, H 2048, F 1408 657 / 632, 6000
-    // tokens 884 / 874, 8192 tokens 1121 / 1124; 3000 tokens on 16 experts, top-2, F 4096 391 / 379; 4000 tokens on 32, top-4, F 2048
+    // A workgroup of one of several segments is bound by the matrix units, one of an expert's only segment, where that is short, more by
+    // the stream of its weights.  Sorted by rows all of the latter came last, with the matrix units idle; now three quarters of them go out
+    // between the others and the rest make the end.  Us a layer sorted / mixed, Zipf-skewed: 4096 tokens on 64 experts, top-8, H 2048, F 1408
+    // 657 / 632, 6000 tokens 884 / 874, 8192 tokens 1121 / 1124; 3000 tokens on 16 experts, top-2, F 4096 391 / 379; 4000 tokens on 32, top-4, F 2048
     // 460 / 454; 1500 tokens on 8 experts, H 4096, F 14336 959 / 949.  With half of them between the others the first five 643, 868, 1124,
     // 379, 464, with all of them 644, -, 1126, -, 459.  Least favourable of 14 drawn: 1085 tokens on 32, top-8, H 1664, F 3584 406 / 408.  4-bit weights, a quarter of the bytes, stay sorted (6000 tokens on 64 experts 793 / 796).
-    if (!stream && !four_bit) {
+    // It costs reads, because a block of columns may now end on another XCD than it began on: gate-up and down sorted / mixed, MB, 8192 tokens on 64
+    // experts 2110 / 2620 and 915 / 1000, 4096 tokens 1415 / 1715 and 630 / 720, 3000 on 16 experts, H 4096, 1535 / 1480 and 765 / 805; no launch is
+    // bound by them, and 8192 tokens take as long either way.
+    // Only segments of experts with one are longer than the others where experts have about 256 rows.  They are not bound by their weights then, and
+    // between the others they break blocks that share weights: 1060 tokens on 8 experts 858 / 895, 1130 tokens, enqueued in 4 K ranges
+    // 890 / 945, 16 experts, F 7168, 2100 tokens 827 / 848.  By the mean rows of the only segments over those of the others, mixed over sorted of 43
+    // bf16 layouts of 8 and 16 experts: up to 0.85 0.991 (0.967 to 1.028), to 1 0.997 (0.973 to 1.033), beyond 1.024 (0.997 to 1.065).
+    const size_t heavy = (size_t)(std::find_if(groups.begin(), groups.end(), [](const Group &g) { return g.rows <= 256; }) - groups.begin());
+    long all[2] = {0, 0}, rows[2] = {0, 0}, out_segs[2] = {0, 0};       // segments, and their rows, of the groups before and from `heavy` on
+    for (size_t i = 0; i < groups.size(); ++i) {
+        all[i >= heavy] += groups[i].count;
+        for (int j = 0; j < groups[i].count; ++j) rows[i >= heavy] += s[groups[i].first + j].rows;
+    }
+    if (!stream && !four_bit && rows[1] * all[0] < rows[0] * all[1]) {
         std::vector<Group> mixed;
-        const size_t heavy = (size_t)(std::find_if(groups.begin(), groups.end(), [](const Group &g) { return g.rows <= 256; }) - groups.begin());
-        long all[2] = {0, 0}, out_segs[2] = {0, 0};                 // segments of the groups before and from `heavy` on
-        for (size_t i = 0; i < groups.size(); ++i) all[i >= heavy] += groups[i].count;
         for (size_t i = 0, j = heavy; i < heavy || j < groups.size();) {
             const bool light = j < groups.size() && (i == heavy || 4 * (out_segs[1] + groups[j].count) * all[0] <= 3 * out_segs[0] * all[1]);
             mixed.push_back(groups[light ? j++ : i++]);

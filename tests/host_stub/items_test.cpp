@@ -3,6 +3,7 @@
 // and of the pieces a launch is cut into.
 #include <cstdio>
 #include <cstdlib>
+#include <string>
 #include <vector>
 
 #include "expert_items.h"
@@ -150,6 +151,38 @@ int main() {
         }
         const int n = dealt[0];
         CHECK(dealt[0] > 400 && dealt[0] < 3600);
+    }
+    {   // order of the list: 'H' a segment of an expert with several, 'l' the only one of its expert, each kind by falling rows of the expert
+        auto order = [](const std::vector<int> &rows, bool four_bit) {
+            std::vector<Run> runs;
+            uint32_t row = 0;
+            for (size_t e = 0; e < rows.size(); row += (uint32_t)rows[e++]) runs.push_back(Run{row, (uint32_t)rows[e], (uint16_t)e});
+            const std::vector<Seg> segs = cut_runs(runs, true);
+            const int n = (int)segs.size();
+            const unsigned cols = 112;
+            std::vector<ItemSeg> it(segs.size());
+            uint32_t xcd[kXcds + 1];
+            CHECK(!plan_items(segs.data(), n, items_stream(segs.data(), n), cols, four_bit, it.data(), xcd));
+            std::string kinds;
+            int last[2] = {1 << 30, 1 << 30};
+            for (const ItemSeg &v : it) {
+                const int total = rows[v.expert];
+                kinds += total > 256 ? 'H' : 'l';
+                CHECK(total <= last[total > 256]);
+                last[total > 256] = total;
+            }
+            return kinds;
+        };
+        const std::vector<int> skewed = {1500, 20, 90, 10, 60, 1200, 80, 30};       // groups of 3, 3, 3 and 2 segments; of 6 only ones
+        // l may be out before h of the 11 where 4 l / 6 <= 3 h / 11: none before 3, 1 before 6, 2 before 9, 3 before the last 2
+        const int n = 0;
+        const unsigned cols = 0;
+        const std::string mixed = order(skewed, false);
+        CHECK(mixed == "HHHlHHHlHHHlHHlll");
+        CHECK(order(skewed, true) == "HHHHHHHHHHHllllll");                          // 4-bit weights: sorted
+        CHECK(order({1500, 1200, 900}, false) == std::string(6 + 5 + 4, 'H'));
+        CHECK(order({227, 300, 284, 280, 353, 304, 233, 279}, false) == "HHHHHHHHHHHHll");      // only segments that are the longer ones: last
+        CHECK(order({20, 90, 10, 60, 80, 30, 70, 50, 40}, false).find('H') == std::string::npos);
     }
     {   // cuts: two bf16 segments of up to 8 runs between fragments, anything else in tiles of 32
         const int n = 0;
