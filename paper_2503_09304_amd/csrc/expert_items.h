@@ -30,6 +30,13 @@
 
 namespace qmoe {
 
+namespace bf16k {
+// Weight formats of the expert matrices: bf16 row-major, bf16 in MFMA-ordered 1 KiB blocks, and
+// 4-bit microscaling floats (e2m1 elements, one power-of-two e8m0 scale per 32 elements along K) in
+// MFMA-ordered blocks, turned into bf16 operands in registers (exactly: every such value is a bf16).
+enum { WF_ROWMAJOR = 0, WF_PACKED = 1, WF_MXFP4 = 2 };
+}  // namespace bf16k
+
 constexpr int kXcds = 8;
 constexpr int kXcdCus = 32;
 constexpr int kGroupSegs = 4;
@@ -235,6 +242,34 @@ inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool 
     }
     for (const Group &g : groups) place(g);
     return false;
+}
+
+// Columns per wave of a gate-up launch.  A workgroup stays on its CU for the whole of K, so a launch
+// costs whole rounds of the chip's CUs, and a weight-streaming launch moves bytes in proportion to
+// rounds x columns per workgroup.  Narrower waves (28 .. 16 columns; a wave's 32 MFMA rows stay, those
+// beyond its columns repeat its last one and are dropped) are taken when they make the last round full:
+// 8 experts x 14336 columns are 896 workgroups of 128 columns = 3.5 rounds of 256 CUs, but exactly 4
+// rounds of 112.  Layer us with 32 / the rule's columns, top-2 of 8 experts, H 4096, F 14336 unless stated (gate-up in brackets):
+//   bf16 packed, up to 96 rows: 64 tokens (305) / (299) with 28, 300 tokens 483 (317) / 467 (298) with 28;
+//   one round, where narrower waves only put more CUs to work: one token, top-8 of 64, H 2048, F 1408 56.4 (28.4) / 50.8 (22.7) with 16,
+//   two 71.6 / 71.0 with 24, one, top-4 of 32, F 1024 47.7 / 42.8 with 16, one on 8 experts 129.3 / 128.0 with 28;
+//   row-major, whose lanes read 64 bytes of a row at a time, any number of rows: 400 tokens 776 (508) / 721 (458) with 28, 700 tokens 829 (531) /
+//   798 (499), 850 tokens 852 / 832; of widths that cost the same the narrower one up to 96 rows: 20 tokens 616 (383) with 28 / 600 (369) with 16,
+//   64 tokens 660 (423) / 629 (394); beyond, 300 tokens with more than 96 rows 706 / 713.
+// Not: bf16 packed of more than 96 rows (400 tokens 484 / 481, 430 tokens 487 / 491, 512 tokens 501 / 519, 700 tokens 550 / 578: the rows that
+// repeat cost power); 4-bit weights, whose workgroups share a CU and are not bound by bytes (28 columns: 64 tokens, skewed (84) / (94),
+// one token 60 / 61; only 4 to 16 tokens gain, 8 tokens 142 / 136); launches whose segments share weights, which are MFMA-bound.
+inline int gate_up_wave_columns(bool stream, int wfmt, int tiles, int nseg, int F, long cus) {
+    if (!stream || wfmt == bf16k::WF_MXFP4 || (wfmt == bf16k::WF_PACKED && tiles > 3)) return 32;
+    const bool narrower = wfmt == bf16k::WF_ROWMAJOR && tiles <= 3;      // of widths that cost the same
+    int best = 32;
+    long best_cost = 0;
+    for (int cw = 32; cw >= 16; cw -= 4) {
+        const long wgs = (long)nseg * ((F + 4 * cw - 1) / (4 * cw));
+        const long cost = (wgs + cus - 1) / cus * cw;
+        if (cw == 32 || cost < best_cost + (narrower ? 1 : 0)) { best = cw; best_cost = cost; }
+    }
+    return best;
 }
 
 }  // namespace qmoe

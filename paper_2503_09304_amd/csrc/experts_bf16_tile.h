@@ -54,11 +54,6 @@
 namespace qmoe {
 namespace bf16k {
 
-// Weight formats of the expert matrices: bf16 row-major, bf16 in MFMA-ordered 1 KiB blocks, and
-// 4-bit microscaling floats (e2m1 elements, one power-of-two e8m0 scale per 32 elements along K) in
-// MFMA-ordered blocks, turned into bf16 operands in registers (exactly: every such value is a bf16).
-enum { WF_ROWMAJOR = 0, WF_PACKED = 1, WF_MXFP4 = 2 };
-
 // Smallest number of 32-row pieces whose variant keeps three LDS stages (see P3 in expert_tile).
 constexpr int kP3MinT = 3;
 

@@ -49,7 +49,11 @@ static void walk_dealt(int n, unsigned cols, const uint32_t (&xcd)[kXcds + 1], c
     CHECK(kXcds * *std::max_element(load, load + kXcds) <= total * 1.15);
 }
 
-int main() {
+// With arguments: the gate-up wave's columns on 256 CUs for each (weight format, 32-row tiles, segments, F) of a launch that streams.
+int main(int argc, char **argv) {
+    for (int i = 1; i + 3 < argc; i += 4)
+        std::printf("%d\n", gate_up_wave_columns(true, std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoi(argv[i + 2]), std::atoi(argv[i + 3]), 256));
+    if (argc > 1) return 0;
     int n_dealt = 0;
     std::srand(5);
     for (int n : {1, 2, 3, 4, 5, 8, 9, 31, 32, 33, 64, 65, 383, 384})

@@ -1,20 +1,38 @@
 """The order in which a bf16 expert launch deals its work to the XCDs (csrc/expert_items.h), on the CPU:
-host_stub/items_test.cpp walks the workgroups of launches with 1 to 384 segments and 1 to 128 columns."""
+host_stub/items_test.cpp walks the workgroups of launches with 1 to 384 segments and 1 to 128 columns.  The columns of its gate-up waves."""
 import os
 import subprocess
+
+from test_gpu_fragments import WAVE_COLUMNS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 STUB = os.path.join(ROOT, "tests", "host_stub")
 
 
-def test_every_item_once_and_equal_shares(tmp_path):
+def items_test(tmp_path, *args):
     exe = str(tmp_path / "items_test")
     cmd = ["g++", "-std=c++17", "-O1", "-Wall", "-I", STUB, "-I", os.path.join(ROOT, "include"),
            "-I", os.path.join(ROOT, "paper_2503_09304_amd", "csrc"), os.path.join(STUB, "items_test.cpp"), "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-4000:]
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
-    assert r.returncode == 0 and "all item checks passed" in r.stdout, r.stdout[-2000:]
+    r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-2000:]
+    return r.stdout
+
+
+def test_every_item_once_and_equal_shares(tmp_path):
+    assert "all item checks passed" in items_test(tmp_path)
+
+
+def test_wave_columns_that_the_gpu_cases_take(tmp_path):
+    """Each case of test_wave_columns_of_the_rule runs with the width it is listed for, and every width is among them."""
+    args = []
+    for fmt, E, H, F, rows, width in WAVE_COLUMNS:
+        args += [("rowmajor", "packed", "mxfp4").index(fmt), (rows + 31) // 32, E, F]
+    widths = [int(v) for v in items_test(tmp_path, *args).split()]
+    assert widths == [case[-1] for case in WAVE_COLUMNS]
+    for fmt in ("rowmajor", "packed"):
+        assert {w for case, w in zip(WAVE_COLUMNS, widths) if case[0] == fmt} == {16, 20, 24, 28, 32}
 
 
 def test_few_tokens_split_the_down_projection_by_the_experts_they_reach():

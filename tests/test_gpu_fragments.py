@@ -140,13 +140,19 @@ def test_narrow_down_projection(fmt, E, H, F, rows):
         assert error(outs[0][e * rows: (e + 1) * rows], x, W, e) <= bar("bf16", H, F)
 
 
-# one round of the CUs, in which the narrowest waves are taken; two rounds of 28 columns for 32 (8 experts x 36 or 42 workgroups),
-# row-major also beyond 96 rows; equal cost, where row-major of few rows goes to 16 columns
-@pytest.mark.parametrize("fmt,E,H,F,rows", [("packed", 3, 128, 512, 1), ("packed", 8, 64, 2176, 33), ("rowmajor", 3, 128, 192, 97), ("rowmajor", 8, 64, 4608, 129),
-                                            ("rowmajor", 8, 64, 4608, 256), ("packed", 8, 64, 4608, 96), ("rowmajor", 64, 64, 1408, 5)])
-def test_wave_columns_of_the_rule(fmt, E, H, F, rows, monkeypatch):
+# E experts of `rows` rows each and the columns that the launch rule gives a gate-up wave on 256 CUs (test_expert_items.py asks the rule
+# itself): launches of one round, two and more, row-major also beyond 96 rows, of equal cost (row-major of few rows goes to 16 columns)
+WAVE_COLUMNS = [("packed", 3, 128, 512, 1, 16), ("packed", 8, 64, 2176, 33, 20), ("rowmajor", 3, 128, 192, 97, 16), ("rowmajor", 8, 64, 4608, 129, 20),
+                ("rowmajor", 8, 64, 4608, 256, 20), ("packed", 8, 64, 4608, 96, 20), ("rowmajor", 64, 64, 1408, 5, 16),
+                ("packed", 8, 64, 2624, 17, 24), ("packed", 16, 64, 1408, 64, 24), ("packed", 8, 64, 3584, 32, 28), ("packed", 16, 64, 3136, 1, 28),
+                ("rowmajor", 8, 64, 3072, 33, 24), ("rowmajor", 16, 64, 1664, 160, 28), ("rowmajor", 8, 64, 3136, 97, 28),
+                ("packed", 8, 64, 3648, 96, 32), ("packed", 8, 64, 3584, 97, 32), ("rowmajor", 8, 64, 3648, 97, 32), ("mxfp4", 8, 64, 3584, 32, 32)]
+
+
+@pytest.mark.parametrize("fmt,E,H,F,rows,width", WAVE_COLUMNS)
+def test_wave_columns_of_the_rule(fmt, E, H, F, rows, width, monkeypatch):
     """Narrower gate-up waves than 32 columns, as the launch rule takes them, give the bits of 32 columns, and plain products."""
-    print("case", fmt, E, H, F, rows, flush=True)
+    print("case", fmt, E, H, F, rows, "columns", width, flush=True)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(rows + F)
     x, Wg = torch.randn((rows, H), generator=gen, device=DEV).bfloat16(), (torch.randn((H, E), generator=gen, device=DEV) * 0.02).bfloat16()
