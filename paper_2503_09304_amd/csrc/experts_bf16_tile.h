@@ -34,7 +34,7 @@
 //
 // A launch works on row segments: the host joins the row-adjacent units of one expert in a call (the
 // LS and BE part of its queue, consecutive chunks) and cuts each such run into segments of at most 256
-// rows with equal counts of 32, so that one pass over the weights serves them and workgroups
+// rows, equal within a tile of 32 rows or a fragment of 16 (cut_runs), so that one pass over the weights serves them and workgroups
 // that share weight tiles keep the same pace.
 //
 // Determinism.  Each output element is one chain of MFMA accumulations over K in ascending order
@@ -300,7 +300,7 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     // launches rises; a loop of nothing but MFMAs on random operands 2.06 -> 2.10 PFLOP/s, gate-up of 3584 tokens on 8 experts 1367 -> 1351 us, with
     // 4-bit weights 1251 -> 1238, 8192 tokens on 64 experts 674 -> 667), one LDS fragment read (LA
     // slots before its use), and its share of the T + 8 global loads and of the T LDS writes of the next token tile (last slots).
-    // The loads of the four waves keep the texture path busy for about 16 clocks each, 960 of an iteration's 2048 clocks of MFMA with
+    // The loads of the four waves keep the texture path busy for about 16 clocks each, 1024 of an iteration's 2048 clocks of MFMA with
     // 256 rows: dealt out over the first half of the slots they queue, and a wave that cannot issue its load issues no MFMA either.
     // With more than 64 rows and bf16 weights they are dealt out over all slots: down projection us with the first half / all, top-2 of
     // 8 experts, H 4096, F 14336: 3584 tokens 694 / 640, 1531 tokens in 4 K ranges 355 / 335, 700 tokens 188 / 184; 8192 tokens on 64 experts
@@ -313,8 +313,8 @@ __device__ __forceinline__ void expert_tile(const KArgs &p, const moe_unit un, c
     // iteration earlier, so not where the weight stream is the bound (128 tokens on 8 experts, 4 K ranges 540 -> 544 us), and not for 4-bit
     // weights, whose operands of step 1 are made during step 0.  An accumulator's sums run in the same order either way.
     constexpr bool CHAIN = !MX && P3 && !STREAM;
-    constexpr int SL = 2 * NF, RF = CHAIN ? 2 * (P3 ? 3 : (NF < 3 ? NF : 3)) : P3 ? 6 : (SL < 4 ? SL : 4);
-    constexpr int LA = CHAIN ? 2 * (NF < 2 ? NF : 2) : RF - 1;     // slots read ahead
+    constexpr int SL = 2 * NF, RF = P3 ? 6 : (SL < 4 ? SL : 4);
+    constexpr int LA = CHAIN ? 4 : RF - 1;     // slots read ahead
     static_assert(!P3 || U * SL % RF == 0, "the ring of fragments goes on from iteration to iteration");
     bf16x8 af[RF];
     const char *a_at[2];                    // this lane's piece of step 0 and 1 in a token row
