@@ -114,6 +114,7 @@ struct Run { uint32_t row0, rows; uint16_t expert; };
 // With more experts or segments longer and shorter ones mix on an XCD, and it costs up to 1 % (1199 tokens, top-8 of 32, H 2048, F 7040, 846 -> 854).
 inline std::vector<Seg> cut_runs(const std::vector<Run> &runs, bool bf16) {
     std::vector<Seg> segs;
+    segs.reserve(runs.size() + 8);
     const bool few = runs.size() <= kXcds;
     for (const Run &r : runs) {
         const uint32_t nseg = (r.rows + 255) / 256, tile = nseg == 2 && few && bf16 ? 16 : 32, tiles = (r.rows + tile - 1) / tile;

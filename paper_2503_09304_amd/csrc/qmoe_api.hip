@@ -482,6 +482,7 @@ static int32_t launch_unit_list(moe_ctx *ctx, const void *x, const moe_weights *
     });
     // First the runs of row-adjacent units of one expert, then each run cut into segments (cut_runs).
     std::vector<qmoe::Run> runs;
+    runs.reserve(idx.size());
     for (uint32_t i : idx) {
         const moe_unit &u = un[i];
         if (!runs.empty() && runs.back().expert == (uint16_t)u.expert && runs.back().row0 + runs.back().rows == (uint32_t)u.row0)
