@@ -149,18 +149,19 @@ inline bool items_stream(const Seg *segs, int n) {
 // Returns true if the launch deals its groups to the XCDs: segments xcd[x] .. xcd[x+1] - 1 are XCD x's alone.
 // With the common list all XCDs work on the same expert at a time, and its last round is partly filled; an XCD that keeps to
 // its own experts fetches fewer tokens for the same columns and ends with them, if the shares (seg_cost, the largest over the
-// mean) come out even.  Us a layer with the list / dealt out, top-2 of 8 experts, H 4096, F 14336 unless stated:
-//   some experts of one segment: 1130 tokens, 15 segments (share 1.11) 866 / 810, enqueued in 4 K ranges 891 / 844, 1100 tokens, 14
-//   segments (1.09) 859 / 813, 16 experts, F 4096, 2100 tokens (1.01) 554 / 528, 64 experts, top-8, H 2048, F 1408, 2100 tokens (1.00)
-//   432 / 403.  25 layouts of 1040 to 1250 tokens by share, dealt out over list on average, bf16 whole and enqueued, 4-bit whole and
-//   enqueued: up to 1.06 0.96, 0.96, 0.94, 0.94; to 1.09 0.96, 1.00, 0.95, 0.97; to 1.12 0.96, 0.97, 0.97, 0.96; to 1.15 0.99, 1.00,
-//   0.98, 0.98; beyond 0.99, 1.01, 1.00, 1.01, and 1.4 to 1.8 with a hot expert: dealt out up to 1.15;
-//   launches below two rounds of the chip, where the list's last quarter takes as long as a round: down projection of 2010 tokens
-//   (1.10) 1353 / 1292, 4-bit 1205 / 1134, 1960 tokens (1.13) 1277 / 1244 and 1141 / 1090, (1.19) 1247 / 1258 and 1142 / 1085: up to 1.15;
-//   two or more segments for every expert: 32 experts, top-4, H 2048, F 1536, 4000 tokens (1.01) 370 / 353, 4-bit 332 / 319; 16 experts,
-//   F 4096, 3000 tokens (1.01) 590 / 570; 58 layouts of 8 experts, 1100 to 1850 tokens, as above: up to 1.03 1.00, 1.01, 1.01, 1.01; to
-//   1.09 1.01, 1.01, 1.00, 1.01; to 1.15 1.01, 1.03, 1.01, 1.03; to 1.2 1.03, 1.04, 1.03, 1.05: up to 1.02.
-// More segments per expert: 2300 tokens (three, 1.05) 1440 / 1451, 4-bit 1276 / 1267, 3584 tokens (four, 1.03) 1912 / 1926: the list.
+// mean) come out even.  Time dealt out over list, bf16 / 4-bit, shares in brackets; top-2 of 8 experts, H 4096, F 14336 unless stated:
+//   less than two rounds of the chip, where the list's last round weighs most: layers whose down projection alone is dealt out, 900 to 1160
+//   tokens in 9 to 15 segments (1.04 to 1.14) 0.97 / 0.96 on average, in 2 K ranges 0.96 / 0.95, 1900 to 2080 tokens in 17 to 20 segments (1.04
+//   to 1.19) 0.97 / 0.94: up to 1.15;
+//   1.5 to 2 segments an expert: 1040 to 1250 tokens in 12 (1.05 to 1.13) 0.96 / 0.92, 13 (1.07 to 1.13) 1.00 / 0.99, 14 (1.04 to 1.16) 0.95 / 0.93
+//   and 15 (1.08 to 1.14) 0.97 / 0.97, enqueued in 4 K ranges 1.03 / 0.99, 0.99 / 0.96, 0.95 / 0.93 and 0.98 / 0.97, (1.15 to 1.25) 1.00 / 1.01; 16
+//   experts, F 4096 (1.01 to 1.04) 0.96 / 0.93; 64 experts, top-8, H 2048, F 1408 (1.00) 0.96 / 0.97: up to 1.15;
+//   fewer: gate-up of 9 (1.10 to 1.14) 1.10 / 1.04 and 10 segments (1.07 to 1.14) 1.02 / 0.98, down projection in 4 K ranges 1.00 / 1.01 and 1.03 / 1.02;
+//   16 experts, F 4096 (1.02 to 1.06) 0.98 / 0.93, F 7168 1.02 / 0.97; 32 experts, top-4, H 2048, F 2048 (1.01) 0.95 / 0.92: up to 1.04;
+//   two for every expert: 1100 to 1850 tokens whole (up to 1.06) 1.00 / 1.00, (1.06 to 1.12) 1.01 / 1.00, (1.12 to 1.18) 1.02 / 1.02, enqueued 1.01 /
+//   1.01, 1.02 / 1.02 and 1.03 / 1.04; 16 experts, F 4096 and 7168 (1.01 to 1.04) 0.96 / 0.98; 32 experts, top-4, H 2048, F 1536 (1.01) 0.95 / 0.96: up to 1.04;
+//   more: 2300 to 3000 tokens in 24 and 26 (1.03 to 1.07) 1.01 / 0.99, 3584 in 32 (1.03) 1.01 / 1.00: up to 2.5 an expert and 1.02.
+// A hot expert: 1.4 to 1.8 times as long dealt out.
 inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool four_bit, ItemSeg *out, uint32_t (&xcd)[kXcds + 1]) {
     struct Group { int first, count, rows; };
     std::vector<Seg> s(segs, segs + n);
@@ -202,8 +203,8 @@ inline bool plan_items(const Seg *segs, int n, bool stream, unsigned cols, bool 
             total += cost;
         }
         const long share = 100 * kXcds * *std::max_element(load, load + kXcds);      // of the mean, in percent x total
-        const bool uneven = n < 2 * experts || (unsigned)n * cols < 2 * kXcds * kXcdCus;
-        if (share <= (uneven ? 115 : 102) * total) {
+        const bool below_two_rounds = (unsigned)n * cols < 2 * kXcds * kXcdCus, one_or_two = 2 * n >= 3 * experts && n < 2 * experts;
+        if (share <= (below_two_rounds || one_or_two ? 115 : n <= 2 * experts ? 104 : 102) * total) {
             for (int x = 0; x < kXcds; ++x) {
                 xcd[x] = (uint32_t)at;
                 for (size_t i = 0; i < groups.size(); ++i)
