@@ -27,8 +27,8 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, published
 
 # HBM bytes per launch of the gate-up kernel measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE,
 # scaled by what the same counters read for a 1 GiB device copy (profiles/bench_<workload>.md).
-MEASURED_TRAFFIC_BYTES = {"cfg2": 2002971420, "cfg4": 1917271552, "cfg3_be": 3370626927, "cfg5": 2402177070,
-                          "cfg4_mxfp4": 509106658, "cfg3_be_mxfp4": 1569210485}
+MEASURED_TRAFFIC_BYTES = {"cfg2": 1998154146, "cfg4": 1917013636, "cfg3_be": 3215085960, "cfg5": 2904766237,
+                          "cfg4_mxfp4": 508850389, "cfg3_be_mxfp4": 1549618804}
 
 
 def log(*a):
