@@ -119,6 +119,10 @@ int main(int argc, char **argv) {
         CHECK(deals(three, 112, false) == 0 && deals(three, 16, false) == 1 && deals(three, 64, false) == 0);
         CHECK(deals(even, 12, false) == 1 && deals(even, 12, true) == 1);
         CHECK(deals(skewed, 112, false) == 0 && deals(skewed, 16, false) == 0);
+        // by segments an expert: 10 segments (share 1.08), 12 (1.13), 16 (1.02)
+        const std::vector<int> ten = {224, 244, 239, 261, 236, 250, 258, 248}, twelve = {250, 290, 240, 266, 252, 284, 246, 260}, flat = {382, 380, 385, 384, 390, 384, 377, 383};
+        CHECK(deals(ten, 112, false) == 0 && deals(ten, 64, false) == 0 && deals(ten, 16, false) == 1);
+        CHECK(deals(twelve, 112, false) == 1 && deals(twelve, 112, true) == 1 && deals(flat, 112, false) == 1 && deals(flat, 112, true) == 1);
         CHECK(deals(even, 12, false, false) == 1);
         CHECK(deals(std::vector<int>(8, 896), 112, false) == 0 && deals(std::vector<int>(8, 250), 112, false) == 0);
     }
